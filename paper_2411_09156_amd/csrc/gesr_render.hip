@@ -81,30 +81,76 @@ __device__ __forceinline__ void stage_record(const float* rec, uint32_t vi, floa
     sc = make_float4(c.x, c.y, c.z, -kappa * b.z);
 }
 
-// Adds the opacity, beta and footprint gradient terms of one composited
-// fragment to gr (partial layout: d/du, d/dv, d/dL00, d/dL10, d/dL11, d/do,
-// d/dbeta, d/dr, d/dg, d/db); dLda = dL/dalpha, c2 = -kappa ln2 / 2.  With
-// G = exp(-kappa P), P = q^(beta/2):
-//   dL/do    = dLda G                        (alpha = o G below the cap)
-//   dL/dbeta = dLda o G P (-kappa/2) ln q    = X log2(q) c2,  X = dLda o G P
-//   2 dL/dq  = dLda o G P (-kappa beta) / q  = X rc.w / q
-// and q = t^2 + w^2 with t = L00 dx + L10 dy, w = L11 dy, (dx, dy) = pixel - (u, v).
-__device__ __forceinline__ void add_fragment_grad(const Fragment& f, const float4& ra, const float4& rb,
-                                                  float rcw, float dLda, float alpha_max, float c2,
-                                                  float (&gr)[GESR_PARTIAL_FLOATS]) {
-    if (f.oG > alpha_max) return;  // alpha clamped: no gradient to o, beta or the footprint
-    gr[5] = fmaf(dLda, f.G, gr[5]);
-    if (!(f.q > 1e-30f)) return;   // pixel at the centre: dq/d(geometry) = 0
-    const float X = dLda * f.oG * f.P;
-    gr[6] = fmaf(X * f.l2q, c2, gr[6]);
-    const float d2 = X * rcw * hw_rcp(f.q);
-    const float tq = d2 * f.t, wq = d2 * f.w;
-    gr[0] = fmaf(-tq, ra.z, gr[0]);
-    gr[1] = fmaf(-tq, ra.w, gr[1]);
-    gr[1] = fmaf(-wq, rb.x, gr[1]);
+// One pixel's state of the reverse traversal: transmittance in front of the
+// fragment last visited, upstream gradients (colour; depth and opacity of the
+// extended channels) and D, the dot product of the upstream gradients with
+// what is behind (per unit transmittance).  The upstream gradients are fixed
+// per pixel, so this one number stands for the colour, depth and opacity behind:
+//   dL/dalpha = T (c.g - D),  D <- D + alpha (c.g - D)
+// (four instructions per fragment fewer than with a colour behind, and eight
+// registers fewer over a lane's four pixels).
+struct PixelAdjoint {
+    float T, g0, g1, g2, gD, gA, D;
+};
+
+// Adds one fragment's gradient terms to the splat's raw sums gr.  With
+// G = exp(-kappa P), P = q^(beta/2), X = dL/dalpha G P and s = X / q,
+// q = t^2 + w^2, t = L00 dx + L10 dy, w = L11 dy, (dx, dy) = pixel - (u, v):
+//   gr = (sum s t, sum s w, sum s t dx, sum s t dy, sum s w dy, sum dL/dalpha G,
+//         sum X log2 q, dL/dr, dL/dg, dL/db)
+// The splat's own factors (opacity, -kappa beta, L, -kappa ln2 / 2) are the same
+// for all of a tile's pixels, so they multiply the sums once, in
+// `splat_partial`.  The kernel is bound by these instructions: 40 instead of 53
+// per composited fragment took the one-wave adjoint from 6.0 to 5.4 ms on 3M
+// splats x 16 views at 1920x1080 and from 1.93 to 1.74 ms on 1M flattened
+// splats x 4 views.  f.q may be 0 (then P and X are 0: log2 and 1/q are taken of
+// clamped values, and every term but dL/do is 0).  The alpha cap removes the
+// dependence on opacity and footprint; a fragment below alpha_min has alpha 0
+// here, which leaves T (rcp(1) = 1), D and the sums as they are.
+template <bool EXT>
+__device__ __forceinline__ void add_fragment(const Fragment& f, const float4& rc, float z, const DevSettings& st,
+                                             PixelAdjoint& px, float (&gr)[GESR_PARTIAL_FLOATS], float& gz) {
+    const bool ok = !(f.alpha < st.alpha_min);
+    const float al = ok ? f.alpha : 0.0f;
+    px.T *= hw_rcp(1.0f - al);
+    const float aT = al * px.T;
+    gr[7] = fmaf(aT, px.g0, gr[7]);
+    gr[8] = fmaf(aT, px.g1, gr[8]);
+    gr[9] = fmaf(aT, px.g2, gr[9]);
+    float cg = fmaf(rc.z, px.g2, fmaf(rc.y, px.g1, rc.x * px.g0));
+    if (EXT) {
+        cg = fmaf(z, px.gD, cg) + px.gA;
+        gz = fmaf(aT, px.gD, gz);
+    }
+    const float e = cg - px.D;
+    px.D = fmaf(al, e, px.D);
+    const float dl = ok && !(f.oG > st.alpha_max) ? px.T * e : 0.0f;
+    gr[5] = fmaf(dl, f.G, gr[5]);
+    const float X = dl * f.G * f.P;
+    gr[6] = fmaf(X, fmaxf(f.l2q, -1e30f), gr[6]);
+    const float sx = X * hw_rcp(__builtin_amdgcn_fmed3f(f.q, 1e-30f, 3e38f));
+    const float tq = sx * f.t, wq = sx * f.w;
+    gr[0] += tq;
+    gr[1] += wq;
     gr[2] = fmaf(tq, f.dx, gr[2]);
     gr[3] = fmaf(tq, f.dy, gr[3]);
     gr[4] = fmaf(wq, f.dy, gr[4]);
+}
+
+// The instance's partials (layout: d/du, d/dv, d/dL00, d/dL10, d/dL11, d/do,
+// d/dbeta, d/dr, d/dg, d/db) from the raw sums s and the staged record:
+// 2 dL/dq per unit s is o (-kappa beta) (ra.x.. = u, v, L00, L10; rb = L11, o;
+// rcw = -kappa beta), dL/dbeta = o (-kappa ln2 / 2) sum X log2 q.
+__device__ __forceinline__ void splat_partial(float (&s)[GESR_PARTIAL_FLOATS + 1], const float4& ra, const float4& rb,
+                                              float rcw, float c2) {
+    const float f = rb.y * rcw;
+    const float st = f * s[0], sw = f * s[1];
+    s[0] = -(st * ra.z);
+    s[1] = -fmaf(sw, rb.x, st * ra.w);
+    s[2] *= f;
+    s[3] *= f;
+    s[4] *= f;
+    s[6] *= rb.y * c2;
 }
 
 constexpr uint32_t kNoInstance = 0xFFFFFFFFu;
@@ -227,16 +273,16 @@ __global__ __launch_bounds__(TW * TH) void k_render_bwd(RenderArgs a) {
     const float px = (float)ti.x + 0.5f, py = (float)ti.y + 0.5f;
     const uint32_t lane = __lane_id(), wave = threadIdx.x >> 6;
 
-    float T = 0.f, g0 = 0.f, g1 = 0.f, g2 = 0.f;
+    PixelAdjoint pa{};
     uint32_t nc = 0;
     if (ti.inside) {
-        T = a.final_T[ti.pix];
+        pa.T = a.final_T[ti.pix];
         nc = a.n_contrib[ti.pix];
-        g0 = a.dL_dimage[ti.img];
-        g1 = a.dL_dimage[ti.img + ti.ch];
-        g2 = a.dL_dimage[ti.img + 2 * ti.ch];
+        pa.g0 = a.dL_dimage[ti.img];
+        pa.g1 = a.dL_dimage[ti.img + ti.ch];
+        pa.g2 = a.dL_dimage[ti.img + 2 * ti.ch];
+        pa.D = fmaf(st.bg[2], pa.g2, fmaf(st.bg[1], pa.g1, st.bg[0] * pa.g0));
     }
-    float Br = st.bg[0], Bg = st.bg[1], Bb = st.bg[2];  // colour behind, per unit transmittance
 
     // deepest list position any pixel of the tile composited
     const uint32_t wmax = wave_max_u32(nc);
@@ -272,21 +318,9 @@ __global__ __launch_bounds__(TW * TH) void k_render_bwd(RenderArgs a) {
                 const float q = ges_q(ra, rb.x, px, py, f);
                 if (q <= rb.w) {
                     ges_alpha(q, rb.z, rb.y, st, amax, f);
-                    if (f.alpha >= st.alpha_min) {
-                        act = true;
-                        const float4 rc = sC[j];
-                        const float Tk = T * hw_rcp(1.0f - f.alpha);
-                        const float aT = f.alpha * Tk;
-                        gr[7] = aT * g0;
-                        gr[8] = aT * g1;
-                        gr[9] = aT * g2;
-                        const float dLda = Tk * ((rc.x - Br) * g0 + (rc.y - Bg) * g1 + (rc.z - Bb) * g2);
-                        Br = fmaf(f.alpha, rc.x - Br, Br);
-                        Bg = fmaf(f.alpha, rc.y - Bg, Bg);
-                        Bb = fmaf(f.alpha, rc.z - Bb, Bb);
-                        T = Tk;
-                        add_fragment_grad(f, ra, rb, rc.w, dLda, st.alpha_max, c2, gr);
-                    }
+                    act = true;
+                    float gz = 0.0f;
+                    add_fragment<false>(f, sC[j], 0.0f, st, pa, gr, gz);
                 }
             }
             if (__ballot(act) != 0ull) {
@@ -299,12 +333,13 @@ __global__ __launch_bounds__(TW * TH) void k_render_bwd(RenderArgs a) {
         __syncthreads();
         for (int jj = threadIdx.x; jj < cnt; jj += NT) {
             if (sInst[jj] == kNoInstance) continue;
-            float s[NP];
+            float s[NP + 1];
 #pragma unroll
             for (int k = 0; k < NP; ++k) s[k] = sRed[0][jj][k];
             for (int w = 1; w < NW; ++w)
 #pragma unroll
                 for (int k = 0; k < NP; ++k) s[k] += sRed[w][jj][k];
+            splat_partial(s, sA[jj], sB[jj], sC[jj].w, c2);
             write_partial<false>(a, sInst[jj], s);
         }
         __syncthreads();
@@ -468,32 +503,28 @@ __global__ __launch_bounds__(64) void k_render_bwd_wave16(RenderArgs a) {
 
     // pixel centres: quadrant q adds (q & 1) * 8 and (q >> 1) * 8 to the lane's base
     const float pxb = (float)(tx * 16 + (lane & 7)) + 0.5f, pyb = (float)(ty * 16 + (lane >> 3)) + 0.5f;
-    float T[4], g0[4], g1[4], g2[4], Br[4], Bg[4], Bb[4];
-    float gD[4], gA[4], BD[4], BA[4];  // extended channels: upstream gradients, depth and opacity behind
+    PixelAdjoint pa[4];
     uint32_t nc[4];
     uint32_t mymax = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int x = (int)tx * 16 + (q & 1) * 8 + (int)(lane & 7);
         const int y = (int)ty * 16 + (q >> 1) * 8 + (int)(lane >> 3);
-        Br[q] = st.bg[0];
-        Bg[q] = st.bg[1];
-        Bb[q] = st.bg[2];
-        T[q] = 0.f;
-        g0[q] = g1[q] = g2[q] = 0.f;
-        gD[q] = gA[q] = BD[q] = BA[q] = 0.f;
+        pa[q] = PixelAdjoint{};
         nc[q] = 0;
         if (x < w.W && y < w.H) {
             const uint32_t local = (uint32_t)y * (uint32_t)w.W + (uint32_t)x;
             const uint32_t pix = w.pix_base + local, img = 3u * w.pix_base + local;
-            T[q] = a.final_T[pix];
+            pa[q].T = a.final_T[pix];
             nc[q] = a.n_contrib[pix];
-            g0[q] = a.dL_dimage[img];
-            g1[q] = a.dL_dimage[img + ch];
-            g2[q] = a.dL_dimage[img + 2 * ch];
+            pa[q].g0 = a.dL_dimage[img];
+            pa[q].g1 = a.dL_dimage[img + ch];
+            pa[q].g2 = a.dL_dimage[img + 2 * ch];
+            // the background has no depth and no opacity
+            pa[q].D = fmaf(st.bg[2], pa[q].g2, fmaf(st.bg[1], pa[q].g1, st.bg[0] * pa[q].g0));
             if (EXT) {
-                if (a.dL_ddepth) gD[q] = a.dL_ddepth[pix];
-                if (a.dL_dalpha) gA[q] = a.dL_dalpha[pix];
+                if (a.dL_ddepth) pa[q].gD = a.dL_ddepth[pix];
+                if (a.dL_dalpha) pa[q].gA = a.dL_dalpha[pix];
             }
         }
         mymax = max(mymax, nc[q]);
@@ -536,43 +567,8 @@ __global__ __launch_bounds__(64) void k_render_bwd_wave16(RenderArgs a) {
                 // decisions are selects (a zeroed term leaves the sums as they
                 // are), so the wave takes one branch per quadrant.
                 ges_alpha(qq, rb.z, rb.y, st, amax, f);
-                const bool ok = !(f.alpha < st.alpha_min);
-                act = act || ok;
-                // a skipped fragment has alpha 0 here: it leaves T (rcp(1) = 1), the
-                // colour behind and the sums as they are
-                const float al = ok ? f.alpha : 0.0f;
-                const float Tk = T[q] * hw_rcp(1.0f - al);
-                const float aT = al * Tk;
-                gr[7] += aT * g0[q];
-                gr[8] += aT * g1[q];
-                gr[9] += aT * g2[q];
-                float dLda = Tk * ((rc.x - Br[q]) * g0[q] + (rc.y - Bg[q]) * g1[q] + (rc.z - Bb[q]) * g2[q]);
-                Br[q] = fmaf(al, rc.x - Br[q], Br[q]);
-                Bg[q] = fmaf(al, rc.y - Bg[q], Bg[q]);
-                Bb[q] = fmaf(al, rc.z - Bb[q], Bb[q]);
-                if (EXT) {
-                    dLda += Tk * ((z - BD[q]) * gD[q] + (1.0f - BA[q]) * gA[q]);
-                    gz += aT * gD[q];
-                    BD[q] = fmaf(al, z - BD[q], BD[q]);
-                    BA[q] = fmaf(al, 1.0f - BA[q], BA[q]);
-                }
-                T[q] = Tk;
-                // add_fragment_grad with its two early exits as selects
-                const bool live = ok && !(f.oG > st.alpha_max);
-                const float dl = live ? dLda : 0.0f;
-                gr[5] = fmaf(dl, f.G, gr[5]);
-                const bool geo = live && f.q > 1e-30f;
-                const float X = geo ? dl * f.oG * f.P : 0.0f;
-                const float lq = geo ? f.l2q : 0.0f;
-                gr[6] = fmaf(X * lq, c2, gr[6]);
-                const float d2 = X * rc.w * hw_rcp(geo ? f.q : 1.0f);
-                const float tq = d2 * f.t, wq = d2 * f.w;
-                gr[0] = fmaf(-tq, ra.z, gr[0]);
-                gr[1] = fmaf(-tq, ra.w, gr[1]);
-                gr[1] = fmaf(-wq, rb.x, gr[1]);
-                gr[2] = fmaf(tq, f.dx, gr[2]);
-                gr[3] = fmaf(tq, f.dy, gr[3]);
-                gr[4] = fmaf(wq, f.dy, gr[4]);
+                act = true;
+                add_fragment<EXT>(f, rc, z, st, pa[q], gr, gz);
             }
             if (__ballot(act) != 0ull) {
                 const float tot = wave_sum10(gr, lane);
@@ -586,7 +582,13 @@ __global__ __launch_bounds__(64) void k_render_bwd_wave16(RenderArgs a) {
             }
         }
         __syncthreads();
-        if ((int)lane < cnt && sInst[lane] != kNoInstance) write_partial<EXT>(a, sInst[lane], sRed[lane]);
+        if ((int)lane < cnt && sInst[lane] != kNoInstance) {
+            float s[NP + 1];
+#pragma unroll
+            for (int k = 0; k <= NP; ++k) s[k] = EXT || k < NP ? sRed[lane][k] : 0.0f;
+            splat_partial(s, sA[lane], sB[lane], sC[lane].w, c2);
+            write_partial<EXT>(a, sInst[lane], s);
+        }
         __syncthreads();
         hi = lo;
     }

@@ -44,6 +44,15 @@ __device__ __forceinline__ float hw_log2(float x) { return __builtin_amdgcn_logf
 __device__ __forceinline__ float hw_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float hw_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
+// a b with 0 times anything = 0 (v_mul_legacy_f32; otherwise the rounded product).
+// `trans` operands may come straight from a transcendental instruction, whose
+// result needs one wait state before another vector instruction reads it.
+__device__ __forceinline__ float mul_legacy(float a, float trans) {
+    float r;
+    asm("s_nop 0\n\tv_mul_legacy_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(trans));
+    return r;
+}
+
 // Index of the view that owns global tile `t` (views are few; linear scan).
 __device__ __forceinline__ int view_of_tile(const DevCams& c, uint32_t t) {
     int v = 0;
@@ -72,14 +81,26 @@ __device__ __forceinline__ float ges_q(const float4& a, float L11, float px, flo
 // alpha = min(opacity G, alpha_max) as one median-of-three: opacity G >= 0, so
 // med3(opacity G, 0, alpha_max) is that minimum (and needs no NaN quieting of
 // the kernel argument per fragment, as a min would).
-__device__ __forceinline__ void ges_alpha(float q, float half_beta, float opacity, const DevSettings& st,
+__device__ __forceinline__ void ges_alpha(float q, float half_beta, float opacity, float neg_kappa_log2e,
                                           float alpha_max, Fragment& f) {
     f.q = q;
     f.l2q = hw_log2(q);                    // -inf at q = 0
     f.P = hw_exp2(half_beta * f.l2q);      // q^(beta/2); 0 at q = 0
-    f.G = hw_exp2(st.neg_kappa_log2e * f.P);
+    f.G = hw_exp2(neg_kappa_log2e * f.P);
     f.oG = opacity * f.G;
     f.alpha = __builtin_amdgcn_fmed3f(f.oG, 0.0f, alpha_max);
+}
+
+// A wave-uniform value kept in a vector register: on gfx950 a float32 multiply,
+// add or multiply-add takes 2.3 cycles per wave with vector operands and 4.3 with
+// a scalar one.
+__device__ __forceinline__ float in_vgpr(float x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+__device__ __forceinline__ uint32_t in_vgpr(uint32_t x) {
+    asm volatile("" : "+v"(x));
+    return x;
 }
 
 // A zero the compiler cannot treat as a constant.  Accumulators that start

@@ -82,34 +82,32 @@ __device__ __forceinline__ void stage_record(const float* rec, uint32_t vi, floa
 }
 
 // One pixel's state of the reverse traversal: transmittance in front of the
-// fragment last visited, upstream gradients (colour; depth and opacity of the
-// extended channels) and D, the dot product of the upstream gradients with
-// what is behind (per unit transmittance).  The upstream gradients are fixed
-// per pixel, so this one number stands for the colour, depth and opacity behind:
-//   dL/dalpha = T (c.g - D),  D <- D + alpha (c.g - D)
-// (four instructions per fragment fewer than with a colour behind, and eight
-// registers fewer over a lane's four pixels).
+// fragment last visited, upstream gradients, and what lies behind per unit
+// transmittance (colour; depth and opacity with the extended channels).
 struct PixelAdjoint {
-    float T, g0, g1, g2, gD, gA, D;
+    float T, g0, g1, g2, Br, Bg, Bb, gD, gA, BD, BA;
 };
 
-// Adds one fragment's gradient terms to the splat's raw sums gr.  With
-// G = exp(-kappa P), P = q^(beta/2), X = dL/dalpha G P and s = X / q,
-// q = t^2 + w^2, t = L00 dx + L10 dy, w = L11 dy, (dx, dy) = pixel - (u, v):
-//   gr = (sum s t, sum s w, sum s t dx, sum s t dy, sum s w dy, sum dL/dalpha G,
-//         sum X log2 q, dL/dr, dL/dg, dL/db)
-// The splat's own factors (opacity, -kappa beta, L, -kappa ln2 / 2) are the same
-// for all of a tile's pixels, so they multiply the sums once, in
-// `splat_partial`.  The kernel is bound by these instructions: 40 instead of 53
-// per composited fragment took the one-wave adjoint from 6.0 to 5.4 ms on 3M
-// splats x 16 views at 1920x1080 and from 1.93 to 1.74 ms on 1M flattened
-// splats x 4 views.  f.q may be 0 (then P and X are 0: log2 and 1/q are taken of
-// clamped values, and every term but dL/do is 0).  The alpha cap removes the
-// dependence on opacity and footprint; a fragment below alpha_min has alpha 0
-// here, which leaves T (rcp(1) = 1), D and the sums as they are.
+// Adds one fragment's gradient terms to the splat's sums gr.  With
+// G = exp(-kappa P), P = q^(beta/2), X = dL/dalpha o G P and d = -kappa beta X / q
+// = 2 dL/dq, q = t^2 + w^2, t = L00 dx + L10 dy, w = L11 dy, (dx, dy) = pixel - (u, v):
+//   gr = (sum d t, sum d w, sum d t dx, sum d t dy, sum d w dy, sum dL/dalpha G,
+//         sum X ln q (-kappa / 2), dL/dr, dL/dg, dL/db)
+// The conic factor is the same for all of a tile's pixels, so the centre's
+// gradient takes it once, in `splat_partial`.  At q = 0 the footprint and beta terms
+// are 0: P and X are, and the legacy product takes 0 times infinity as 0.  The
+// alpha cap removes the dependence on opacity and footprint; a fragment below
+// alpha_min has alpha 0 here, which leaves T (rcp(1) = 1), what lies behind and the
+// sums as they are.  A flat splat seen edge-on amplifies the rounding of the three
+// footprint sums in its scale gradient, so their terms keep this order of products.
+// The kernel is bound by these instructions: the products in place of selects and
+// the two sums for the centre took 53 instructions to 47 (a compare or select
+// takes 4.3 cycles per wave on gfx950, a product 2.3), a step over 3M splats x 16
+// views from 20.2 to 19.7 ms and over 1M flat splats x 4 views from 5.00 to 4.90 ms.
 template <bool EXT>
 __device__ __forceinline__ void add_fragment(const Fragment& f, const float4& rc, float z, const DevSettings& st,
-                                             PixelAdjoint& px, float (&gr)[GESR_PARTIAL_FLOATS], float& gz) {
+                                             float c2, PixelAdjoint& px, float (&gr)[GESR_PARTIAL_FLOATS],
+                                             float& gz) {
     const bool ok = !(f.alpha < st.alpha_min);
     const float al = ok ? f.alpha : 0.0f;
     px.T *= hw_rcp(1.0f - al);
@@ -117,19 +115,24 @@ __device__ __forceinline__ void add_fragment(const Fragment& f, const float4& rc
     gr[7] = fmaf(aT, px.g0, gr[7]);
     gr[8] = fmaf(aT, px.g1, gr[8]);
     gr[9] = fmaf(aT, px.g2, gr[9]);
-    float cg = fmaf(rc.z, px.g2, fmaf(rc.y, px.g1, rc.x * px.g0));
+    const float er = rc.x - px.Br, eg = rc.y - px.Bg, eb = rc.z - px.Bb;
+    float dLda = px.T * fmaf(eb, px.g2, fmaf(er, px.g0, eg * px.g1));
+    px.Br = fmaf(al, er, px.Br);
+    px.Bg = fmaf(al, eg, px.Bg);
+    px.Bb = fmaf(al, eb, px.Bb);
     if (EXT) {
-        cg = fmaf(z, px.gD, cg) + px.gA;
+        const float ed = z - px.BD, ea = 1.0f - px.BA;
+        dLda = fmaf(px.T, fmaf(ed, px.gD, ea * px.gA), dLda);
         gz = fmaf(aT, px.gD, gz);
+        px.BD = fmaf(al, ed, px.BD);
+        px.BA = fmaf(al, ea, px.BA);
     }
-    const float e = cg - px.D;
-    px.D = fmaf(al, e, px.D);
-    const float dl = ok && !(f.oG > st.alpha_max) ? px.T * e : 0.0f;
+    const float dl = ok && !(f.oG > st.alpha_max) ? dLda : 0.0f;
     gr[5] = fmaf(dl, f.G, gr[5]);
-    const float X = dl * f.G * f.P;
-    gr[6] = fmaf(X, fmaxf(f.l2q, -1e30f), gr[6]);
-    const float sx = X * hw_rcp(__builtin_amdgcn_fmed3f(f.q, 1e-30f, 3e38f));
-    const float tq = sx * f.t, wq = sx * f.w;
+    const float X = dl * f.oG * f.P;
+    gr[6] = fmaf(mul_legacy(X, f.l2q), c2, gr[6]);
+    const float d = mul_legacy(X * rc.w, hw_rcp(f.q));
+    const float tq = d * f.t, wq = d * f.w;
     gr[0] += tq;
     gr[1] += wq;
     gr[2] = fmaf(tq, f.dx, gr[2]);
@@ -138,19 +141,12 @@ __device__ __forceinline__ void add_fragment(const Fragment& f, const float4& rc
 }
 
 // The instance's partials (layout: d/du, d/dv, d/dL00, d/dL10, d/dL11, d/do,
-// d/dbeta, d/dr, d/dg, d/db) from the raw sums s and the staged record:
-// 2 dL/dq per unit s is o (-kappa beta) (ra.x.. = u, v, L00, L10; rb = L11, o;
-// rcw = -kappa beta), dL/dbeta = o (-kappa ln2 / 2) sum X log2 q.
-__device__ __forceinline__ void splat_partial(float (&s)[GESR_PARTIAL_FLOATS + 1], const float4& ra, const float4& rb,
-                                              float rcw, float c2) {
-    const float f = rb.y * rcw;
-    const float st = f * s[0], sw = f * s[1];
+// d/dbeta, d/dr, d/dg, d/db) from the sums s and the staged record (ra = u, v,
+// L00, L10; rb.x = L11).
+__device__ __forceinline__ void splat_partial(float (&s)[GESR_PARTIAL_FLOATS + 1], const float4& ra, const float4& rb) {
+    const float st = s[0], sw = s[1];
     s[0] = -(st * ra.z);
     s[1] = -fmaf(sw, rb.x, st * ra.w);
-    s[2] *= f;
-    s[3] *= f;
-    s[4] *= f;
-    s[6] *= rb.y * c2;
 }
 
 constexpr uint32_t kNoInstance = 0xFFFFFFFFu;
@@ -193,7 +189,7 @@ __global__ __launch_bounds__(TW * TH) void k_render_fwd(RenderArgs a) {
     const uint32_t t = a.worklist[blockIdx.x];
     const TileInfo ti = tile_info<TW, TH>(a, t);
     const DevSettings& st = a.st;
-    const float amax = st.alpha_max;
+    const float amax = st.alpha_max, nk = in_vgpr(st.neg_kappa_log2e);
     const float px = (float)ti.x + 0.5f, py = (float)ti.y + 0.5f;
 
     float T = 1.0f, cr = 0.f, cg = 0.f, cb = 0.f;
@@ -217,7 +213,7 @@ __global__ __launch_bounds__(TW * TH) void k_render_fwd(RenderArgs a) {
                 const float q = ges_q(ra, rb.x, px, py, f);
                 if (COUNT) ++listed;
                 if (q > rb.w) continue;  // beyond the alpha_min footprint
-                ges_alpha(q, rb.z, rb.y, st, amax, f);
+                ges_alpha(q, rb.z, rb.y, nk, amax, f);
                 if (f.alpha < st.alpha_min) continue;
                 if (COUNT) ++hit;
                 const float Tn = T * (1.0f - f.alpha);
@@ -268,12 +264,15 @@ __global__ __launch_bounds__(TW * TH) void k_render_bwd(RenderArgs a) {
     const uint32_t t = a.worklist[blockIdx.x];
     const TileInfo ti = tile_info<TW, TH>(a, t);
     const DevSettings& st = a.st;
-    const float amax = st.alpha_max;
+    const float amax = st.alpha_max, nk = in_vgpr(st.neg_kappa_log2e);
     const float c2 = -0.5f * kLn2 * st.kappa;
     const float px = (float)ti.x + 0.5f, py = (float)ti.y + 0.5f;
     const uint32_t lane = __lane_id(), wave = threadIdx.x >> 6;
 
     PixelAdjoint pa{};
+    pa.Br = st.bg[0];
+    pa.Bg = st.bg[1];
+    pa.Bb = st.bg[2];
     uint32_t nc = 0;
     if (ti.inside) {
         pa.T = a.final_T[ti.pix];
@@ -281,7 +280,6 @@ __global__ __launch_bounds__(TW * TH) void k_render_bwd(RenderArgs a) {
         pa.g0 = a.dL_dimage[ti.img];
         pa.g1 = a.dL_dimage[ti.img + ti.ch];
         pa.g2 = a.dL_dimage[ti.img + 2 * ti.ch];
-        pa.D = fmaf(st.bg[2], pa.g2, fmaf(st.bg[1], pa.g1, st.bg[0] * pa.g0));
     }
 
     // deepest list position any pixel of the tile composited
@@ -317,10 +315,10 @@ __global__ __launch_bounds__(TW * TH) void k_render_bwd(RenderArgs a) {
                 Fragment f;
                 const float q = ges_q(ra, rb.x, px, py, f);
                 if (q <= rb.w) {
-                    ges_alpha(q, rb.z, rb.y, st, amax, f);
+                    ges_alpha(q, rb.z, rb.y, nk, amax, f);
                     act = true;
                     float gz = 0.0f;
-                    add_fragment<false>(f, sC[j], 0.0f, st, pa, gr, gz);
+                    add_fragment<false>(f, sC[j], 0.0f, st, c2, pa, gr, gz);
                 }
             }
             if (__ballot(act) != 0ull) {
@@ -339,7 +337,7 @@ __global__ __launch_bounds__(TW * TH) void k_render_bwd(RenderArgs a) {
             for (int w = 1; w < NW; ++w)
 #pragma unroll
                 for (int k = 0; k < NP; ++k) s[k] += sRed[w][jj][k];
-            splat_partial(s, sA[jj], sB[jj], sC[jj].w, c2);
+            splat_partial(s, sA[jj], sB[jj]);
             write_partial<false>(a, sInst[jj], s);
         }
         __syncthreads();
@@ -357,7 +355,7 @@ __global__ __launch_bounds__(64) void k_render_fwd_wave16(RenderArgs a) {
     __shared__ float4 sA[B], sB[B], sC[B];
     const uint32_t t = a.worklist[blockIdx.x];
     const DevSettings& st = a.st;
-    const float amax = st.alpha_max;
+    const float amax = st.alpha_max, nk = in_vgpr(st.neg_kappa_log2e);
     const uint32_t lane = __lane_id();
     const int v = view_of_tile(a.cams, t);
     const DevView& w = a.cams.v[v];
@@ -425,7 +423,7 @@ __global__ __launch_bounds__(64) void k_render_fwd_wave16(RenderArgs a) {
                 // state changing only where the fragment composites (a zero
                 // weight leaves the sums as they are: colours and depths of
                 // kept records are finite and non-negative).
-                ges_alpha(qq, rb.z, rb.y, st, amax, f);
+                ges_alpha(qq, rb.z, rb.y, nk, amax, f);
                 const bool ok = !(f.alpha < st.alpha_min);
                 if (COUNT) hit[q] += ok ? 1u : 0u;
                 const float Tn = T[q] * (1.0f - f.alpha);
@@ -490,7 +488,7 @@ __global__ __launch_bounds__(64) void k_render_bwd_wave16(RenderArgs a) {
 
     const uint32_t t = a.worklist[blockIdx.x];
     const DevSettings& st = a.st;
-    const float amax = st.alpha_max;
+    const float amax = st.alpha_max, nk = in_vgpr(st.neg_kappa_log2e);
     const float c2 = -0.5f * kLn2 * st.kappa;
     const uint32_t lane = __lane_id();
     const int v = view_of_tile(a.cams, t);
@@ -510,7 +508,10 @@ __global__ __launch_bounds__(64) void k_render_bwd_wave16(RenderArgs a) {
     for (int q = 0; q < 4; ++q) {
         const int x = (int)tx * 16 + (q & 1) * 8 + (int)(lane & 7);
         const int y = (int)ty * 16 + (q >> 1) * 8 + (int)(lane >> 3);
-        pa[q] = PixelAdjoint{};
+        pa[q] = PixelAdjoint{};  // the background has no depth and no opacity
+        pa[q].Br = st.bg[0];
+        pa[q].Bg = st.bg[1];
+        pa[q].Bb = st.bg[2];
         nc[q] = 0;
         if (x < w.W && y < w.H) {
             const uint32_t local = (uint32_t)y * (uint32_t)w.W + (uint32_t)x;
@@ -520,8 +521,6 @@ __global__ __launch_bounds__(64) void k_render_bwd_wave16(RenderArgs a) {
             pa[q].g0 = a.dL_dimage[img];
             pa[q].g1 = a.dL_dimage[img + ch];
             pa[q].g2 = a.dL_dimage[img + 2 * ch];
-            // the background has no depth and no opacity
-            pa[q].D = fmaf(st.bg[2], pa[q].g2, fmaf(st.bg[1], pa[q].g1, st.bg[0] * pa[q].g0));
             if (EXT) {
                 if (a.dL_ddepth) pa[q].gD = a.dL_ddepth[pix];
                 if (a.dL_dalpha) pa[q].gA = a.dL_dalpha[pix];
@@ -566,9 +565,9 @@ __global__ __launch_bounds__(64) void k_render_bwd_wave16(RenderArgs a) {
                 // the alpha cap and a centred pixel are rarer still: those
                 // decisions are selects (a zeroed term leaves the sums as they
                 // are), so the wave takes one branch per quadrant.
-                ges_alpha(qq, rb.z, rb.y, st, amax, f);
+                ges_alpha(qq, rb.z, rb.y, nk, amax, f);
                 act = true;
-                add_fragment<EXT>(f, rc, z, st, pa[q], gr, gz);
+                add_fragment<EXT>(f, rc, z, st, c2, pa[q], gr, gz);
             }
             if (__ballot(act) != 0ull) {
                 const float tot = wave_sum10(gr, lane);
@@ -586,7 +585,7 @@ __global__ __launch_bounds__(64) void k_render_bwd_wave16(RenderArgs a) {
             float s[NP + 1];
 #pragma unroll
             for (int k = 0; k <= NP; ++k) s[k] = EXT || k < NP ? sRed[lane][k] : 0.0f;
-            splat_partial(s, sA[lane], sB[lane], sC[lane].w, c2);
+            splat_partial(s, sA[lane], sB[lane]);
             write_partial<EXT>(a, sInst[lane], s);
         }
         __syncthreads();

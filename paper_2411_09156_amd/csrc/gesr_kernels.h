@@ -49,6 +49,7 @@ struct RenderArgs {
     const uint32_t* worklist;
     const uint32_t* inst_base;
     uint32_t n_items;  // number of work items (tiles) in the worklist
+    uint32_t n_split;  // 16x16 renderers: leading worklist tiles that take a workgroup each (set by the launchers)
     int batch;         // records staged in LDS per round (one-wave renderers: 32 or 64)
     uint32_t* tile_work;  // forward: list positions each tile evaluated (nullable)
     // forward outputs / backward inputs

@@ -5,7 +5,7 @@
 // space).  One workgroup per (view, tile) work item, taken in worklist order
 // (most work first: the list length, or the positions a previous forward
 // evaluated per tile, so the hardware dispatcher schedules greedily by
-// load); each wave covers an 8x8 pixel block so lanes of a wave see similar
+// load); a wave's lanes cover 8x8 pixel blocks so that they see similar
 // footprints.  Splat records are staged through LDS in batches and every lane
 // reads them by broadcast.
 //
@@ -345,15 +345,62 @@ __global__ __launch_bounds__(TW * TH) void k_render_bwd(RenderArgs a) {
     }
 }
 
-// Forward, one wave per 16x16 tile with 4 pixels per lane (one per 8x8
+// Orders a wave's LDS writes before its own later reads of other lanes' data
+// (the waves of a workgroup run different tiles: no workgroup barrier).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One pixel of the forward traversal.  A terminated pixel (and one outside the
+// image) keeps its transmittance with the sign bit set: the sign then fails the
+// termination test of every later fragment, so no separate flag is carried.
+struct FwdPixel {
+    float T, r, g, b, d;
+    uint32_t contrib;
+};
+
+// Composites one fragment; alpha is 0 where it is skipped (T and the sums then stay
+// as they are: colours and depths of kept records are finite and non-negative).
+template <bool EXT>
+__device__ __forceinline__ void blend(FwdPixel& p, float alpha, bool ok, const float4& rc, float z, uint32_t pos,
+                                      float t_min) {
+    const float Tn = p.T * (1.0f - alpha);
+    const bool keep = !(Tn < t_min);
+    const float wgt = keep ? alpha * p.T : 0.0f;
+    p.r = fmaf(rc.x, wgt, p.r);
+    p.g = fmaf(rc.y, wgt, p.g);
+    p.b = fmaf(rc.z, wgt, p.b);
+    if (EXT) p.d = fmaf(z, wgt, p.d);
+    p.contrib = ok && keep ? pos : p.contrib;
+    p.T = keep ? Tn : -fabsf(p.T);
+}
+
+template <bool EXT>
+__device__ __forceinline__ void write_pixel(const RenderArgs& a, const DevView& w, int x, int y, const FwdPixel& p) {
+    const uint32_t ch = (uint32_t)w.W * (uint32_t)w.H;
+    const uint32_t local = (uint32_t)y * (uint32_t)w.W + (uint32_t)x;
+    const uint32_t pix = w.pix_base + local, img = 3u * w.pix_base + local;
+    const float T = fabsf(p.T);
+    a.image[img] = fmaf(T, a.st.bg[0], p.r);
+    a.image[img + ch] = fmaf(T, a.st.bg[1], p.g);
+    a.image[img + 2 * ch] = fmaf(T, a.st.bg[2], p.b);
+    a.final_T[pix] = T;
+    a.n_contrib[pix] = p.contrib;
+    if (EXT) {
+        if (a.out_depth) a.out_depth[pix] = p.d;
+        if (a.out_alpha) a.out_alpha[pix] = 1.0f - T;
+    }
+}
+
+// Forward of one 16x16 tile by one wave with 4 pixels per lane (one per 8x8
 // quadrant): a staged splat's LDS reads serve 256 pixels; the wave leaves the
-// tile once all its pixels have terminated.
+// tile once all its pixels have terminated.  sA, sB, sC: the wave's stage.
 // EXT: also the extended channels (depth composited over zero, alpha = 1 - T).
 template <bool COUNT, int B, bool EXT>
-__global__ __launch_bounds__(64) void k_render_fwd_wave16(RenderArgs a) {
+__device__ __forceinline__ void fwd_wave_tile(const RenderArgs& a, uint32_t t, float4* sA, float4* sB, float4* sC) {
     static_assert(B >= 1 && B <= 64, "one staged record per lane");
-    __shared__ float4 sA[B], sB[B], sC[B];
-    const uint32_t t = a.worklist[blockIdx.x];
     const DevSettings& st = a.st;
     const float amax = st.alpha_max, nk = in_vgpr(st.neg_kappa_log2e);
     const uint32_t lane = __lane_id();
@@ -364,20 +411,15 @@ __global__ __launch_bounds__(64) void k_render_fwd_wave16(RenderArgs a) {
     const uint2 rg = reinterpret_cast<const uint2*>(a.ranges)[t];
     const uint32_t r0 = rg.x, r1 = rg.y;
 
-    float px[4], py[4], T[4], cr[4], cg[4], cb[4], cd[4];
-    uint32_t contrib[4], listed[4], hit[4];
-    bool done[4], inside[4];
+    const int x0 = (int)tx * 16 + (int)(lane & 7), y0 = (int)ty * 16 + (int)(lane >> 3);
+    const float pxb = (float)x0 + 0.5f, pyb = (float)y0 + 0.5f;
+    FwdPixel p[4];
+    uint32_t listed[4], hit[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int x = (int)tx * 16 + (q & 1) * 8 + (int)(lane & 7);
-        const int y = (int)ty * 16 + (q >> 1) * 8 + (int)(lane >> 3);
-        px[q] = (float)x + 0.5f;
-        py[q] = (float)y + 0.5f;
-        T[q] = 1.0f;
-        cr[q] = cg[q] = cb[q] = cd[q] = 0.f;
-        contrib[q] = listed[q] = hit[q] = 0;
-        inside[q] = x < w.W && y < w.H;
-        done[q] = !inside[q];
+        const int x = x0 + (q & 1) * 8, y = y0 + (q >> 1) * 8;
+        p[q] = FwdPixel{x < w.W && y < w.H ? 1.0f : -1.0f, 0.f, 0.f, 0.f, 0.f, 0u};
+        listed[q] = hit[q] = 0;
     }
     // the next batch's records are loaded into registers while the current
     // batch is rendered from LDS
@@ -394,8 +436,7 @@ __global__ __launch_bounds__(64) void k_render_fwd_wave16(RenderArgs a) {
     fetch(r0);
     uint32_t stop = r1;  // first list position not evaluated
     for (uint32_t base = r0; base < r1; base += B) {
-        const bool all_done = done[0] && done[1] && done[2] && done[3];
-        if (__ballot(!all_done) == 0ull) {
+        if (__ballot(fmaxf(fmaxf(p[0].T, p[1].T), fmaxf(p[2].T, p[3].T)) > 0.0f) == 0ull) {
             stop = base;
             break;
         }
@@ -404,66 +445,188 @@ __global__ __launch_bounds__(64) void k_render_fwd_wave16(RenderArgs a) {
             sB[lane] = make_float4(nb.x, nb.y, 0.5f * nb.z, nb.w);
             sC[lane] = nc;
         }
-        __syncthreads();
+        wave_lds_sync();
         if (base + B < r1) fetch(base + B);
-        const int cnt = (int)min<uint32_t>(B, r1 - base);
+        const int cnt = (int)__builtin_amdgcn_readfirstlane(min<uint32_t>(B, r1 - base));
+        uint32_t pos = in_vgpr(base - r0);
         for (int j = 0; j < cnt; ++j) {
             const float4 ra = sA[j];
             const float4 rb = sB[j];
             const float4 rc = sC[j];
+            ++pos;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                if (done[q]) continue;
                 Fragment f;
-                const float qq = ges_q(ra, rb.x, px[q], py[q], f);
-                if (COUNT) ++listed[q];
-                if (qq > rb.w) continue;  // beyond the alpha_min footprint
-                // Inside the footprint alpha almost never falls below alpha_min
-                // and a pixel terminates once: both decisions are selects, the
-                // state changing only where the fragment composites (a zero
-                // weight leaves the sums as they are: colours and depths of
-                // kept records are finite and non-negative).
+                const float qq = ges_q(ra, rb.x, pxb + (float)((q & 1) * 8), pyb + (float)((q >> 1) * 8), f);
+                const bool on = p[q].T > 0.0f;
+                if (COUNT) listed[q] += on ? 1u : 0u;
+                // Beyond the alpha_min footprint or terminated.  Inside it alpha
+                // almost never falls below alpha_min and a pixel terminates once:
+                // both decisions are selects, one branch per quadrant.
+                if (!((int)on & (int)!(qq > rb.w))) continue;
                 ges_alpha(qq, rb.z, rb.y, nk, amax, f);
                 const bool ok = !(f.alpha < st.alpha_min);
                 if (COUNT) hit[q] += ok ? 1u : 0u;
-                const float Tn = T[q] * (1.0f - f.alpha);
-                const bool stop = ok && Tn < st.t_min;
-                const bool acc = ok && !stop;
-                done[q] = stop;
-                const float wgt = acc ? f.alpha * T[q] : 0.0f;
-                cr[q] = fmaf(rc.x, wgt, cr[q]);
-                cg[q] = fmaf(rc.y, wgt, cg[q]);
-                cb[q] = fmaf(rc.z, wgt, cb[q]);
-                if (EXT) cd[q] = fmaf(rc.w, wgt, cd[q]);  // rc.w: the splat's depth
-                T[q] = acc ? Tn : T[q];
-                contrib[q] = acc ? base + (uint32_t)j + 1u - r0 : contrib[q];
+                blend<EXT>(p[q], ok ? f.alpha : 0.0f, ok, rc, rc.w, pos, st.t_min);
             }
         }
-        __syncthreads();
+        wave_lds_sync();
     }
     if (a.tile_work && lane == 0) a.tile_work[t] = stop - r0;
-    const uint32_t ch = (uint32_t)w.W * (uint32_t)w.H;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        if (!inside[q]) continue;
-        const int x = (int)tx * 16 + (q & 1) * 8 + (int)(lane & 7);
-        const int y = (int)ty * 16 + (q >> 1) * 8 + (int)(lane >> 3);
-        const uint32_t local = (uint32_t)y * (uint32_t)w.W + (uint32_t)x;
-        const uint32_t pix = w.pix_base + local, img = 3u * w.pix_base + local;
-        a.image[img] = fmaf(T[q], st.bg[0], cr[q]);
-        a.image[img + ch] = fmaf(T[q], st.bg[1], cg[q]);
-        a.image[img + 2 * ch] = fmaf(T[q], st.bg[2], cb[q]);
-        a.final_T[pix] = T[q];
-        a.n_contrib[pix] = contrib[q];
+        const int x = x0 + (q & 1) * 8, y = y0 + (q >> 1) * 8;
+        if (x >= w.W || y >= w.H) continue;
+        write_pixel<EXT>(a, w, x, y, p[q]);
         if (COUNT) {
+            const uint32_t pix = w.pix_base + (uint32_t)y * (uint32_t)w.W + (uint32_t)x;
             a.n_listed[pix] = listed[q];
             a.n_hit[pix] = hit[q];
         }
-        if (EXT) {
-            if (a.out_depth) a.out_depth[pix] = cd[q];
-            if (a.out_alpha) a.out_alpha[pix] = 1.0f - T[q];
-        }
     }
+}
+
+// Whether no pixel centre (u + dx, v + dy), dx in [dx0, dx1], dy in [dy0, dy1],
+// can pass the footprint test q <= qmax of record (a, b).  Conservative: the
+// ellipse is widened by 1% in q (the renderers' float32 q is off by at most
+// u (12 + 8 s) relative, s = |L10| / L11; at s <= 4096 that and the rounding of
+// the extents below stay under half of it), the ends by 1e-3 px, and anything
+// not finite or more sheared keeps the record.  dx0.. are the renderers' own
+// rounded differences.  Over the band of dy the ellipse's right end
+// (-L10 dy + sqrt(Q - (L11 dy)^2)) / L00 is largest at its rightmost point
+// clamped into the band (the left end mirrors it).
+__device__ __forceinline__ bool quad_misses(const float4& a, const float4& b, float dx0, float dx1, float dy0,
+                                            float dy1) {
+    const float l00 = a.z, l10 = a.w, l11 = b.x;
+    const float Q = b.w * 1.01f;
+    const float sq = __builtin_amdgcn_sqrtf(Q);
+    const float rr = __builtin_amdgcn_sqrtf(l10 * l10 + l11 * l11);
+    const float il11 = hw_rcp(l11), il00 = hw_rcp(l00);
+    const float ym = sq * il11 + 1e-3f;
+    const float dyr = -(l10 * sq) * il11 * hw_rcp(rr);  // dy of the rightmost point
+    const float lo = fmaxf(dy0, -ym), hi = fminf(dy1, ym);
+    const float tr = fminf(fmaxf(dyr, lo), hi), tl = fminf(fmaxf(-dyr, lo), hi);
+    const float wr = l11 * tr, wl = l11 * tl;
+    const float xr = (__builtin_amdgcn_sqrtf(fmaxf(Q - wr * wr, 0.f)) - l10 * tr) * il00 + 1e-3f;
+    const float xl = (-__builtin_amdgcn_sqrtf(fmaxf(Q - wl * wl, 0.f)) - l10 * tl) * il00 - 1e-3f;
+    const bool sound = fabsf(l10) <= 4096.f * l11 && fabsf(dyr) < 1e30f && Q < 1e30f;
+    return sound && (lo > hi || dx0 > xr || dx1 < xl);
+}
+
+// Forward of one 16x16 tile by the four waves of a workgroup, one 8x8 quadrant
+// each (one pixel per lane, no barrier in the list loop).  A wave stages only
+// the records that can reach its quadrant and takes them two at a time: their
+// falloffs are independent chains, so a tile with a long list is bound by
+// far shorter steps than with one wave per tile.  sa, sb, sc: the wave's stage of
+// 65 records (an odd count is padded with a record that no pixel passes).
+template <bool EXT>
+__device__ __forceinline__ void fwd_quad_tile(const RenderArgs& a, uint32_t t, uint32_t wave, float4* sa, float4* sb,
+                                              float4* sc, float* sz, uint32_t* s_stop) {
+    const DevSettings& st = a.st;
+    const float amax = st.alpha_max, amin = st.alpha_min, tmin = st.t_min, nk = in_vgpr(st.neg_kappa_log2e);
+    const uint32_t lane = __lane_id();
+    const int v = view_of_tile(a.cams, t);
+    const DevView& w = a.cams.v[v];
+    const uint32_t lt = t - w.tile_base;
+    const uint32_t tx = lt % (uint32_t)w.tiles_x, ty = lt / (uint32_t)w.tiles_x;
+    const uint2 rg = reinterpret_cast<const uint2*>(a.ranges)[t];
+    const uint32_t r0 = rg.x, r1 = rg.y;
+    const int qx = (int)tx * 16 + (int)(wave & 1) * 8, qy = (int)ty * 16 + (int)(wave >> 1) * 8;
+    const int x = qx + (int)(lane & 7), y = qy + (int)(lane >> 3);
+    const bool inside = x < w.W && y < w.H;
+    const float px = (float)x + 0.5f, py = (float)y + 0.5f;
+    const float qx0 = (float)qx + 0.5f, qx1 = qx0 + 7.0f, qy0 = (float)qy + 0.5f, qy1 = qy0 + 7.0f;
+    FwdPixel p{inside ? 1.0f : -1.0f, 0.f, 0.f, 0.f, 0.f, 0u};
+
+    auto value_at = [&](uint32_t pos) { return pos < r1 ? a.val_sorted[pos] : 0u; };
+    // a batch's records are loaded while the one before is rendered, its splat
+    // ids while the one before that is
+    uint32_t vi = value_at(r0 + lane), vi_n = value_at(r0 + 64 + lane);
+    float4 na = make_float4(0.f, 0.f, 0.f, 0.f), nb = na, nc = na;
+    auto fetch = [&](uint32_t pos, uint32_t id) {
+        if (pos < r1) {
+            const float4* r = reinterpret_cast<const float4*>(a.rec + (size_t)id * GESR_REC_FLOATS);
+            na = r[0];
+            nb = r[1];
+            nc = r[2];
+        }
+    };
+    fetch(r0 + lane, vi);
+    uint32_t stop = r1;  // first list position not evaluated
+    for (uint32_t base = r0; base < r1; base += 64) {
+        if (__ballot(p.T > 0.0f) == 0ull) {
+            stop = base;
+            break;
+        }
+        const bool live = base + lane < r1 && !quad_misses(na, nb, qx0 - na.x, qx1 - na.x, qy0 - na.y, qy1 - na.y);
+        const uint64_t mask = __ballot(live);
+        const uint32_t cnt = (uint32_t)__popcll(mask);
+        if (live) {
+            const uint32_t k = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            sa[k] = na;
+            sb[k] = make_float4(nb.x, nb.y, 0.5f * nb.z, nb.w);
+            sc[k] = make_float4(nc.x, nc.y, nc.z, __uint_as_float(base + lane + 1u - r0));
+            if (EXT) sz[k] = nc.w;
+        }
+        if (lane == 0) {
+            sa[cnt] = sc[cnt] = make_float4(0.f, 0.f, 0.f, 0.f);
+            sb[cnt] = make_float4(0.f, 0.f, 0.f, -1.f);
+            if (EXT) sz[cnt] = 0.f;
+        }
+        wave_lds_sync();
+        vi = vi_n;
+        fetch(base + 64 + lane, vi);
+        vi_n = value_at(base + 128 + lane);
+        for (uint32_t j = 0; j < cnt; j += 2) {
+            bool ok[2];
+            float al[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                Fragment f;
+                const float4 rb = sb[j + u];
+                const float q = ges_q(sa[j + u], rb.x, px, py, f);
+                ges_alpha(q, rb.z, rb.y, nk, amax, f);
+                ok[u] = (int)(q <= rb.w) & (int)!(f.alpha < amin);
+                al[u] = ok[u] ? f.alpha : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const float4 rc = sc[j + u];
+                blend<EXT>(p, al[u], ok[u], rc, EXT ? sz[j + u] : 0.f, __float_as_uint(rc.w), tmin);
+            }
+        }
+        wave_lds_sync();
+    }
+    if (a.tile_work) {
+        if (lane == 0) s_stop[wave] = stop;
+        __syncthreads();
+        if (threadIdx.x == 0) a.tile_work[t] = max(max(s_stop[0], s_stop[1]), max(s_stop[2], s_stop[3])) - r0;
+    }
+    if (inside) write_pixel<EXT>(a, w, x, y, p);
+}
+
+// Forward of 16x16 tiles.  The first a.n_split workgroups take one tile each
+// (fwd_quad_tile), the others four (a tile per wave, fwd_wave_tile).  The two give
+// the same pixels bit for bit.
+template <bool EXT>
+__global__ __launch_bounds__(256) void k_render_fwd16(RenderArgs a) {
+    __shared__ float4 s_a[4][65], s_b[4][65], s_c[4][65];
+    __shared__ float s_z[EXT ? 4 : 1][65];
+    __shared__ uint32_t s_stop[4];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (blockIdx.x < a.n_split) {
+        fwd_quad_tile<EXT>(a, a.worklist[blockIdx.x], wave, s_a[wave], s_b[wave], s_c[wave], s_z[EXT ? wave : 0], s_stop);
+        return;
+    }
+    const uint32_t item = a.n_split + 4u * (blockIdx.x - a.n_split) + wave;
+    if (item < a.n_items) fwd_wave_tile<false, 64, EXT>(a, a.worklist[item], s_a[wave], s_b[wave], s_c[wave]);
+}
+
+// The counting variant: one wave (workgroup) per tile.
+template <int B, bool EXT>
+__global__ __launch_bounds__(64) void k_render_fwd16_counts(RenderArgs a) {
+    __shared__ float4 s_a[B], s_b[B], s_c[B];
+    fwd_wave_tile<true, B, EXT>(a, a.worklist[blockIdx.x], s_a, s_b, s_c);
 }
 
 // Backward, one wave per 16x16 tile: lane l owns pixel (l & 7, l >> 3) of each
@@ -608,29 +771,45 @@ hipError_t bwd_shape(const RenderArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Leading worklist tiles (the ones with most work) that the 16x16 forward takes
+// with four waves each.  Up to 8,192 tiles all of them: with a wave per tile the
+// chip's 8,192 wave slots would be filled once or less and the kernel would last as
+// long as its longest list (one wave takes 220 ns per list position): 200 -> 89 us
+// on 3,024 tiles (100k splats, 1008x756), 145 -> 31 us on 64 tiles, 290 -> 172 us
+// on 8,487.  Above that the first 1,024, which shortens the longest lists: 1,385 ->
+// 810 us on 24,842 tiles of views at 1/8 .. 1 of 1600x1064 (its longest list, 6,208
+// positions against 300 on average, took all of the former time), 880 -> 837 us
+// on 33,948 and unchanged on 130,560 even tiles; with four waves for all tiles these
+// take 944, 991 and (2,530 ->) 3,080 us, because a quadrant wave reads every record
+// from LDS for 64 pixels instead of 256.
+uint32_t fwd_split_tiles(uint32_t n_items) { return n_items <= 8192u ? n_items : 1024u; }
+
 }  // namespace
 
 hipError_t launch_render_fwd(const RenderArgs& a, int tw, int th, bool counts, hipStream_t s) {
     if (a.n_items == 0) return hipSuccess;
     if (tw == 16 && th == 16) {
-        if (a.st.variant == 1) return fwd_shape<16, 16>(a, counts, s);
-        const bool small = a.batch == 32, ext = a.out_depth || a.out_alpha;
-        const dim3 grid(a.n_items), block(64);
-        if (ext) {
-            if (counts) {
-                if (small) hipLaunchKernelGGL((k_render_fwd_wave16<true, 32, true>), grid, block, 0, s, a);
-                else hipLaunchKernelGGL((k_render_fwd_wave16<true, 64, true>), grid, block, 0, s, a);
-            } else {
-                if (small) hipLaunchKernelGGL((k_render_fwd_wave16<false, 32, true>), grid, block, 0, s, a);
-                else hipLaunchKernelGGL((k_render_fwd_wave16<false, 64, true>), grid, block, 0, s, a);
-            }
-        } else if (counts) {
-            if (small) hipLaunchKernelGGL((k_render_fwd_wave16<true, 32, false>), grid, block, 0, s, a);
-            else hipLaunchKernelGGL((k_render_fwd_wave16<true, 64, false>), grid, block, 0, s, a);
-        } else {
-            if (small) hipLaunchKernelGGL((k_render_fwd_wave16<false, 32, false>), grid, block, 0, s, a);
-            else hipLaunchKernelGGL((k_render_fwd_wave16<false, 64, false>), grid, block, 0, s, a);
+        if (a.st.variant == 1 && counts) {
+            hipLaunchKernelGGL((k_render_fwd<16, 16, true>), dim3(a.n_items), dim3(256), 0, s, a);
+            return hipGetLastError();
         }
+        const bool small = a.batch == 32, ext = a.out_depth || a.out_alpha;
+        if (counts) {
+            const dim3 grid(a.n_items), block(64);
+            if (ext) {
+                if (small) hipLaunchKernelGGL((k_render_fwd16_counts<32, true>), grid, block, 0, s, a);
+                else hipLaunchKernelGGL((k_render_fwd16_counts<64, true>), grid, block, 0, s, a);
+            } else {
+                if (small) hipLaunchKernelGGL((k_render_fwd16_counts<32, false>), grid, block, 0, s, a);
+                else hipLaunchKernelGGL((k_render_fwd16_counts<64, false>), grid, block, 0, s, a);
+            }
+            return hipGetLastError();
+        }
+        RenderArgs b = a;
+        b.n_split = a.st.variant == 1 ? a.n_items : fwd_split_tiles(a.n_items);
+        const dim3 grid(b.n_split + (a.n_items - b.n_split + 3) / 4), block(256);
+        if (ext) hipLaunchKernelGGL((k_render_fwd16<true>), grid, block, 0, s, b);
+        else hipLaunchKernelGGL((k_render_fwd16<false>), grid, block, 0, s, b);
         return hipGetLastError();
     }
     if (tw == 8 && th == 8) return fwd_shape<8, 8>(a, counts, s);

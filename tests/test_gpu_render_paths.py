@@ -1,0 +1,76 @@
+"""The 16x16 renderers' ways of sharing a tile among waves give the same bits.
+
+The forward takes a tile with four waves (one 8x8 quadrant each, only the
+records that can reach it) or with one; the counting forward always with one.
+Tile counts on both sides of the dispatch rules, ragged and one-pixel views,
+thin splats (the quadrant's footprint test at its most sheared), beta below 2,
+lists that end mid-batch and pixels that terminate."""
+import numpy as np
+import pytest
+
+import gesr_inputs as gi
+import oracle
+from tests.gpu_util import splats_of
+
+pytestmark = pytest.mark.gpu
+
+
+def _needles(n=700):
+    rng = np.random.default_rng([400, 0])
+    means = rng.uniform(-1.0, 1.0, (n, 3))
+    ls = np.stack([rng.uniform(-2.5, -1.0, n), rng.uniform(-10.0, -6.0, n), rng.uniform(-10.0, -6.0, n)], 1)
+    return gi._finish("needles", rng, means, ls, gi._random_quats(rng, n), rng.uniform(0.7, 4.0, n),
+                      gi._sh_coeffs(rng, n, 0), 0, gi.ring_cameras(2, [(333, 215), (64, 48)]))
+
+
+def _opaque(n=3000):
+    s = gi.tiny_scene(5, n=n, width=90, height=70, deg=0, spread=0.5)
+    s.opacities[:] = 0.98
+    return s
+
+
+def _wide(n=4000):
+    """More than 8,192 tiles: the leading ones with four waves, the rest with one."""
+    rng = np.random.default_rng([401, 0])
+    cams = [gi.look_at((0.0, 0.0, -4.0), width=1800, height=1300), gi.look_at((0.5, 0.3, -4.0), width=37, height=19)]
+    return gi._uniform_cube_scene("wide", rng, n, cams)
+
+
+SCENES = {
+    "ragged": lambda: gi.ragged_scene(1),
+    "one-splat": lambda: gi.tiny_scene(3, n=1, deg=0),
+    "plain": lambda: gi.make_workload(1),
+    "needles": _needles,
+    "opaque": _opaque,
+    "wide": _wide,
+    "drt-20k": lambda: gi.make_workload(3, n_override=20_000),
+}
+
+
+def _rast(scene, **kw):
+    from paper_2411_09156_amd import Rasterizer, RasterSettings
+    return Rasterizer(scene.cameras, RasterSettings(sh_degree=scene.sh_degree, bg=(0.2, 0.1, 0.3), **kw))
+
+
+@pytest.mark.parametrize("name", list(SCENES))
+@pytest.mark.parametrize("channels", [False, True])
+def test_forward_paths_agree_bitwise(name, channels):
+    import torch
+    scene = SCENES[name]()
+    rast, sp = _rast(scene), splats_of(scene)
+    proj = rast.project(sp)
+    bins = rast.bin(proj, sp.n)
+    outs = []
+    for counts in (True, False):
+        f = rast.render_fwd(proj, bins, sp.n, counts=counts, channels=channels)
+        torch.cuda.synchronize()
+        o = {k: f[k].cpu().numpy() for k in ("image", "final_T", "n_contrib") + (("depth", "alpha") if channels else ())}
+        o["tile_work"] = bins["tile_work"].cpu().numpy().copy()
+        outs.append(o)
+    for k in outs[0]:
+        np.testing.assert_array_equal(outs[0][k], outs[1][k], err_msg=k)
+    if not channels:
+        v1 = _rast(scene, variant=1)
+        f = v1.render_fwd(proj, v1.bin(proj, sp.n), sp.n)
+        for k in ("image", "final_T", "n_contrib"):
+            np.testing.assert_array_equal(f[k].cpu().numpy(), outs[0][k], err_msg=k)

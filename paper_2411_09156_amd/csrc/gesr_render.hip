@@ -81,12 +81,56 @@ __device__ __forceinline__ void stage_record(const float* rec, uint32_t vi, floa
     sc = make_float4(c.x, c.y, c.z, -kappa * b.z);
 }
 
-// One pixel's state of the reverse traversal: transmittance in front of the
-// fragment last visited, upstream gradients, and what lies behind per unit
-// transmittance (colour; depth and opacity with the extended channels).
-struct PixelAdjoint {
-    float T, g0, g1, g2, Br, Bg, Bb, gD, gA, BD, BA;
+// One pixel's upstream gradients (colour; depth and opacity with the extended
+// channels) and its state in the reverse traversal: transmittance in front of the
+// fragment last visited and what lies behind per unit transmittance.
+struct PixelUp {
+    float g0, g1, g2, gD, gA;
 };
+struct PixelAdjoint {
+    float T, Br, Bg, Bb, BD, BA;
+};
+
+template <bool EXT>
+__device__ __forceinline__ PixelUp load_up(const RenderArgs& a, uint32_t pix, uint32_t img, uint32_t ch) {
+    PixelUp u{a.dL_dimage[img], a.dL_dimage[img + ch], a.dL_dimage[img + 2 * ch], 0.f, 0.f};
+    if (EXT) {
+        if (a.dL_ddepth) u.gD = a.dL_ddepth[pix];
+        if (a.dL_dalpha) u.gA = a.dL_dalpha[pix];
+    }
+    return u;
+}
+
+// The background has no depth and no opacity.
+__device__ __forceinline__ PixelAdjoint behind_all(const DevSettings& st, float T) {
+    return PixelAdjoint{T, st.bg[0], st.bg[1], st.bg[2], 0.f, 0.f};
+}
+
+// Takes a pixel past one fragment (in reverse): its weight aT = alpha T and
+// dl = dL/dalpha where alpha is neither skipped nor capped, 0 elsewhere.  A
+// fragment with on = false (not the pixel's, or below alpha_min) has alpha 0: it
+// leaves T (rcp(1) = 1) and what lies behind as they are.
+template <bool EXT>
+__device__ __forceinline__ void pixel_step(const Fragment& f, bool on, const float4& rc, float z,
+                                           const DevSettings& st, const PixelUp& u, PixelAdjoint& px, float& aT,
+                                           float& dl) {
+    const bool ok = on && !(f.alpha < st.alpha_min);
+    const float al = ok ? f.alpha : 0.0f;
+    px.T *= hw_rcp(1.0f - al);
+    aT = al * px.T;
+    const float er = rc.x - px.Br, eg = rc.y - px.Bg, eb = rc.z - px.Bb;
+    float dLda = px.T * fmaf(eb, u.g2, fmaf(er, u.g0, eg * u.g1));
+    px.Br = fmaf(al, er, px.Br);
+    px.Bg = fmaf(al, eg, px.Bg);
+    px.Bb = fmaf(al, eb, px.Bb);
+    if (EXT) {
+        const float ed = z - px.BD, ea = 1.0f - px.BA;
+        dLda = fmaf(px.T, fmaf(ed, u.gD, ea * u.gA), dLda);
+        px.BD = fmaf(al, ed, px.BD);
+        px.BA = fmaf(al, ea, px.BA);
+    }
+    dl = ok && !(f.oG > st.alpha_max) ? dLda : 0.0f;
+}
 
 // Adds one fragment's gradient terms to the splat's sums gr.  With
 // G = exp(-kappa P), P = q^(beta/2), X = dL/dalpha o G P and d = -kappa beta X / q
@@ -95,49 +139,35 @@ struct PixelAdjoint {
 //         sum X ln q (-kappa / 2), dL/dr, dL/dg, dL/db)
 // The conic factor is the same for all of a tile's pixels, so the centre's
 // gradient takes it once, in `splat_partial`.  At q = 0 the footprint and beta terms
-// are 0: P and X are, and the legacy product takes 0 times infinity as 0.  The
-// alpha cap removes the dependence on opacity and footprint; a fragment below
-// alpha_min has alpha 0 here, which leaves T (rcp(1) = 1), what lies behind and the
-// sums as they are.  A flat splat seen edge-on amplifies the rounding of the three
-// footprint sums in its scale gradient, so their terms keep this order of products.
+// are 0: P and X are, and the legacy product takes 0 times infinity as 0.  A flat
+// splat seen edge-on amplifies the rounding of the three footprint sums in its
+// scale gradient, so their terms keep this order of products.
 // The kernel is bound by these instructions: the products in place of selects and
 // the two sums for the centre took 53 instructions to 47 (a compare or select
 // takes 4.3 cycles per wave on gfx950, a product 2.3), a step over 3M splats x 16
 // views from 20.2 to 19.7 ms and over 1M flat splats x 4 views from 5.00 to 4.90 ms.
-template <bool EXT>
-__device__ __forceinline__ void add_fragment(const Fragment& f, const float4& rc, float z, const DevSettings& st,
-                                             float c2, PixelAdjoint& px, float (&gr)[GESR_PARTIAL_FLOATS],
-                                             float& gz) {
-    const bool ok = !(f.alpha < st.alpha_min);
-    const float al = ok ? f.alpha : 0.0f;
-    px.T *= hw_rcp(1.0f - al);
-    const float aT = al * px.T;
-    gr[7] = fmaf(aT, px.g0, gr[7]);
-    gr[8] = fmaf(aT, px.g1, gr[8]);
-    gr[9] = fmaf(aT, px.g2, gr[9]);
-    const float er = rc.x - px.Br, eg = rc.y - px.Bg, eb = rc.z - px.Bb;
-    float dLda = px.T * fmaf(eb, px.g2, fmaf(er, px.g0, eg * px.g1));
-    px.Br = fmaf(al, er, px.Br);
-    px.Bg = fmaf(al, eg, px.Bg);
-    px.Bb = fmaf(al, eb, px.Bb);
-    if (EXT) {
-        const float ed = z - px.BD, ea = 1.0f - px.BA;
-        dLda = fmaf(px.T, fmaf(ed, px.gD, ea * px.gA), dLda);
-        gz = fmaf(aT, px.gD, gz);
-        px.BD = fmaf(al, ed, px.BD);
-        px.BA = fmaf(al, ea, px.BA);
-    }
-    const float dl = ok && !(f.oG > st.alpha_max) ? dLda : 0.0f;
-    gr[5] = fmaf(dl, f.G, gr[5]);
+struct FragmentTerms {
+    float aT, dl, G, xl, tq, wq;  // xl = X log2 q, tq = d t, wq = d w
+};
+__device__ __forceinline__ FragmentTerms fragment_terms(const Fragment& f, float rcw, float aT, float dl) {
     const float X = dl * f.oG * f.P;
-    gr[6] = fmaf(mul_legacy(X, f.l2q), c2, gr[6]);
-    const float d = mul_legacy(X * rc.w, hw_rcp(f.q));
-    const float tq = d * f.t, wq = d * f.w;
-    gr[0] += tq;
-    gr[1] += wq;
-    gr[2] = fmaf(tq, f.dx, gr[2]);
-    gr[3] = fmaf(tq, f.dy, gr[3]);
-    gr[4] = fmaf(wq, f.dy, gr[4]);
+    const float d = mul_legacy(X * rcw, hw_rcp(f.q));
+    return FragmentTerms{aT, dl, f.G, mul_legacy(X, f.l2q), d * f.t, d * f.w};
+}
+template <bool EXT>
+__device__ __forceinline__ void add_terms(const FragmentTerms& v, float dx, float dy, float c2, const PixelUp& u,
+                                          float (&gr)[GESR_PARTIAL_FLOATS], float& gz) {
+    gr[7] = fmaf(v.aT, u.g0, gr[7]);
+    gr[8] = fmaf(v.aT, u.g1, gr[8]);
+    gr[9] = fmaf(v.aT, u.g2, gr[9]);
+    if (EXT) gz = fmaf(v.aT, u.gD, gz);
+    gr[5] = fmaf(v.dl, v.G, gr[5]);
+    gr[6] = fmaf(v.xl, c2, gr[6]);
+    gr[0] += v.tq;
+    gr[1] += v.wq;
+    gr[2] = fmaf(v.tq, dx, gr[2]);
+    gr[3] = fmaf(v.tq, dy, gr[3]);
+    gr[4] = fmaf(v.wq, dy, gr[4]);
 }
 
 // The instance's partials (layout: d/du, d/dv, d/dL00, d/dL10, d/dL11, d/do,
@@ -151,15 +181,15 @@ __device__ __forceinline__ void splat_partial(float (&s)[GESR_PARTIAL_FLOATS + 1
 
 constexpr uint32_t kNoInstance = 0xFFFFFFFFu;
 
-// Slot of the instance (splat vi, tile (tx, ty)) in the pair-major order: the
-// splat's instance base plus the tile's row-major position in its rectangle.
+// Slot of the instance of a pair in tile (tx, ty) in the pair-major order: the
+// pair's instance base plus the tile's row-major position in its rectangle.
 // When the lists overflowed their capacity the ranges no longer match the
 // truncated lists, so a listed splat may not cover the tile or its slot may lie
 // beyond the capacity; kNoInstance then suppresses the partial write.
-__device__ __forceinline__ uint32_t instance_index(const RenderArgs& a, uint2 r, uint32_t vi, uint32_t tx,
+__device__ __forceinline__ uint32_t instance_index(const RenderArgs& a, uint2 r, uint32_t base, uint32_t tx,
                                                    uint32_t ty) {
     const uint32_t tx0 = r.x & 0xFFFFu, ty0 = r.x >> 16, tx1 = r.y & 0xFFFFu, ty1 = r.y >> 16;
-    const uint32_t inst = a.inst_base[vi] + (ty - ty0) * (tx1 - tx0 + 1u) + (tx - tx0);
+    const uint32_t inst = base + (ty - ty0) * (tx1 - tx0 + 1u) + (tx - tx0);
     const bool inside = tx >= tx0 && tx <= tx1 && ty >= ty0 && ty <= ty1;
     return inside && inst < a.m_cap ? inst : kNoInstance;
 }
@@ -247,10 +277,6 @@ __global__ __launch_bounds__(TW * TH) void k_render_fwd(RenderArgs a) {
 
 template <int TW, int TH, int BATCH>
 __global__ __launch_bounds__(TW * TH) void k_render_bwd(RenderArgs a) {
-    // The gradient arithmetic may fuse multiply-adds; the alpha, threshold and
-    // transmittance evaluation shared with the forward is written with explicit
-    // fmaf (or has no multiply-add) and compiles identically in both kernels.
-#pragma clang fp contract(fast)
     constexpr int NT = TW * TH;
     constexpr int NW = NT / 64;
     constexpr int NP = GESR_PARTIAL_FLOATS;
@@ -269,17 +295,13 @@ __global__ __launch_bounds__(TW * TH) void k_render_bwd(RenderArgs a) {
     const float px = (float)ti.x + 0.5f, py = (float)ti.y + 0.5f;
     const uint32_t lane = __lane_id(), wave = threadIdx.x >> 6;
 
-    PixelAdjoint pa{};
-    pa.Br = st.bg[0];
-    pa.Bg = st.bg[1];
-    pa.Bb = st.bg[2];
+    PixelAdjoint pa = behind_all(st, 0.f);
+    PixelUp up{};
     uint32_t nc = 0;
     if (ti.inside) {
         pa.T = a.final_T[ti.pix];
         nc = a.n_contrib[ti.pix];
-        pa.g0 = a.dL_dimage[ti.img];
-        pa.g1 = a.dL_dimage[ti.img + ti.ch];
-        pa.g2 = a.dL_dimage[ti.img + 2 * ti.ch];
+        up = load_up<false>(a, ti.pix, ti.img, ti.ch);
     }
 
     // deepest list position any pixel of the tile composited
@@ -300,7 +322,7 @@ __global__ __launch_bounds__(TW * TH) void k_render_bwd(RenderArgs a) {
             stage_record(a.rec, vi, st.kappa, sA[threadIdx.x], sB[threadIdx.x], sC[threadIdx.x]);
             const float4 r3 = reinterpret_cast<const float4*>(a.rec + (size_t)vi * GESR_REC_FLOATS)[3];
             const uint2 r = make_uint2(__float_as_uint(r3.x), __float_as_uint(r3.y));  // the pair's rectangle
-            sInst[threadIdx.x] = instance_index(a, r, vi, ti.tx, ti.ty);
+            sInst[threadIdx.x] = instance_index(a, r, a.inst_base[vi], ti.tx, ti.ty);
         }
         __syncthreads();
         for (int j = 0; j < cnt; ++j) {
@@ -317,8 +339,10 @@ __global__ __launch_bounds__(TW * TH) void k_render_bwd(RenderArgs a) {
                 if (q <= rb.w) {
                     ges_alpha(q, rb.z, rb.y, nk, amax, f);
                     act = true;
-                    float gz = 0.0f;
-                    add_fragment<false>(f, sC[j], 0.0f, st, c2, pa, gr, gz);
+                    const float4 rc = sC[j];
+                    float gz = 0.0f, aT, dl;
+                    pixel_step<false>(f, true, rc, 0.0f, st, up, pa, aT, dl);
+                    add_terms<false>(fragment_terms(f, rc.w, aT, dl), f.dx, f.dy, c2, up, gr, gz);
                 }
             }
             if (__ballot(act) != 0ull) {
@@ -629,65 +653,122 @@ __global__ __launch_bounds__(64) void k_render_fwd16_counts(RenderArgs a) {
     fwd_wave_tile<true, B, EXT>(a, a.worklist[blockIdx.x], s_a, s_b, s_c);
 }
 
-// Backward, one wave per 16x16 tile: lane l owns pixel (l & 7, l >> 3) of each
+// The 64-bit value of lane l (wave-uniform).
+__device__ __forceinline__ uint64_t read_lane(uint64_t x, int l) {
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), l);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)x, l);
+    return (uint64_t)hi << 32 | lo;
+}
+
+// Stage of one batch of records of a 16x16 tile's adjoint, and the batch's sums
+// (column 10: dz, extended channels).
+constexpr int kBwdBatch = 64;
+template <bool EXT>
+struct BwdStage {
+    float4 a[kBwdBatch], b[kBwdBatch], c[kBwdBatch];
+    uint32_t inst[kBwdBatch];
+    float red[kBwdBatch][GESR_PARTIAL_FLOATS + 1];
+    float z[EXT ? kBwdBatch : 1];
+};
+
+// One record on its way to the stage: the loads are issued by `load`, what is derived
+// from them waits until `store`.
+template <bool EXT>
+struct BwdRecord {
+    float4 a, b, c, r;
+    uint32_t base;
+    __device__ __forceinline__ void load(const RenderArgs& A, uint32_t vi) {
+        const float4* p = reinterpret_cast<const float4*>(A.rec + (size_t)vi * GESR_REC_FLOATS);
+        a = p[0];
+        b = p[1];
+        c = p[2];
+        r = p[3];
+        base = A.inst_base[vi];
+    }
+    __device__ __forceinline__ void store(const RenderArgs& A, BwdStage<EXT>& s, uint32_t k, uint32_t tx,
+                                          uint32_t ty) const {
+        s.a[k] = a;
+        s.b[k] = make_float4(b.x, b.y, 0.5f * b.z, b.w);
+        s.c[k] = make_float4(c.x, c.y, c.z, -A.st.kappa * b.z);
+        s.inst[k] = instance_index(A, make_uint2(__float_as_uint(r.x), __float_as_uint(r.y)), base, tx, ty);
+        if (EXT) s.z[k] = c.w;
+    }
+};
+
+template <bool EXT>
+__device__ __forceinline__ void write_batch(const RenderArgs& a, BwdStage<EXT>& s, uint32_t lane, uint32_t cnt) {
+    constexpr int NP = GESR_PARTIAL_FLOATS;
+    if (lane >= cnt || s.inst[lane] == kNoInstance) return;
+    float v[NP + 1];
+#pragma unroll
+    for (int k = 0; k <= NP; ++k) v[k] = EXT || k < NP ? s.red[lane][k] : 0.0f;
+    splat_partial(v, s.a[lane], s.b[lane]);
+    write_partial<EXT>(a, s.inst[lane], v);
+}
+
+// Sums of a record over the wave's lanes into its row of the batch.
+template <bool EXT>
+__device__ __forceinline__ void reduce_record(BwdStage<EXT>& s, uint32_t j, const float (&gr)[GESR_PARTIAL_FLOATS],
+                                              float gz, uint32_t lane, int slot) {
+    static_assert(GESR_PARTIAL_FLOATS == 10, "wave_sum10 reduces ten values");
+    const float tot = wave_sum10(gr, lane);
+    if (slot < GESR_PARTIAL_FLOATS) s.red[j][slot] = tot;
+    if (EXT) {
+        const float tz = wave_sum(gz);
+        if (lane == 0) s.red[j][GESR_PARTIAL_FLOATS] = tz;
+    }
+}
+
+struct TilePlace {
+    const DevView* w;
+    uint32_t tx, ty, ch, r0;
+};
+__device__ __forceinline__ TilePlace place_tile(const RenderArgs& a, uint32_t t) {
+    TilePlace p;
+    p.w = &a.cams.v[view_of_tile(a.cams, t)];
+    const uint32_t lt = t - p.w->tile_base;
+    p.tx = lt % (uint32_t)p.w->tiles_x;
+    p.ty = lt / (uint32_t)p.w->tiles_x;
+    p.ch = (uint32_t)p.w->W * (uint32_t)p.w->H;
+    p.r0 = a.ranges[2 * (size_t)t];
+    return p;
+}
+
+// Adjoint of one 16x16 tile by one wave: lane l owns pixel (l & 7, l >> 3) of each
 // 8x8 quadrant (4 pixels per lane), so a staged splat's LDS reads and its
 // 10-value wave reduction serve 256 pixels, and no cross-wave reduction or
-// workgroup barrier beyond the wave itself is needed.  EXT: the extended
-// channels' upstream gradients too (depth and opacity as colour channels over
-// a zero background; the depth term dz is the eleventh partial value).
-template <int B, bool EXT>
-__global__ __launch_bounds__(64) void k_render_bwd_wave16(RenderArgs a) {
-    // The gradient arithmetic may fuse multiply-adds; the alpha, threshold and
-    // transmittance evaluation shared with the forward is written with explicit
-    // fmaf (or has no multiply-add) and compiles identically in both kernels.
-#pragma clang fp contract(fast)
-    static_assert(B >= 1 && B <= 64, "one staged record per lane");
+// workgroup barrier is needed.  EXT: the extended channels' upstream gradients
+// too (depth and opacity as colour channels over a zero background; the depth
+// term dz is the eleventh partial value).
+template <bool EXT>
+__device__ __forceinline__ void bwd_wave_tile(const RenderArgs& a, uint32_t t, BwdStage<EXT>& s) {
     constexpr int NP = GESR_PARTIAL_FLOATS;
-    static_assert(NP == 10, "wave_sum10 reduces ten values");
-    __shared__ float4 sA[B], sB[B], sC[B];
-    __shared__ uint32_t sInst[B];
-    __shared__ float sRed[B][NP + 1];  // column NP: dz (extended channels)
-    __shared__ float sZ[EXT ? B : 1];   // staged splat depths (extended channels)
-
-    const uint32_t t = a.worklist[blockIdx.x];
     const DevSettings& st = a.st;
     const float amax = st.alpha_max, nk = in_vgpr(st.neg_kappa_log2e);
     const float c2 = -0.5f * kLn2 * st.kappa;
     const uint32_t lane = __lane_id();
-    const int v = view_of_tile(a.cams, t);
-    const DevView& w = a.cams.v[v];
-    const uint32_t lt = t - w.tile_base;
-    const uint32_t tx = lt % (uint32_t)w.tiles_x, ty = lt / (uint32_t)w.tiles_x;
-    const uint2 rg = reinterpret_cast<const uint2*>(a.ranges)[t];
-    const uint32_t r0 = rg.x;
-    const uint32_t ch = (uint32_t)w.W * (uint32_t)w.H;
+    const TilePlace tp = place_tile(a, t);
+    const uint32_t r0 = tp.r0;
 
     // pixel centres: quadrant q adds (q & 1) * 8 and (q >> 1) * 8 to the lane's base
-    const float pxb = (float)(tx * 16 + (lane & 7)) + 0.5f, pyb = (float)(ty * 16 + (lane >> 3)) + 0.5f;
+    const float pxb = (float)(tp.tx * 16 + (lane & 7)) + 0.5f, pyb = (float)(tp.ty * 16 + (lane >> 3)) + 0.5f;
     PixelAdjoint pa[4];
+    PixelUp up[4];
     uint32_t nc[4];
     uint32_t mymax = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int x = (int)tx * 16 + (q & 1) * 8 + (int)(lane & 7);
-        const int y = (int)ty * 16 + (q >> 1) * 8 + (int)(lane >> 3);
-        pa[q] = PixelAdjoint{};  // the background has no depth and no opacity
-        pa[q].Br = st.bg[0];
-        pa[q].Bg = st.bg[1];
-        pa[q].Bb = st.bg[2];
+        const int x = (int)tp.tx * 16 + (q & 1) * 8 + (int)(lane & 7);
+        const int y = (int)tp.ty * 16 + (q >> 1) * 8 + (int)(lane >> 3);
+        pa[q] = behind_all(st, 0.f);
+        up[q] = PixelUp{};
         nc[q] = 0;
-        if (x < w.W && y < w.H) {
-            const uint32_t local = (uint32_t)y * (uint32_t)w.W + (uint32_t)x;
-            const uint32_t pix = w.pix_base + local, img = 3u * w.pix_base + local;
+        if (x < tp.w->W && y < tp.w->H) {
+            const uint32_t local = (uint32_t)y * (uint32_t)tp.w->W + (uint32_t)x;
+            const uint32_t pix = tp.w->pix_base + local;
             pa[q].T = a.final_T[pix];
             nc[q] = a.n_contrib[pix];
-            pa[q].g0 = a.dL_dimage[img];
-            pa[q].g1 = a.dL_dimage[img + ch];
-            pa[q].g2 = a.dL_dimage[img + 2 * ch];
-            if (EXT) {
-                if (a.dL_ddepth) pa[q].gD = a.dL_ddepth[pix];
-                if (a.dL_dalpha) pa[q].gA = a.dL_dalpha[pix];
-            }
+            up[q] = load_up<EXT>(a, pix, 3u * tp.w->pix_base + local, tp.ch);
         }
         mymax = max(mymax, nc[q]);
     }
@@ -696,24 +777,19 @@ __global__ __launch_bounds__(64) void k_render_bwd_wave16(RenderArgs a) {
     const int slot = lane < 16 ? wave_sum10_slot(lane) : NP;  // value this lane writes after a reduction
 
     for (uint32_t hi = end; hi > r0;) {
-        const uint32_t lo = (hi - r0 > (uint32_t)B) ? hi - B : r0;
-        const int cnt = (int)(hi - lo);
-        if ((int)lane < cnt) {
-            const uint32_t pos = hi - 1u - lane;
-            const uint32_t vi = a.val_sorted[pos];
-            stage_record(a.rec, vi, st.kappa, sA[lane], sB[lane], sC[lane]);
-            if (EXT) sZ[lane] = a.rec[(size_t)vi * GESR_REC_FLOATS + 11];
-            const float4 r3 = reinterpret_cast<const float4*>(a.rec + (size_t)vi * GESR_REC_FLOATS)[3];
-            const uint2 r = make_uint2(__float_as_uint(r3.x), __float_as_uint(r3.y));  // the pair's rectangle
-            sInst[lane] = instance_index(a, r, vi, tx, ty);
+        const uint32_t cnt = min(hi - r0, (uint32_t)kBwdBatch);
+        if (lane < cnt) {
+            BwdRecord<EXT> r;
+            r.load(a, a.val_sorted[hi - 1u - lane]);
+            r.store(a, s, lane, tp.tx, tp.ty);
         }
-        __syncthreads();
-        for (int j = 0; j < cnt; ++j) {
-            const uint32_t prel = hi - 1u - (uint32_t)j - r0;  // 0-based list position
-            const float4 ra = sA[j];
-            const float4 rb = sB[j];
-            const float4 rc = sC[j];
-            const float z = EXT ? sZ[j] : 0.0f;
+        wave_lds_sync();
+        for (uint32_t j = 0; j < cnt; ++j) {
+            const uint32_t prel = hi - 1u - j - r0;  // 0-based list position
+            const float4 ra = s.a[j];
+            const float4 rb = s.b[j];
+            const float4 rc = s.c[j];
+            const float z = EXT ? s.z[j] : 0.0f;
             float gr[NP], gz = 0.0f;
 #pragma unroll
             for (int k = 0; k < NP; k += 2) opaque_zero2(gr[k], gr[k + 1]);
@@ -726,34 +802,197 @@ __global__ __launch_bounds__(64) void k_render_bwd_wave16(RenderArgs a) {
                 if (prel >= nc[q] || qq > rb.w) continue;  // behind the pixel's last or beyond the footprint
                 // Inside the footprint alpha almost never falls below alpha_min,
                 // the alpha cap and a centred pixel are rarer still: those
-                // decisions are selects (a zeroed term leaves the sums as they
-                // are), so the wave takes one branch per quadrant.
+                // decisions are selects or zero products (a zeroed term leaves the
+                // sums as they are), so the wave takes one branch per quadrant.
                 ges_alpha(qq, rb.z, rb.y, nk, amax, f);
                 act = true;
-                add_fragment<EXT>(f, rc, z, st, c2, pa[q], gr, gz);
+                float aT, dl;
+                pixel_step<EXT>(f, true, rc, z, st, up[q], pa[q], aT, dl);
+                add_terms<EXT>(fragment_terms(f, rc.w, aT, dl), f.dx, f.dy, c2, up[q], gr, gz);
             }
-            if (__ballot(act) != 0ull) {
-                const float tot = wave_sum10(gr, lane);
-                if (slot < NP) sRed[j][slot] = tot;
-                if (EXT) {
-                    const float tz = wave_sum(gz);
-                    if (lane == 0) sRed[j][NP] = tz;
-                }
-            } else if ((int)lane < (EXT ? NP + 1 : NP)) {
-                sRed[j][lane] = 0.f;
-            }
+            if (__ballot(act) != 0ull) reduce_record(s, j, gr, gz, lane, slot);
+            else if ((int)lane < (EXT ? NP + 1 : NP)) s.red[j][lane] = 0.f;
         }
-        __syncthreads();
-        if ((int)lane < cnt && sInst[lane] != kNoInstance) {
-            float s[NP + 1];
-#pragma unroll
-            for (int k = 0; k <= NP; ++k) s[k] = EXT || k < NP ? sRed[lane][k] : 0.0f;
-            splat_partial(s, sA[lane], sB[lane]);
-            write_partial<EXT>(a, sInst[lane], s);
-        }
-        __syncthreads();
-        hi = lo;
+        wave_lds_sync();
+        write_batch(a, s, lane, cnt);
+        wave_lds_sync();
+        hi -= cnt;
     }
+}
+
+// Adjoint of one 16x16 tile by the four waves of a workgroup, with the sums of
+// bwd_wave_tile bit for bit.  Rounds of four list positions in two phases.  Phase 1:
+// wave q takes its quadrant's pixels (one per lane) past the round's records that
+// can reach it and leaves each fragment's terms in LDS; the falloffs of two records
+// are independent chains, only T and the colour behind are serial.  Phase 2: wave w
+// adds the w-th record's terms over the whole tile (4 pixels per lane, quadrants in
+// order) and reduces them.
+template <bool EXT>
+struct BwdSplit {
+    BwdStage<EXT> s;
+    float4 v0[4][4][64];  // [record][quadrant][lane]: aT, dl, G, xl
+    float2 v1[4][4][64];  // tq, wq
+    uint64_t live[4];
+    uint32_t maxnc[4];
+};
+
+template <bool EXT>
+__device__ __forceinline__ void bwd_split_tile(const RenderArgs& a, uint32_t t, uint32_t wave, BwdSplit<EXT>& S) {
+    constexpr int NP = GESR_PARTIAL_FLOATS;
+    constexpr int R = 4, GRP = 2;  // records per round, and side by side in phase 1
+    BwdStage<EXT>& s = S.s;
+    const DevSettings& st = a.st;
+    const float amax = st.alpha_max, nk = in_vgpr(st.neg_kappa_log2e);
+    const float c2 = -0.5f * kLn2 * st.kappa;
+    const uint32_t lane = __lane_id();
+    const TilePlace tp = place_tile(a, t);
+    const uint32_t r0 = tp.r0;
+    const float pxb = (float)(tp.tx * 16 + (lane & 7)) + 0.5f, pyb = (float)(tp.ty * 16 + (lane >> 3)) + 0.5f;
+    const float qx = (float)(tp.tx * 16 + (wave & 1) * 8) + 0.5f, qy = (float)(tp.ty * 16 + (wave >> 1) * 8) + 0.5f;
+    const float px = pxb + (float)((wave & 1) * 8), py = pyb + (float)((wave >> 1) * 8);
+    PixelUp up[4], mine{};
+    PixelAdjoint pa = behind_all(st, 0.f);
+    uint32_t nc = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int x = (int)tp.tx * 16 + (q & 1) * 8 + (int)(lane & 7);
+        const int y = (int)tp.ty * 16 + (q >> 1) * 8 + (int)(lane >> 3);
+        up[q] = PixelUp{};
+        if (x < tp.w->W && y < tp.w->H) {
+            const uint32_t local = (uint32_t)y * (uint32_t)tp.w->W + (uint32_t)x;
+            const uint32_t pix = tp.w->pix_base + local;
+            up[q] = load_up<EXT>(a, pix, 3u * tp.w->pix_base + local, tp.ch);
+            if (q == (int)wave) {
+                pa.T = a.final_T[pix];
+                nc = a.n_contrib[pix];
+                mine = up[q];
+            }
+        }
+    }
+    const uint32_t wmax = __builtin_amdgcn_readfirstlane(wave_max_u32(nc));  // this quadrant's deepest position
+    if (lane == 0) S.maxnc[wave] = wmax;
+    __syncthreads();
+    const uint32_t maxnc = __builtin_amdgcn_readfirstlane(max(max(S.maxnc[0], S.maxnc[1]), max(S.maxnc[2], S.maxnc[3])));
+    const int slot = lane < 16 ? wave_sum10_slot(lane) : NP;
+
+    // the first wave stages: a batch's records are loaded while the one before is
+    // taken, its splat ids while the one before that is
+    BwdRecord<EXT> r;
+    uint32_t hi = r0 + maxnc, vi = 0;
+    auto value_at = [&](uint32_t back) { return back + lane < hi - r0 ? a.val_sorted[hi - 1u - back - lane] : 0u; };
+    if (wave == 0) {
+        vi = value_at(0);
+        if (lane < hi - r0) r.load(a, vi);
+        vi = value_at(kBwdBatch);
+    }
+    while (hi > r0) {
+        const uint32_t cnt = min(hi - r0, (uint32_t)kBwdBatch);
+        if (wave == 0 && lane < cnt) r.store(a, s, lane, tp.tx, tp.ty);
+        __syncthreads();
+        if (wave == 0) {
+            if (kBwdBatch + lane < hi - r0) r.load(a, vi);
+            vi = value_at(2 * kBwdBatch);
+        }
+        bool can = false;
+        if (lane < cnt && hi - 1u - lane - r0 < wmax) {
+            const float4 la = s.a[lane];
+            can = !quad_misses(la, s.b[lane], qx - la.x, (qx + 7.0f) - la.x, qy - la.y, (qy + 7.0f) - la.y);
+        }
+        const uint64_t live = __ballot(can);
+        if (lane == 0) S.live[wave] = live;
+        __syncthreads();
+        const uint64_t own = S.live[lane & 3];
+        const uint64_t live_of[4] = {read_lane(own, 0), read_lane(own, 1), read_lane(own, 2), read_lane(own, 3)};
+        for (uint32_t b = 0; b < cnt; b += R) {
+            uint32_t m = (uint32_t)(live >> b) & ((1u << R) - 1u);
+            while (m != 0u) {
+                uint32_t k[GRP];
+                bool have[GRP];
+#pragma unroll
+                for (int u = 0; u < GRP; ++u) {  // past the last record: that one again, off
+                    have[u] = m != 0u;
+                    k[u] = have[u] ? (uint32_t)__builtin_ctz(m) : k[u > 0 ? u - 1 : 0];
+                    m = have[u] ? m & (m - 1) : 0u;
+                }
+                Fragment f[GRP];
+                bool on[GRP];
+#pragma unroll
+                for (int u = 0; u < GRP; ++u) {
+                    const float4 rb = s.b[b + k[u]];
+                    const float qq = ges_q(s.a[b + k[u]], rb.x, px, py, f[u]);
+                    on[u] = (int)(hi - 1u - (b + k[u]) - r0 < nc) & (int)!(qq > rb.w) & (int)have[u];
+                    // q = 1 where the fragment is not the pixel's: its terms are exact zeros
+                    ges_alpha(on[u] ? qq : 1.0f, rb.z, rb.y, nk, amax, f[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < GRP; ++u) {
+                    const float4 rc = s.c[b + k[u]];
+                    float aT, dl;
+                    pixel_step<EXT>(f[u], on[u], rc, EXT ? s.z[b + k[u]] : 0.0f, st, mine, pa, aT, dl);
+                    if (have[u]) {
+                        const FragmentTerms v = fragment_terms(f[u], rc.w, aT, dl);
+                        S.v0[k[u]][wave][lane] = make_float4(v.aT, v.dl, v.G, v.xl);
+                        S.v1[k[u]][wave][lane] = make_float2(v.tq, v.wq);
+                    }
+                }
+            }
+            __syncthreads();
+            const uint32_t j = b + wave;
+            if (j >= cnt) {
+            } else if (((live_of[0] | live_of[1] | live_of[2] | live_of[3]) >> j & 1u) == 0u) {
+                if ((int)lane < (EXT ? NP + 1 : NP)) s.red[j][lane] = 0.f;
+            } else {
+                const float2 uv = make_float2(s.a[j].x, s.a[j].y);
+                float gr[NP], gz = 0.0f;
+                // all reads in flight together (a quadrant without the record holds stale terms: not added)
+                float4 v0[4];
+                float2 v1[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    v0[q] = S.v0[wave][q][lane];
+                    v1[q] = S.v1[wave][q][lane];
+                }
+#pragma unroll
+                for (int i = 0; i < NP; i += 2) opaque_zero2(gr[i], gr[i + 1]);
+                if (EXT) gz = opaque_zero();
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (!(live_of[q] >> j & 1u)) continue;
+                    add_terms<EXT>(FragmentTerms{v0[q].x, v0[q].y, v0[q].z, v0[q].w, v1[q].x, v1[q].y},
+                                   (pxb + (float)((q & 1) * 8)) - uv.x, (pyb + (float)((q >> 1) * 8)) - uv.y, c2, up[q],
+                                   gr, gz);
+                }
+                reduce_record(s, j, gr, gz, lane, slot);
+            }
+            __syncthreads();
+        }
+        if (wave == 0) write_batch(a, s, lane, cnt);
+        hi -= cnt;
+    }
+}
+
+// Adjoint of 16x16 tiles: the first a.n_split workgroups take one tile each, the
+// others four (a tile per wave).
+template <bool EXT>
+__global__ __launch_bounds__(256, EXT ? 4 : 5) void k_render_bwd16(RenderArgs a) {
+    __shared__ union {
+        BwdStage<EXT> wave[4];
+        BwdSplit<EXT> split;
+    } S;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (blockIdx.x < a.n_split) {
+        bwd_split_tile<EXT>(a, a.worklist[blockIdx.x], wave, S.split);
+        return;
+    }
+    const uint32_t item = a.n_split + 4u * (blockIdx.x - a.n_split) + wave;
+    if (item < a.n_items) bwd_wave_tile<EXT>(a, a.worklist[item], S.wave[wave]);
+}
+
+// A workgroup of one wave per tile.
+template <bool EXT>
+__global__ __launch_bounds__(64) void k_render_bwd16_wave(RenderArgs a) {
+    __shared__ BwdStage<EXT> S;
+    bwd_wave_tile<EXT>(a, a.worklist[blockIdx.x], S);
 }
 
 template <int TW, int TH>
@@ -783,6 +1022,18 @@ hipError_t bwd_shape(const RenderArgs& a, hipStream_t s) {
 // take 944, 991 and (2,530 ->) 3,080 us, because a quadrant wave reads every record
 // from LDS for 64 pixels instead of 256.
 uint32_t fwd_split_tiles(uint32_t n_items) { return n_items <= 8192u ? n_items : 1024u; }
+
+// The 16x16 adjoint's tiles with four waves each: all of them up to 4,096 (one wave
+// takes 300 ns per list position and the chip's wave slots would be filled once or
+// less: 270 -> 147 us on 64 tiles, 360 -> 218 us on 3,024; 6,048 tiles would take 475
+// us instead of 410), the worklist's first 256 up to 32,768 (2,000 -> 1,826 us on
+// 24,842 tiles of views at 1/8 .. 1 of 1600x1064, where the longest list alone took
+// the whole time, 510 -> 346 us on 8,487, 403 against 410 us on 6,048).  Above that a
+// wave slot takes six tiles or more and no list sets the end: one-wave
+// workgroups, whose slots free up singly, take 1,790 us on 33,948 tiles and 5.55 ms
+// on 130,560 against 1,890 us and 5.77 ms with four waves to a workgroup.
+constexpr uint32_t kBwdMixedMax = 32768u;
+uint32_t bwd_split_tiles(uint32_t n_items) { return n_items <= 4096u ? n_items : 256u; }
 
 }  // namespace
 
@@ -824,14 +1075,17 @@ hipError_t launch_render_bwd(const RenderArgs& a, int tw, int th, int batch, hip
         if (a.st.variant == 1)  // one workgroup of 4 waves per tile
             return batch >= 128 ? bwd_shape<16, 16, 128>(a, s) : bwd_shape<16, 16, 64>(a, s);
         const bool ext = a.dL_ddepth || a.dL_dalpha;
-        const dim3 grid(a.n_items), block(64);
-        if (ext) {
-            if (batch == 32) hipLaunchKernelGGL((k_render_bwd_wave16<32, true>), grid, block, 0, s, a);
-            else hipLaunchKernelGGL((k_render_bwd_wave16<64, true>), grid, block, 0, s, a);
-        } else {
-            if (batch == 32) hipLaunchKernelGGL((k_render_bwd_wave16<32, false>), grid, block, 0, s, a);
-            else hipLaunchKernelGGL((k_render_bwd_wave16<64, false>), grid, block, 0, s, a);
+        if (a.n_items > kBwdMixedMax) {
+            const dim3 grid(a.n_items), block(64);
+            if (ext) hipLaunchKernelGGL((k_render_bwd16_wave<true>), grid, block, 0, s, a);
+            else hipLaunchKernelGGL((k_render_bwd16_wave<false>), grid, block, 0, s, a);
+            return hipGetLastError();
         }
+        RenderArgs b = a;
+        b.n_split = bwd_split_tiles(a.n_items);
+        const dim3 grid(b.n_split + (a.n_items - b.n_split + 3) / 4), block(256);
+        if (ext) hipLaunchKernelGGL((k_render_bwd16<true>), grid, block, 0, s, b);
+        else hipLaunchKernelGGL((k_render_bwd16<false>), grid, block, 0, s, b);
         return hipGetLastError();
     }
     if (tw == 8 && th == 8) return bwd_shape<8, 8, 64>(a, s);

@@ -74,3 +74,43 @@ def test_forward_paths_agree_bitwise(name, channels):
         f = v1.render_fwd(proj, v1.bin(proj, sp.n), sp.n)
         for k in ("image", "final_T", "n_contrib"):
             np.testing.assert_array_equal(f[k].cpu().numpy(), outs[0][k], err_msg=k)
+
+
+@pytest.mark.parametrize("name", [k for k in SCENES if k != "wide"])
+@pytest.mark.parametrize("channels", [False, True])
+def test_adjoint_paths_agree_bitwise(name, channels):
+    """The adjoint takes every tile with four waves where tiles are few, the
+    worklist's first 256 up to 32,768 tiles and none above: a view's screen-space
+    gradients are the same alone and beside a view that brings the batch to each."""
+    import copy
+
+    import torch
+    scene = SCENES[name]()
+    n, V = scene.n, scene.n_views
+    sp = splats_of(scene)
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    P = scene.n_pixels
+    up = [torch.randn(k, generator=gen, device="cuda") for k in (3 * P, P, P)]
+    ref, tiles = None, []
+    for pad in (None, (1500, 1100), (4200, 2200)):
+        s = copy.copy(scene)
+        s.cameras = list(scene.cameras) + ([gi.look_at((0.0, 0.0, -4.0), width=pad[0], height=pad[1])] if pad else [])
+        rast = _rast(s)
+        proj = rast.project(sp)
+        bins = rast.bin(proj, n)
+        f = rast.render_fwd(proj, bins, n, channels=channels)
+        Q = rast.n_pixels
+        dL = [torch.zeros(k, device="cuda") for k in (3 * Q, Q, Q)]
+        for d, u in zip(dL, up):
+            d[:u.numel()] = u
+        if pad:
+            dL[0][3 * P:] = 0.25
+        ws = rast.render_bwd_tiles(proj, bins, n, f["final_T"], f["n_contrib"], dL[0],
+                                   dL_ddepth=dL[1] if channels else None, dL_dalpha=dL[2] if channels else None)
+        g = rast.project_bwd(sp, proj, bins, ws, want_grad2d=True)["grad2d"][:n * V * 12].cpu().numpy()
+        tiles.append(bins["total_tiles"])
+        if ref is None:
+            ref = g
+            assert np.abs(g).max() > 0
+        np.testing.assert_array_equal(g, ref, err_msg=str(pad))
+    assert 4096 < tiles[1] <= 32768 < tiles[2]

@@ -308,9 +308,10 @@ gesr_status gesr_render_fwd_ext(gesr_ctx* ctx, const gesr_proj* proj, const gesr
  * projection adjoint, summed over views in ascending order.
  * `workspace` (DEVICE, gesr_sizes.bwd_workspace_bytes) holds, in order and
  * 256-byte aligned: the visited bits (uint32 [ceil(m_cap / 32)], one bit per
- * instance slot), the screen-space gradients (float [V*n][12]) and the
- * per-instance partials (float [m_cap][12], indexed by instance slot, see
- * inst_base).  grad2d (DEVICE [V*n][12], 16-byte aligned, nullable) receives
+ * instance slot), the screen-space gradients (float [V*n][12]; the rows of
+ * pairs that no tile reached are not written), the per-instance partials (float
+ * [m_cap][12], indexed by instance slot, see inst_base) and a bit per pair, set
+ * where its row is written.  grad2d (DEVICE [V*n][12], 16-byte aligned, nullable) receives
  * the screen-space gradients du, dv, dL00, dL10, dL11, dopacity, dbeta, dr,
  * dg, db, dz and a zero pad (dbeta here is the falloff term only; the
  * phi(beta) term is added in the projection adjoint; dz, the gradient of the

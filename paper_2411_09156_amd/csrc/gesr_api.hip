@@ -232,6 +232,7 @@ struct BwdWorkspace {
     uint32_t* visited;   // [ceil(m_cap / 32)] bit per instance slot
     float* grad2d;       // [V*n][GESR_GRAD2D_FLOATS]
     float* partials;     // [m_cap][kPartialStride]
+    uint32_t* nonzero;   // [seg_nonzero_words] bit per pair with a gradient
     size_t bytes;
 };
 
@@ -247,6 +248,7 @@ BwdWorkspace carve_bwd(void* base, uint64_t vn, uint64_t m_cap, uint64_t T) {
     w.visited = (uint32_t*)take(((m_cap + 31) / 32) * 4);
     w.grad2d = (float*)take((vn > 0 ? vn : 1) * GESR_GRAD2D_FLOATS * 4);
     w.partials = (float*)take(m_cap * kPartialStride * 4);
+    w.nonzero = (uint32_t*)take(seg_nonzero_words(vn) * 4);
     w.bytes = off;
     return w;
 }
@@ -699,6 +701,8 @@ gesr_status gesr_project_bwd(gesr_ctx* ctx, const gesr_splats* splats, const ges
     r.partials = ws.partials;
     r.m_cap = bins->m_cap;
     r.grad2d = g2;
+    r.nonzero = ws.nonzero;
+    r.all_rows = grad2d != nullptr;
     GESR_TRY(hip_check(ctx, launch_seg_reduce(r, (hipStream_t)stream), "seg_reduce launch"));
     ProjectBwdArgs b;
     b.n = splats->n;
@@ -708,8 +712,8 @@ gesr_status gesr_project_bwd(gesr_ctx* ctx, const gesr_splats* splats, const ges
     b.opacity = splats->opacity;
     b.beta = splats->beta;
     b.sh = splats->sh;
-    b.tiles_touched = proj->tiles_touched;
     b.grad2d = g2;
+    b.nonzero = ws.nonzero;
     b.g_mean = out->mean;
     b.g_scale = out->scale;
     b.g_quat = out->quat;

@@ -22,8 +22,8 @@ struct ProjectArgs {
 struct ProjectBwdArgs {
     int n;
     const float *mean, *scale, *quat, *opacity, *beta, *sh;
-    const uint32_t* tiles_touched;
-    const float* grad2d;  // [V*n][GESR_GRAD2D_FLOATS] screen-space gradients
+    const float* grad2d;      // [V*n][GESR_GRAD2D_FLOATS] screen-space gradients
+    const uint32_t* nonzero;  // bit per pair: its row of grad2d is written and not zero
     float *g_mean, *g_scale, *g_quat, *g_opacity, *g_beta, *g_sh;
     DevSettings st;
     DevCams cams;
@@ -39,7 +39,11 @@ struct SegReduceArgs {
     const float* partials;
     uint64_t m_cap;
     float* grad2d;
+    uint32_t* nonzero;  // [seg_nonzero_words(vn)] bit per pair: a tile reached it
+    bool all_rows;      // write the zero rows of grad2d too
 };
+// Words of the pair bits (whole 256-pair workgroups).
+inline uint64_t seg_nonzero_words(uint64_t vn) { return (vn + 255) / 256 * 8; }
 
 struct RenderArgs {
     int n;

@@ -114,3 +114,32 @@ def test_adjoint_paths_agree_bitwise(name, channels):
             assert np.abs(g).max() > 0
         np.testing.assert_array_equal(g, ref, err_msg=str(pad))
     assert 4096 < tiles[1] <= 32768 < tiles[2]
+
+
+def _giant():
+    s = gi.tiny_scene(8, n=40, width=700, height=520, deg=1)
+    s.scales[::2] = np.float32(0.9)  # half of the pairs over hundreds of instance slots
+    return s
+
+
+@pytest.mark.parametrize("name", ["ragged", "one-splat", "needles", "opaque", "drt-20k", "giant"])
+def test_gradients_with_and_without_all_rows(name):
+    """Pairs that no tile reached have no row of screen-space gradients unless the
+    caller asks for them: the parameter gradients are the same either way."""
+    import torch
+    scene = _giant() if name == "giant" else SCENES[name]()
+    rast, sp = _rast(scene), splats_of(scene)
+    f = rast.forward(sp)
+    dL = torch.randn(3 * rast.n_pixels, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+    dL[:dL.numel() // 2] = 0.0  # many tiles without a gradient
+    out = []
+    for rows in (False, True):
+        ws = rast.alloc_workspace(sp.n, f["bins"]["m_cap"])
+        ws.fill_(0xFF)  # NaN wherever a row or partial is not written
+        rast.render_bwd_tiles(f["proj"], f["bins"], sp.n, f["final_T"], f["n_contrib"], dL, workspace=ws)
+        g = rast.project_bwd(sp, f["proj"], f["bins"], ws, want_grad2d=rows)
+        out.append({k: v.cpu().numpy() for k, v in g.items()})
+    assert np.isfinite(out[1]["grad2d"]).all()
+    for k in out[0]:
+        assert np.isfinite(out[0][k]).all(), k
+        np.testing.assert_array_equal(out[0][k], out[1][k], err_msg=k)

@@ -104,7 +104,7 @@ __device__ __forceinline__ void frame_affine(const Frame& fr, const float x0[3],
 }
 
 // o exp(-kappa (m^2)^(beta/2)) for m^2 = |a + s b|^2
-__device__ __forceinline__ float affine_term(const Affine& f, float s, const DevSettings& st) {
+__device__ __forceinline__ float affine_term(const Affine& f, float s, float neg_kappa_log2e) {
     float m2 = 0.f;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -112,49 +112,75 @@ __device__ __forceinline__ float affine_term(const Affine& f, float s, const Dev
         m2 = fmaf(y, y, m2);
     }
     const float P = hw_exp2(f.half_beta * hw_log2(m2));  // 0 at m2 = 0
-    return f.o * hw_exp2(st.neg_kappa_log2e * P);
+    return f.o * hw_exp2(neg_kappa_log2e * P);
 }
 
 // Calls body(frame, list position) for every candidate of pixel (px, py)
 // among the list entries rg.x + u, + S, + 2S, ... (u: the lane's place among
 // the S lanes of its ray): the splats whose screen footprint covers the pixel
-// (q <= qmax, the renderers' test).  The next entry's splat id is loaded while
-// the current entry is processed.
+// (q <= qmax, the renderers' test).  An entry's records are loaded while the one
+// before is processed, its splat id while the one before that is.  pair0: the view's
+// first pair.
 template <int S, class F>
-__device__ __forceinline__ void for_candidates(const SurfaceArgs& A, uint2 rg, uint32_t u, float px, float py,
-                                               F&& body) {
+__device__ __forceinline__ void for_candidates(const SurfaceArgs& A, uint2 rg, uint32_t pair0, uint32_t u, float px,
+                                               float py, F&& body) {
     uint32_t k = rg.x + u;
-    uint32_t vi = k < rg.y ? A.val_sorted[k] : 0u;
+    auto id_at = [&](uint32_t pos) { return pos < rg.y ? A.val_sorted[pos] : pair0; };
+    uint32_t vi = id_at(k), vn = id_at(k + S);
+    float4 ra, rb, na, nb;
+    Frame fr, fn;
+    auto load = [&](uint32_t id, float4& a, float4& b, Frame& f) {
+        const float4* r = reinterpret_cast<const float4*>(A.rec + (size_t)id * GESR_REC_FLOATS);
+        a = r[0];
+        b = r[1];
+        load_frame(A.frames, id - pair0, f);
+    };
+    if (k < rg.y) load(vi, ra, rb, fr);
     for (; k < rg.y; k += S) {
-        const float4* r = reinterpret_cast<const float4*>(A.rec + (size_t)vi * GESR_REC_FLOATS);
-        const float4 ra = r[0], rb = r[1];
-        Frame fr;
-        load_frame(A.frames, vi % (uint32_t)A.n, fr);
-        const uint32_t kn = k + S;
-        vi = kn < rg.y ? A.val_sorted[kn] : 0u;
+        if (k + S < rg.y) load(vn, na, nb, fn);
+        vn = id_at(k + 2 * S);
         Fragment f;
         if (ges_q(ra, rb.x, px, py, f) <= rb.w) body(fr, k);
+        ra = na;
+        rb = nb;
+        fr = fn;
     }
 }
 
-// Sum over the L lanes of a ray's group (xor steps stay inside the group).
-template <int L>
-__device__ __forceinline__ float lane_group_sum(float x) {
+// Eight rays per wave, eight lanes each (lane = place in the ray * 8 + ray).  Rays of
+// the same tile (the caller passes pixels grouped by tile) traverse the same list in
+// lockstep, so the lanes that load one entry for different rays hit the same
+// addresses; rays of different tiles are simply handled side by side.  Those lanes are
+// neighbours: the cache serves a load four lanes at a time, and with a ray's own lanes
+// side by side instead every four lanes asked for four lines, which bound the kernel.
+constexpr int kRaysPerWave = 8, kLanesPerRay = 64 / kRaysPerWave;
+
+// Sum over the lanes of a ray (lane = u * kRaysPerWave + ray).
+__device__ __forceinline__ float ray_sum(float x) {
 #pragma unroll
-    for (int m = L / 2; m >= 1; m >>= 1) x += __shfl_xor(x, m, 64);
+    for (int m = kLanesPerRay / 2; m >= 1; m >>= 1) x += __shfl_xor(x, m * kRaysPerWave, 64);
     return x;
 }
 
-// Eight rays per wave, eight lanes each.  Rays of the same tile (the caller
-// passes pixels grouped by tile) traverse the same list in lockstep, so the
-// lanes that load one entry for different rays hit the same addresses; rays of
-// different tiles are simply handled side by side.
-constexpr int kRaysPerWave = 8, kLanesPerRay = 64 / kRaysPerWave;
 
-__global__ __launch_bounds__(64) void k_surface_points(SurfaceArgs A) {
+// Four waves share a group of eight rays.  Pass 1 (an exact maximum) takes every
+// fourth set of list entries per wave; in pass 2 each wave takes a quarter of the
+// samples over the whole list, which leaves every sample's sum in its former order;
+// pass 3 runs on the first wave.  65,536 rays of 32 samples on 100k shell splats (1,300
+// list entries a ray, up to 5,300): 3.5 ms with one wave per group and a ray's lanes
+// side by side, 3.1 ms with one wave and the lanes of an entry side by side, 2.5 ms
+// with two waves, 2.4 ms with four (a quarter of the registers for samples, and the
+// longest lists end sooner).  FULL: all kMaxSamples samples, as straight-line code.
+constexpr int kSurfWaves = 4, kSurfPart = kMaxSamples / kSurfWaves;
+
+template <bool FULL>
+__global__ __launch_bounds__(64 * kSurfWaves) void k_surface_points(SurfaceArgs A) {
     __shared__ float sPart[64][kMaxSamples + 1];
     __shared__ float sDen[kRaysPerWave][kMaxSamples];
-    const uint32_t lane = __lane_id(), slot = lane / kLanesPerRay, u = lane % kLanesPerRay;
+    __shared__ float sBest[kSurfWaves][kRaysPerWave];
+    __shared__ uint32_t sPos[kSurfWaves][kRaysPerWave], sCand[kSurfWaves][kRaysPerWave];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t lane = __lane_id(), slot = lane % kRaysPerWave, u = lane / kRaysPerWave;
     const uint32_t ray = blockIdx.x * kRaysPerWave + slot;
     const bool has_ray = ray < A.n_rays;
     const DevSettings& st = A.st;
@@ -163,10 +189,12 @@ __global__ __launch_bounds__(64) void k_surface_points(SurfaceArgs A) {
     int v = 0;
     while (v + 1 < A.cams.V && views[v + 1].pix_base <= pix) ++v;
     const DevView& w = views[v];
+    const uint32_t pair0 = (uint32_t)v * (uint32_t)A.n;
+    const float nk = in_vgpr(st.neg_kappa_log2e);
     const uint32_t local = pix - w.pix_base;
     const int px = (int)(local % (uint32_t)w.W), py = (int)(local / (uint32_t)w.W);
     const float alpha = has_ray ? A.alpha[pix] : 0.f, depth = has_ray ? A.depth[pix] : 0.f;
-    if (has_ray && u == 0) {
+    if (has_ray && threadIdx.x == slot) {
         reinterpret_cast<float4*>(A.points)[ray] = make_float4(0.f, 0.f, 0.f, 0.f);
         reinterpret_cast<float4*>(A.normals)[ray] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (A.dominant) A.dominant[ray] = 0xFFFFFFFFu;
@@ -188,11 +216,11 @@ __global__ __launch_bounds__(64) void k_surface_points(SurfaceArgs A) {
     // pass 1: the dominating splat at x0 (largest term; ties to the earliest list position)
     float best = -1.0f;
     uint32_t best_pos = 0xFFFFFFFFu, ncand = 0;
-    for_candidates<kLanesPerRay>(A, rg, u, fpx, fpy, [&](const Frame& fr, uint32_t k) {
+    for_candidates<kSurfWaves * kLanesPerRay>(A, rg, pair0, wave * kLanesPerRay + u, fpx, fpy, [&](const Frame& fr, uint32_t k) {
         ++ncand;
         Affine f;
         frame_affine(fr, x0, wd, f);
-        const float val = affine_term(f, 0.0f, st);
+        const float val = affine_term(f, 0.0f, nk);
         if (val > best) {
             best = val;
             best_pos = k;
@@ -200,23 +228,41 @@ __global__ __launch_bounds__(64) void k_surface_points(SurfaceArgs A) {
     });
 #pragma unroll
     for (int m = kLanesPerRay / 2; m >= 1; m >>= 1) {
-        const float ob = __shfl_xor(best, m, 64);
-        const uint32_t op = (uint32_t)__shfl_xor((int)best_pos, m, 64);
+        const float ob = __shfl_xor(best, m * kRaysPerWave, 64);
+        const uint32_t op = (uint32_t)__shfl_xor((int)best_pos, m * kRaysPerWave, 64);
         if (ob > best || (ob == best && op < best_pos)) {
             best = ob;
             best_pos = op;
         }
     }
-    const uint32_t tot = (uint32_t)lane_group_sum<kLanesPerRay>((float)ncand);  // exact below 2^24
-    if (live && u == 0 && A.n_candidates) A.n_candidates[ray] = tot;
+    uint32_t tot = (uint32_t)ray_sum((float)ncand);  // exact below 2^24
+    if (u == 0) {
+        sBest[wave][slot] = best;
+        sPos[wave][slot] = best_pos;
+        sCand[wave][slot] = tot;
+    }
+    __syncthreads();
+    tot = 0;
+#pragma unroll
+    for (int v2 = 0; v2 < kSurfWaves; ++v2) {
+        const float ob = sBest[v2][slot];
+        const uint32_t op = sPos[v2][slot];
+        if (ob > best || (ob == best && op < best_pos)) {
+            best = ob;
+            best_pos = op;
+        }
+        tot += sCand[v2][slot];
+    }
+    const bool first = threadIdx.x == slot;
+    if (live && first && A.n_candidates) A.n_candidates[ray] = tot;
     live = live && best_pos != 0xFFFFFFFFu;
     const uint32_t g_vi = live ? A.val_sorted[best_pos] : 0u;
-    if (live && u == 0 && A.dominant) A.dominant[ray] = g_vi;
+    if (live && first && A.dominant) A.dominant[ray] = g_vi;
     // sigma_g(w) = |M_g^T w| = |diag(ps) R^T w|
     float sg = 0.f;
     if (live) {
         float R[9], ps[3];
-        splat_frame(A, g_vi % (uint32_t)A.n, R, ps);
+        splat_frame(A, g_vi - pair0, R, ps);
         float acc = 0.f;
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
@@ -226,30 +272,33 @@ __global__ __launch_bounds__(64) void k_surface_points(SurfaceArgs A) {
         sg = sqrtf(acc);
     }
     if (!live) rg = make_uint2(0u, 0u);
-    const int K = A.n_samples;
+    const int K = FULL ? kMaxSamples : A.n_samples;
     const float step = 2.0f * A.span * sg / (float)(K - 1), s0 = -A.span * sg;
 
-    // pass 2: partial densities of the K samples
-    float part[kMaxSamples];
+    // pass 2: partial densities of this wave's samples
+    const int j0 = (int)wave * kSurfPart;
+    float part[kSurfPart];
 #pragma unroll
-    for (int k = 0; k < kMaxSamples; ++k) part[k] = 0.f;
-    for_candidates<kLanesPerRay>(A, rg, u, fpx, fpy, [&](const Frame& fr, uint32_t) {
-        Affine f;
-        frame_affine(fr, x0, wd, f);
+    for (int k = 0; k < kSurfPart; ++k) part[k] = 0.f;
+    if (FULL || j0 < K)
+        for_candidates<kLanesPerRay>(A, rg, pair0, u, fpx, fpy, [&](const Frame& fr, uint32_t) {
+            Affine f;
+            frame_affine(fr, x0, wd, f);
 #pragma unroll
-        for (int j = 0; j < kMaxSamples; ++j)
-            if (j < K) part[j] += affine_term(f, fmaf((float)j, step, s0), st);
-    });
+            for (int j = 0; j < kSurfPart; ++j)
+                if (FULL || j0 + j < K) part[j] += affine_term(f, fmaf((float)(j0 + j), step, s0), nk);
+        });
 #pragma unroll
-    for (int j = 0; j < kMaxSamples; ++j) sPart[lane][j] = part[j];
+    for (int j = 0; j < kSurfPart; ++j) sPart[lane][j0 + j] = part[j];
     __syncthreads();
     // densities: sample j of the ray summed over its lanes in lane order
-    for (int j = (int)u; j < K; j += kLanesPerRay) {
+    for (int j = j0 + (int)u; j < min(j0 + kSurfPart, K); j += kLanesPerRay) {
         float d = 0.f;
-        for (int l = 0; l < kLanesPerRay; ++l) d += sPart[slot * kLanesPerRay + l][j];
+        for (int l = 0; l < kLanesPerRay; ++l) d += sPart[l * kRaysPerWave + slot][j];
         sDen[slot][j] = d;
     }
     __syncthreads();
+    if (wave != 0) return;
     int kc = -1;
     if (live)
         for (int k = 0; k + 1 < K; ++k)
@@ -268,7 +317,7 @@ __global__ __launch_bounds__(64) void k_surface_points(SurfaceArgs A) {
     // pass 3: density gradient at x0 + ss w
     float gd[3] = {0.f, 0.f, 0.f};
     const float xs[3] = {x0[0] + ss * wd[0], x0[1] + ss * wd[1], x0[2] + ss * wd[2]};
-    for_candidates<kLanesPerRay>(A, rg, u, fpx, fpy, [&](const Frame& fr, uint32_t) {
+    for_candidates<kLanesPerRay>(A, rg, pair0, u, fpx, fpy, [&](const Frame& fr, uint32_t) {
         const float d[3] = {xs[0] - fr.mu[0], xs[1] - fr.mu[1], xs[2] - fr.mu[2]};
         float y[3], m2 = 0.f;
 #pragma unroll
@@ -279,7 +328,7 @@ __global__ __launch_bounds__(64) void k_surface_points(SurfaceArgs A) {
         if (!(m2 > 0.f)) return;  // at the centre the gradient vanishes
         const float l2 = hw_log2(m2);
         const float P = hw_exp2(fr.half_beta * l2);
-        const float G = fr.o * hw_exp2(st.neg_kappa_log2e * P);
+        const float G = fr.o * hw_exp2(nk * P);
         // grad = -kappa beta (m^2)^(beta/2 - 1) G M^-T y
         const float coef = -st.kappa * 2.0f * fr.half_beta * hw_exp2((fr.half_beta - 1.0f) * l2) * G;
 #pragma unroll
@@ -287,7 +336,7 @@ __global__ __launch_bounds__(64) void k_surface_points(SurfaceArgs A) {
             gd[a] = fmaf(coef, fr.m[a] * y[0] + fr.m[3 + a] * y[1] + fr.m[6 + a] * y[2], gd[a]);
     });
 #pragma unroll
-    for (int a = 0; a < 3; ++a) gd[a] = lane_group_sum<kLanesPerRay>(gd[a]);
+    for (int a = 0; a < 3; ++a) gd[a] = ray_sum(gd[a]);
     const float gn = sqrtf(gd[0] * gd[0] + gd[1] * gd[1] + gd[2] * gd[2]);
     if (live && gn > 0.f && u == 0) {
         reinterpret_cast<float4*>(A.points)[ray] = make_float4(xs[0], xs[1], xs[2], 1.0f);
@@ -301,8 +350,9 @@ hipError_t launch_surface_points(const SurfaceArgs& a, hipStream_t stream) {
     if (a.n_rays == 0) return hipSuccess;
     if (a.n_samples < 2 || a.n_samples > kMaxSamples) return hipErrorInvalidValue;
     if (a.n > 0) hipLaunchKernelGGL(k_surface_frames, dim3((a.n + 255) / 256), dim3(256), 0, stream, a);
-    hipLaunchKernelGGL(k_surface_points, dim3((a.n_rays + kRaysPerWave - 1) / kRaysPerWave), dim3(64), 0, stream,
-                       a);
+    const dim3 grid((a.n_rays + kRaysPerWave - 1) / kRaysPerWave), block(64 * kSurfWaves);
+    if (a.n_samples == kMaxSamples) hipLaunchKernelGGL(k_surface_points<true>, grid, block, 0, stream, a);
+    else hipLaunchKernelGGL(k_surface_points<false>, grid, block, 0, stream, a);
     return hipGetLastError();
 }
 

@@ -172,7 +172,7 @@ struct BinScratch {
     uint2* srect;                                         // rectangles in (view, depth) order, [V*n]
     float4* sell;                                         // footprint ellipses in that order, [2 V*n]
     uint32_t *row_count, *row_start;                      // [total rows]
-    uint32_t *seg_chunks, *chunk_off;                     // [segments + 1]
+    uint32_t* chunk_off;                                  // [segments + 1]
     uint32_t* mat;                                        // per-chunk bucket counts
     uint64_t mat_chunks;
     uint32_t* counters;                                   // [4]: row-list entries, overflow, listed
@@ -207,7 +207,6 @@ BinScratch carve(void* base, const Geometry& g, const DevCams& dc, int n, uint64
     s.sell = reinterpret_cast<float4*>(take(8 * vn1));
     s.row_count = take(g.total_rows + 1);
     s.row_start = take(g.total_rows + 1);
-    s.seg_chunks = take(nseg);
     s.chunk_off = take(nseg);
     s.mat_chunks = std::max(is_chunk_bound(dc, 1, n, 0), is_chunk_bound(dc, 2, n, m_cap));
     s.mat = take(s.mat_chunks * is_window());
@@ -414,22 +413,30 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
     hipStream_t strm = (hipStream_t)stream;
     const uint64_t T = g.total_tiles;
 
-    // 1. (view, depth, pair) order of the (view, splat) pairs: LSD passes over
-    //    the 32 depth bits and then the view bits, which the last pass or two
-    //    take from the pair index (view = pair / n)
+    // 1. (view, depth, pair) order of the (view, splat) pairs.  Eight-bit digits (the
+    //    default): each view's pairs by their 32 depth bits, the counts in the part of the
+    //    scratch that holds the ellipses later; narrower ones: LSD passes over the 32
+    //    depth bits and then the view bits, which the last pass or two take from the pair
+    //    index (view = pair / n)
     SortBuffers db{s.d_keys_a, s.d_vals_a, s.d_keys_b, s.d_vals_b, s.block_hist, s.scan_partials};
-    bool in_b = false;
-    const int vbits = bits_for((uint64_t)V);
-    GESR_TRY(hip_check(ctx,
-                       radix_sort(proj->depth_key, nullptr, g.vn, nullptr, 32 + vbits, st->radix_bits, db, &in_b,
-                                  strm, vbits > 0 ? (uint32_t)n : 0u),
-                       "depth and view sort"));
-    const uint32_t* order_vd = in_b ? s.d_vals_b : s.d_vals_a;
-    // 2. instance slots: exclusive scan of tiles_touched in pair order; M -> counters[0]
+    uint32_t* order_vd = nullptr;
+    if (st->radix_bits == 8) {
+        db.block_hist = reinterpret_cast<uint32_t*>(s.sell);
+        GESR_TRY(hip_check(ctx, depth_sort(proj->depth_key, (uint32_t)n, (uint32_t)V, db, &order_vd, strm), "depth sort"));
+    } else {
+        bool in_b = false;
+        const int vbits = bits_for((uint64_t)V);
+        GESR_TRY(hip_check(ctx,
+                           radix_sort(proj->depth_key, nullptr, g.vn, nullptr, 32 + vbits, st->radix_bits, db, &in_b,
+                                      strm, vbits > 0 ? (uint32_t)n : 0u),
+                           "depth and view sort"));
+        order_vd = in_b ? s.d_vals_b : s.d_vals_a;
+    }
+    // 2. instance slots: exclusive scan of tiles_touched in pair order; M and its
+    //    capacity words -> counters
     GESR_TRY(hip_check(ctx, scan_exclusive(proj->tiles_touched, bins->inst_base, g.vn, s.scan_partials,
-                                           bins->counters, strm),
+                                           bins->counters, strm, bins->m_cap),
                        "instance slots"));
-    GESR_TRY(hip_check(ctx, launch_set_counters(bins->counters, bins->m_cap, strm), "counters"));
     if (flags & GESR_BIN_SYNC) {
         uint32_t m = 0;
         GESR_TRY(hip_check(ctx, hipMemcpyAsync(&m, bins->counters, sizeof m, hipMemcpyDeviceToHost, strm), "M copy"));
@@ -462,11 +469,11 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
     l1.item_ell = s.sell;  // each row entry carries its own row's columns
     l1.tile_w = st->tile_w;
     l1.tile_h = st->tile_h;
-    GESR_TRY(hip_check(ctx,
-                       launch_interval_scatter(l1, 1, (uint32_t)g.total_rows, s.counters, s.seg_chunks,
-                                               s.scan_partials, strm),
-                       "row lists"));
-    GESR_TRY(hip_check(ctx, launch_set_counters(s.counters, bins->m_cap, strm), "row counters"));
+    GESR_TRY(hip_check(ctx, launch_interval_lists(l1, 1, strm), "row list counts"));
+    GESR_TRY(hip_check(ctx, scan_exclusive(s.row_count, s.row_start, g.total_rows, s.scan_partials, s.counters, strm,
+                                           bins->m_cap),
+                       "row list starts"));
+    GESR_TRY(hip_check(ctx, launch_interval_scatter(l1, 1, strm), "row lists"));
     // 4. tile lists: every row-list entry in the tiles of its columns (level 2)
     IsArgs l2 = ia;
     l2.items = s.rowlist;
@@ -479,19 +486,22 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
     l2.out_vals = bins->val_sorted;
     l2.out_keys = bins->tile_sorted;
     l2.out_cap = bins->m_cap;
-    GESR_TRY(hip_check(ctx,
-                       launch_interval_scatter(l2, 2, (uint32_t)T, bins->counters + 3, s.seg_chunks, s.scan_partials,
-                                               strm),
-                       "tile lists"));
-    GESR_TRY(hip_check(ctx, launch_ranges_from_counts(s.tile_count, s.tile_start, T, bins->counters + 2,
-                                                      bins->ranges, strm),
-                       "ranges"));
-    // 5. worklist: tiles by decreasing list length, or by decreasing work of a
-    //    previous forward (the positions each tile evaluated before terminating)
-    const uint32_t* work = (flags & GESR_BIN_WORK_ORDER) ? bins->tile_work : nullptr;
-    GESR_TRY(hip_check(ctx, launch_worklist_keys(bins->ranges, work, T, s.w_keys_b, strm), "worklist keys"));
-    SortBuffers wb{s.w_keys_a, s.w_vals_a, s.w_keys_b, bins->worklist, s.block_hist, s.scan_partials};
-    GESR_TRY(hip_check(ctx, radix_sort(s.w_keys_b, nullptr, T, nullptr, 16, 8, wb, &in_b, strm), "worklist sort"));
+    GESR_TRY(hip_check(ctx, launch_interval_lists(l2, 2, strm), "tile list counts"));
+    // 5. list starts, ranges, and the worklist: tiles by decreasing list length, or by
+    //    decreasing work of a previous forward (the positions each tile evaluated
+    //    before terminating)
+    TileListArgs tl;
+    tl.total_tiles = T;
+    tl.counts = s.tile_count;
+    tl.starts = s.tile_start;
+    tl.total = bins->counters + 3;
+    tl.listed = bins->counters + 2;
+    tl.work = (flags & GESR_BIN_WORK_ORDER) ? bins->tile_work : nullptr;
+    tl.ranges = bins->ranges;
+    tl.worklist = bins->worklist;
+    tl.sort = SortBuffers{s.w_keys_a, s.w_vals_a, s.w_keys_b, nullptr, s.block_hist, s.scan_partials};
+    GESR_TRY(hip_check(ctx, launch_tile_lists(tl, strm), "tile list starts"));
+    GESR_TRY(hip_check(ctx, launch_interval_scatter(l2, 2, strm), "tile lists"));
     ctx->err.clear();
     return GESR_OK;
 }

@@ -5,8 +5,8 @@
 // Every instance is ordered by the 64-bit key (global tile id << 32 | depth
 // bits), ties by (view, splat) index.  All instances of one (view, splat)
 // share its depth and its tiles form a rectangle, so no instance is ever
-// sorted: the (view, splat) pairs are radix-sorted by depth and then stably
-// by view; each pair is written, in that order, into the row lists of the
+// sorted: the (view, splat) pairs are radix-sorted by depth within their
+// view; each pair is written, in that order, into the row lists of the
 // tile rows its rectangle covers, and each row-list entry into the tile lists
 // of the columns it covers.  Both writes are stable bucketings, so every tile
 // list holds its instances in exactly the order of the stable key sort.
@@ -68,54 +68,67 @@ __global__ __launch_bounds__(256) void k_scan_reduce(const uint32_t* in, uint64_
     if (threadIdx.x == 0) partials[blockIdx.x] = tot;
 }
 
-// One block of 1024 threads: exclusive scan of up to SCAN_TOP_MAX values
-// (in may equal out), the total to *total (nullable).
-__global__ __launch_bounds__(1024) void k_scan_single(const uint32_t* in, uint32_t* out, uint32_t count,
-                                                      uint32_t* total) {
-    __shared__ uint32_t s_wave[17];
-    constexpr int PER = SCAN_TOP_MAX / 1024;
-    const uint32_t t = threadIdx.x;
-    uint32_t v[PER];
-    uint32_t sum = 0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const uint32_t idx = t * PER + k;
-        v[k] = idx < count ? in[idx] : 0u;
-        sum += v[k];
+// The grand total of a scan, and with cap != 0 the capacity words behind it:
+// total[1] = total > cap, total[2] = min(total, cap).
+__device__ __forceinline__ void write_total(uint32_t* total, uint32_t m, uint64_t cap) {
+    if (!total) return;
+    total[0] = m;
+    if (cap != 0u) {
+        total[1] = (uint64_t)m > cap ? 1u : 0u;
+        total[2] = (uint32_t)((uint64_t)m > cap ? cap : m);
     }
-    uint32_t tot;
-    uint32_t run = block_exclusive_scan(sum, s_wave, &tot);
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const uint32_t idx = t * PER + k;
-        if (idx < count) out[idx] = run;
-        run += v[k];
-    }
-    if (t == 0 && total) *total = tot;
 }
 
-// One block of 1024 threads scans up to SCAN_TOP_MAX partials in place.
-__global__ __launch_bounds__(1024) void k_scan_top(uint32_t* partials, uint32_t nb, uint32_t* total) {
-    __shared__ uint32_t s_wave[17];
-    constexpr int PER = SCAN_TOP_MAX / 1024;
+// Exclusive scan of `count` values by one block of 1024 threads (in may equal
+// out), 4,096 at a time: coalesced loads, turned in LDS so that each thread scans
+// four consecutive ones.  Bound by a tile's chain (load, two barriers, store): 11 us
+// for 31,488 values and 4.5 for few; with 32 consecutive values per thread and
+// strided loads the former was 31.
+__device__ __forceinline__ uint32_t scan_by_block(const uint32_t* in, uint32_t* out, uint32_t count, uint32_t* s_tile,
+                                                  uint32_t* s_wave) {
     const uint32_t t = threadIdx.x;
-    uint32_t v[PER];
-    uint32_t sum = 0;
+    uint32_t run = 0, nx[4];
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        uint32_t idx = t * PER + k;
-        v[k] = idx < nb ? partials[idx] : 0u;
-        sum += v[k];
-    }
-    uint32_t tot;
-    uint32_t run = block_exclusive_scan(sum, s_wave, &tot);
+    for (int j = 0; j < 4; ++j) nx[j] = j * 1024u + t < count ? in[j * 1024u + t] : 0u;
+    for (uint32_t base = 0; base < count; base += 4096u) {
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        uint32_t idx = t * PER + k;
-        if (idx < nb) partials[idx] = run;
-        run += v[k];
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t l = j * 1024u + t, idx = base + 4096u + l;
+            s_tile[l + (l >> 5)] = nx[j];
+            nx[j] = idx < count ? in[idx] : 0u;
+        }
+        __syncthreads();
+        uint32_t v[4], sum = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t l = 4u * t + k;
+            v[k] = s_tile[l + (l >> 5)];
+            sum += v[k];
+        }
+        uint32_t tot, pre = run + block_exclusive_scan(sum, s_wave, &tot);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t l = 4u * t + k;
+            s_tile[l + (l >> 5)] = pre;
+            pre += v[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t l = j * 1024u + t;
+            if (base + l < count) out[base + l] = s_tile[l + (l >> 5)];
+        }
+        run += tot;
+        __syncthreads();
     }
-    if (t == 0 && total) *total = tot;
+    return run;
+}
+
+__global__ __launch_bounds__(1024) void k_scan_single(const uint32_t* in, uint32_t* out, uint32_t count,
+                                                      uint32_t* total, uint64_t cap) {
+    __shared__ uint32_t s_tile[4096 + 128], s_wave[17];
+    const uint32_t run = scan_by_block(in, out, count, s_tile, s_wave);
+    if (threadIdx.x == 0) write_total(total, run, cap);
 }
 
 __global__ __launch_bounds__(256) void k_scan_apply(const uint32_t* in, uint32_t* out, uint64_t count,
@@ -320,6 +333,196 @@ hipError_t sort_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, u
     else
         hipLaunchKernelGGL((k_radix_scatter<BITS, false>), dim3(nblocks), dim3(SORT_THREADS), 0, stream, kin, vin,
                            kout, vout, count_static, count_dev, shift, view_n, b.block_hist, nblocks);
+    return hipGetLastError();
+}
+
+// Stable sort of `count` <= 1024 * ITEMS words in LDS by their bits [lo, hi) in 8-bit
+// digits, by one block of 1024 threads; pay (nullable) moves along.  Each wave ranks a
+// contiguous share (ballots and its own running counts), so equal digits keep order.
+template <int ITEMS, bool PAY>
+__device__ __forceinline__ void lds_sort(uint32_t* s_key, uint32_t* s_pay, uint32_t count, int lo, int hi,
+                                         uint32_t (*s_hist)[256], uint32_t* s_start, uint32_t* s_wave) {
+    const uint32_t lane = __lane_id(), wave = threadIdx.x >> 6;
+    const uint32_t base = wave * (64u * ITEMS) + lane;
+    const uint64_t lt = lanemask_lt();
+    for (int sh = lo; sh < hi; sh += 8) {
+        for (uint32_t j = threadIdx.x; j < 16u * 256u; j += 1024u) (&s_hist[0][0])[j] = 0u;
+        __syncthreads();
+        uint32_t key[ITEMS], pay[ITEMS], rank[ITEMS];
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            const uint32_t idx = base + 64u * r;
+            const bool valid = idx < count;
+            key[r] = valid ? s_key[idx] : 0u;
+            pay[r] = PAY && valid ? s_pay[idx] : 0u;
+        }
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            const bool valid = base + 64u * r < count;
+            const uint32_t d = (key[r] >> sh) & 255u;
+            const uint64_t peers = match_digit<8>(d, __ballot(valid));
+            const uint32_t old = valid ? s_hist[wave][d] : 0u;
+            rank[r] = old + (uint32_t)__popcll(peers & lt);
+            if (valid && (peers & lt) == 0ull) s_hist[wave][d] = old + (uint32_t)__popcll(peers);
+        }
+        __syncthreads();
+        uint32_t cnt = 0;
+        if (threadIdx.x < 256u) {
+            for (int w = 0; w < 16; ++w) {
+                const uint32_t c = s_hist[w][threadIdx.x];
+                s_hist[w][threadIdx.x] = cnt;
+                cnt += c;
+            }
+        }
+        uint32_t tot;
+        const uint32_t ds = block_exclusive_scan(cnt, s_wave, &tot);
+        if (threadIdx.x < 256u) s_start[threadIdx.x] = ds;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r)
+            if (base + 64u * r < count) {
+                const uint32_t d = (key[r] >> sh) & 255u;
+                const uint32_t pos = s_start[d] + s_hist[wave][d] + rank[r];
+                s_key[pos] = key[r];
+                if (PAY) s_pay[pos] = pay[r];
+            }
+        __syncthreads();
+    }
+}
+
+// -------------------------------------------------------- (view, depth) sort
+// The pairs come view by view (pair = view * n + splat), so the (view, depth) order
+// is each view's pairs by their 32 depth bits: blocks of keys never straddle a view
+// and a digit's counts are taken per view, so no pass is spent on view bits.
+
+// n <= 4,096: one workgroup per view sorts in LDS.  Bound by its four serial digit
+// passes; 2,000 pairs take 13 us, where the launches of four passes over memory
+// (counts, scan and scatter) took 60.
+template <int ITEMS>
+__global__ __launch_bounds__(1024) void k_depth_sort_small(const uint32_t* keys, uint32_t n, uint32_t* order) {
+    __shared__ uint32_t s_key[1024 * ITEMS], s_pay[1024 * ITEMS], s_hist[16][256], s_start[256], s_wave[17];
+    const uint32_t first = blockIdx.x * n;
+    for (uint32_t i = threadIdx.x; i < n; i += 1024u) {
+        s_key[i] = keys[first + i];
+        s_pay[i] = first + i;
+    }
+    __syncthreads();
+    lds_sort<ITEMS, true>(s_key, s_pay, n, 0, 32, s_hist, s_start, s_wave);
+    for (uint32_t i = threadIdx.x; i < n; i += 1024u) order[first + i] = s_pay[i];
+}
+
+// Longer views: four passes of 8-bit digits.  Bound by the launches and the ranking's
+// serial ballots up to some 500,000 pairs (100,000: 56 us, against 78 with view bits and
+// scans between the kernels), by the scattered writes beyond (48 million in 16 views:
+// 1.6 ms, against 1.8).
+struct DepthPass {
+    const uint32_t *keys_in, *vals_in;  // vals_in null: the pair index
+    uint32_t *keys_out, *vals_out;      // keys_out null: not needed after the last pass
+    uint32_t n, bpv, shift;             // pairs per view, blocks per view
+    uint32_t* hist;                     // INLINE: [view][block][256], else [view][256][block], scanned
+};
+
+// Digit counts of one block of 256 * ITEMS keys of one view.
+template <int ITEMS, bool INLINE>
+__global__ __launch_bounds__(256) void k_depth_hist(DepthPass a) {
+    __shared__ uint32_t hist[256];
+    const uint32_t v = blockIdx.x / a.bpv, b = blockIdx.x - v * a.bpv;
+    hist[threadIdx.x] = 0u;
+    __syncthreads();
+    uint32_t k[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const uint32_t i = b * (256u * ITEMS) + r * 256u + threadIdx.x;
+        k[r] = i < a.n ? a.keys_in[(uint64_t)v * a.n + i] : 0u;
+    }
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r)
+        if (b * (256u * ITEMS) + r * 256u + threadIdx.x < a.n) atomicAdd(&hist[(k[r] >> a.shift) & 255u], 1u);
+    __syncthreads();
+    const uint64_t d = threadIdx.x;
+    a.hist[INLINE ? (uint64_t)blockIdx.x * 256u + d : ((uint64_t)v * 256u + d) * a.bpv + b] = hist[d];
+}
+
+// Stable scatter of one block (see k_radix_scatter).  INLINE: a block finds its digits'
+// offsets itself from its view's counts (at most DEPTH_INLINE_MAX rows), which saves the
+// scan launches between the two kernels of a pass.
+constexpr uint32_t DEPTH_INLINE_MAX = 64;
+template <int ITEMS, bool INLINE>
+__global__ __launch_bounds__(256) void k_depth_scatter(DepthPass a) {
+    constexpr uint32_t TILE = 256u * ITEMS;
+    __shared__ uint32_t hist[4][256], digit_start[256], g_off[256], s_wave[8];
+    __shared__ uint32_t s_keys[TILE], s_vals[TILE];
+    const uint32_t v = blockIdx.x / a.bpv, b = blockIdx.x - v * a.bpv;
+    const uint64_t first = (uint64_t)v * a.n;
+    const uint32_t lane = __lane_id(), wave = threadIdx.x >> 6;
+    const uint32_t base = b * TILE + wave * (64u * ITEMS) + lane;
+    const uint64_t lt = lanemask_lt();
+    for (int j = threadIdx.x; j < 4 * 256; j += 256) (&hist[0][0])[j] = 0u;
+    uint32_t k[ITEMS], val[ITEMS], rank[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const uint32_t i = base + 64u * r;
+        k[r] = i < a.n ? a.keys_in[first + i] : 0u;
+        val[r] = i < a.n ? (a.vals_in ? a.vals_in[first + i] : (uint32_t)first + i) : 0u;
+    }
+    uint32_t before = 0u, all = 0u;  // this thread's digit: counts of the view's earlier blocks, of all
+    if (INLINE) {
+        const uint32_t* h = a.hist + (uint64_t)v * a.bpv * 256u + threadIdx.x;
+#pragma unroll 8
+        for (uint32_t q = 0; q < a.bpv; ++q) {
+            const uint32_t c = h[q * 256u];
+            before += q < b ? c : 0u;
+            all += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const bool valid = base + 64u * r < a.n;
+        const uint32_t d = (k[r] >> a.shift) & 255u;
+        const uint64_t peers = match_digit<8>(d, __ballot(valid));
+        const uint32_t old = valid ? hist[wave][d] : 0u;
+        rank[r] = old + (uint32_t)__popcll(peers & lt);
+        if (valid && (peers & lt) == 0ull) hist[wave][d] = old + (uint32_t)__popcll(peers);
+    }
+    __syncthreads();
+    uint32_t cnt = 0, tot;
+    for (int w = 0; w < 4; ++w) {
+        const uint32_t c = hist[w][threadIdx.x];
+        hist[w][threadIdx.x] = cnt;
+        cnt += c;
+    }
+    digit_start[threadIdx.x] = block_exclusive_scan(cnt, s_wave, &tot);
+    if (INLINE) g_off[threadIdx.x] = (uint32_t)first + block_exclusive_scan(all, s_wave, &tot) + before;
+    else g_off[threadIdx.x] = a.hist[((uint64_t)v * 256u + threadIdx.x) * a.bpv + b];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r)
+        if (base + 64u * r < a.n) {
+            const uint32_t d = (k[r] >> a.shift) & 255u;
+            const uint32_t lp = digit_start[d] + hist[wave][d] + rank[r];
+            s_keys[lp] = k[r];
+            s_vals[lp] = val[r];
+        }
+    __syncthreads();
+    const uint32_t in_block = min(TILE, a.n - b * TILE);
+    for (uint32_t j = threadIdx.x; j < in_block; j += 256u) {
+        const uint32_t key = s_keys[j], d = (key >> a.shift) & 255u;
+        const uint32_t pos = g_off[d] + (j - digit_start[d]);
+        if (a.keys_out) a.keys_out[pos] = key;
+        a.vals_out[pos] = s_vals[j];
+    }
+}
+
+template <int ITEMS, bool INLINE>
+hipError_t depth_pass(const DepthPass& a, uint32_t V, uint32_t* scan_partials, hipStream_t stream) {
+    const dim3 grid(V * a.bpv), block(256);
+    hipLaunchKernelGGL((k_depth_hist<ITEMS, INLINE>), grid, block, 0, stream, a);
+    if (!INLINE) {
+        hipError_t e = scan_exclusive(a.hist, a.hist, (uint64_t)V * a.bpv * 256u, scan_partials, nullptr, stream);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((k_depth_scatter<ITEMS, INLINE>), grid, block, 0, stream, a);
     return hipGetLastError();
 }
 
@@ -543,13 +746,28 @@ __device__ __forceinline__ uint32_t chunk_segment(const uint32_t* chunk_off, uin
     return lo;
 }
 
-// Number of chunks of every segment.
+// First chunk of every segment (nseg + 1 entries) and the number of chunks, by one
+// block: one launch of 4.6 us instead of three of 4 (counts, end marker, scan).
 template <int LEVEL>
-__global__ __launch_bounds__(256) void k_is_seg_chunks(IsArgs a, uint32_t* chunks) {
-    const uint32_t s = blockIdx.x * 256 + threadIdx.x;
-    if (s >= a.nseg) return;
-    const Seg g = locate_segment<LEVEL>(a, s);
-    chunks[s] = (g.end - g.begin + IS_CHUNK - 1) / IS_CHUNK;
+__global__ __launch_bounds__(1024) void k_is_plan(IsArgs a) {
+    __shared__ uint32_t s_wave[17];
+    uint32_t run = 0;
+    for (uint32_t base = 0; base < a.nseg; base += 1024u) {
+        const uint32_t s = base + threadIdx.x;
+        uint32_t c = 0;
+        if (s < a.nseg) {
+            const Seg g = locate_segment<LEVEL>(a, s);
+            c = (g.end - g.begin + IS_CHUNK - 1) / IS_CHUNK;
+        }
+        uint32_t tot;
+        const uint32_t ex = run + block_exclusive_scan(c, s_wave, &tot);
+        if (s < a.nseg) a.chunk_off[s] = ex;
+        run += tot;
+    }
+    if (threadIdx.x == 0) {
+        a.chunk_off[a.nseg] = run;
+        *a.chunk_total = run;
+    }
 }
 
 // Inclusive prefix over the IS_W entries row[0..IS_W) by one wave (two per
@@ -870,41 +1088,56 @@ __global__ __launch_bounds__(IS_W * IS_PARTS) void k_is_prefix(IsArgs a) {
 
 // ranges[t] = [start, start + count), clamped to the instances actually listed
 // (min(M, m_cap)); when the capacity overflowed the lists are incomplete and
-// only memory safety is kept.
-__global__ __launch_bounds__(256) void k_ranges_from_counts(const uint32_t* counts, const uint32_t* starts,
-                                                            uint64_t total_tiles, const uint32_t* listed,
-                                                            uint32_t* ranges) {
-    const uint64_t t = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= total_tiles) return;
-    const uint32_t m = *listed;
-    const uint32_t c = counts[t];
-    const uint32_t s0 = starts[t];
+// only memory safety is kept.  Empty tiles get (0, 0).
+__device__ __forceinline__ uint2 tile_range(uint32_t c, uint32_t s0, uint32_t m) {
     const uint32_t s1 = s0 + c;
-    // empty tiles get (0, 0)
-    reinterpret_cast<uint2*>(ranges)[t] = c == 0 ? make_uint2(0u, 0u) : make_uint2(s0 < m ? s0 : m, s1 < m ? s1 : m);
+    return c == 0 ? make_uint2(0u, 0u) : make_uint2(s0 < m ? s0 : m, s1 < m ? s1 : m);
+}
+// Worklist key: more work first (ascending keys, ties by tile id); the work is the
+// list length, or a previous forward's evaluated positions when given.
+__device__ __forceinline__ uint32_t worklist_key(uint2 r, const uint32_t* work, uint64_t t) {
+    const uint32_t len = work ? work[t] : r.y - r.x;
+    return 0xFFFFu - (len < 0xFFFFu ? len : 0xFFFFu);
 }
 
-__global__ void k_set_counters(uint32_t* c, uint64_t m_cap) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        const uint32_t m = c[0];
-        c[1] = (uint64_t)m > m_cap ? 1u : 0u;
-        c[2] = (uint32_t)((uint64_t)m > m_cap ? m_cap : m);
+__global__ __launch_bounds__(256) void k_ranges_from_counts(const uint32_t* counts, const uint32_t* starts,
+                                                            uint64_t total_tiles, const uint32_t* listed,
+                                                            const uint32_t* work, uint32_t* ranges, uint32_t* keys) {
+    const uint64_t t = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= total_tiles) return;
+    const uint2 r = tile_range(counts[t], starts[t], *listed);
+    reinterpret_cast<uint2*>(ranges)[t] = r;
+    keys[t] = worklist_key(r, work, t);
+}
+
+// Up to 1024 * ITEMS tiles by one block: list starts (exclusive scan of the counts),
+// ranges and the worklist, sorted in LDS (key << 16 | tile).  3,024 tiles: 13 us,
+// where nine launches (scan, ranges, keys, two passes of counts, scan and scatter)
+// took 45; beyond 16,384 tiles the keys no longer fit the LDS beside the counts.
+template <int ITEMS>
+__global__ __launch_bounds__(1024) void k_tile_lists_small(const uint32_t* counts, uint32_t* starts, uint32_t T,
+                                                           uint32_t* total, const uint32_t* listed,
+                                                           const uint32_t* work, uint32_t* ranges,
+                                                           uint32_t* worklist) {
+    static_assert(ITEMS <= 16, "tile ids take 16 bits");
+    __shared__ uint32_t s_key[1024 * ITEMS > 4096 + 128 ? 1024 * ITEMS : 4096 + 128];
+    __shared__ uint32_t s_hist[16][256], s_start[256], s_wave[17];
+    const uint32_t run = scan_by_block(counts, starts, T, s_key, s_wave);
+    if (threadIdx.x == 0) *total = run;
+    const uint32_t m = *listed;
+    for (uint32_t t = threadIdx.x; t < T; t += 1024u) {
+        const uint2 r = tile_range(counts[t], starts[t], m);
+        reinterpret_cast<uint2*>(ranges)[t] = r;
+        s_key[t] = worklist_key(r, work, t) << 16 | t;
     }
+    __syncthreads();
+    lds_sort<ITEMS, false>(s_key, nullptr, T, 16, 32, s_hist, s_start, s_wave);
+    for (uint32_t t = threadIdx.x; t < T; t += 1024u) worklist[t] = s_key[t] & 0xFFFFu;
 }
 
 __global__ __launch_bounds__(256) void k_fill_u32(uint32_t* p, uint32_t value, uint64_t count) {
     const uint64_t k = (uint64_t)blockIdx.x * 256 + threadIdx.x;
     if (k < count) p[k] = value;
-}
-
-// Worklist key: more work first (descending, ties by tile id); the work is the
-// list length, or a previous forward's evaluated positions when given.
-__global__ __launch_bounds__(256) void k_worklist_keys(const uint32_t* ranges, const uint32_t* work,
-                                                       uint64_t total_tiles, uint32_t* keys) {
-    const uint64_t t = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= total_tiles) return;
-    const uint32_t len = work ? work[t] : ranges[2 * t + 1] - ranges[2 * t];
-    keys[t] = 0xFFFFu - (len < 0xFFFFu ? len : 0xFFFFu);
 }
 
 __global__ __launch_bounds__(256) void k_l1_grad(const float* image, const float* target, uint64_t count, float scale,
@@ -920,19 +1153,19 @@ inline dim3 grid_for(uint64_t count) { return dim3((unsigned)((count + 255) / 25
 }  // namespace
 
 hipError_t scan_exclusive(const uint32_t* in, uint32_t* out, uint64_t count, uint32_t* partials, uint32_t* total,
-                          hipStream_t stream) {
+                          hipStream_t stream, uint64_t cap) {
     if (count == 0) {
-        if (total) hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, stream, total, 0u, (uint64_t)1);
+        if (total) hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, stream, total, 0u, (uint64_t)(cap ? 3 : 1));
         return hipGetLastError();
     }
-    if (count <= (uint64_t)SCAN_TOP_MAX) {  // one launch
-        hipLaunchKernelGGL(k_scan_single, dim3(1), dim3(1024), 0, stream, in, out, (uint32_t)count, total);
+    if (count <= SCAN_ONE_BLOCK) {  // one launch
+        hipLaunchKernelGGL(k_scan_single, dim3(1), dim3(1024), 0, stream, in, out, (uint32_t)count, total, cap);
         return hipGetLastError();
     }
     const uint64_t nb = (count + SCAN_TILE - 1) / SCAN_TILE;
     if (nb > (uint64_t)SCAN_TOP_MAX) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(256), 0, stream, in, count, partials);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, stream, partials, (uint32_t)nb, total);
+    hipLaunchKernelGGL(k_scan_single, dim3(1), dim3(1024), 0, stream, partials, partials, (uint32_t)nb, total, cap);
     hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(256), 0, stream, in, out, count, partials);
     return hipGetLastError();
 }
@@ -974,6 +1207,41 @@ hipError_t radix_sort(const uint32_t* keys_in, const uint32_t* vals_in, uint64_t
     return hipSuccess;
 }
 
+hipError_t depth_sort(const uint32_t* keys, uint32_t n, uint32_t V, const SortBuffers& b, uint32_t** order,
+                      hipStream_t stream) {
+    *order = b.vals_b;
+    if (n == 0 || V == 0) return hipSuccess;
+    if (n <= 4096u) {
+        const dim3 grid(V), block(1024);
+        if (n <= 1024u) hipLaunchKernelGGL(k_depth_sort_small<1>, grid, block, 0, stream, keys, n, b.vals_b);
+        else if (n <= 2048u) hipLaunchKernelGGL(k_depth_sort_small<2>, grid, block, 0, stream, keys, n, b.vals_b);
+        else hipLaunchKernelGGL(k_depth_sort_small<4>, grid, block, 0, stream, keys, n, b.vals_b);
+        return hipGetLastError();
+    }
+    // keys per block: as few as keep a view's rows of counts within what a block sums
+    // by itself (more blocks in flight), 4,096 otherwise
+    const int items = n <= 1024u * DEPTH_INLINE_MAX ? 4 : (n <= 2048u * DEPTH_INLINE_MAX ? 8 : 16);
+    DepthPass a;
+    a.n = n;
+    a.bpv = (n + 256u * items - 1) / (256u * items);
+    a.hist = b.block_hist;
+    for (int p = 0; p < 4; ++p) {
+        a.keys_in = p == 0 ? keys : (p & 1 ? b.keys_a : b.keys_b);
+        a.vals_in = p == 0 ? nullptr : (p & 1 ? b.vals_a : b.vals_b);
+        a.keys_out = p == 3 ? nullptr : (p & 1 ? b.keys_b : b.keys_a);
+        a.vals_out = p & 1 ? b.vals_b : b.vals_a;
+        a.shift = 8u * p;
+        hipError_t e;
+        if (items == 4) e = depth_pass<4, true>(a, V, b.scan_partials, stream);
+        else if (items == 8) e = depth_pass<8, true>(a, V, b.scan_partials, stream);
+        else if (a.bpv <= DEPTH_INLINE_MAX) e = depth_pass<16, true>(a, V, b.scan_partials, stream);
+        else e = depth_pass<16, false>(a, V, b.scan_partials, stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+uint64_t depth_sort_hist_words(uint64_t n, uint64_t V) { return n <= 4096u ? 0u : V * 256u * ((n + 1023) / 1024); }
+
 hipError_t launch_gather_rects(const uint32_t* order, const float* rec, uint64_t count, uint2* out, float4* ell,
                                hipStream_t stream) {
     if (count == 0) return hipSuccess;
@@ -1008,54 +1276,51 @@ uint64_t is_chunk_bound(const DevCams& cams, int level, int n, uint64_t level2_i
 
 uint32_t is_window() { return IS_W; }
 
-hipError_t launch_interval_scatter(IsArgs a, int level, uint32_t n_buckets, uint32_t* bucket_total,
-                                   uint32_t* seg_chunks, uint32_t* scan_partials, hipStream_t stream) {
+hipError_t launch_interval_lists(IsArgs a, int level, hipStream_t stream) {
     a.nseg = is_segments(a.cams, level);
     if (a.nseg == 0) return hipSuccess;
     const uint32_t grid = (uint32_t)(a.mat_chunks < 1024 ? a.mat_chunks : 1024);
-    auto seg_k = level == 1 ? k_is_seg_chunks<1> : k_is_seg_chunks<2>;
-    hipLaunchKernelGGL(seg_k, dim3((a.nseg + 255) / 256), dim3(256), 0, stream, a, seg_chunks);
-    // chunk_off = exclusive scan of the chunk counts (nseg + 1 entries: the
-    // last one, from a zero count, is the total)
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, stream, seg_chunks + a.nseg, 0u, (uint64_t)1);
-    hipError_t e = scan_exclusive(seg_chunks, const_cast<uint32_t*>(a.chunk_off), (uint64_t)a.nseg + 1, scan_partials,
-                                  const_cast<uint32_t*>(a.chunk_total), stream);
-    if (e != hipSuccess) return e;
+    auto plan_k = level == 1 ? k_is_plan<1> : k_is_plan<2>;
+    hipLaunchKernelGGL(plan_k, dim3(1), dim3(1024), 0, stream, a);
     auto count_k = level == 1 ? k_is_chunks<1, 0> : k_is_chunks<2, 0>;
     hipLaunchKernelGGL(count_k, dim3(grid), dim3(IS_THREADS), 0, stream, a);
     auto prefix_k = level == 1 ? k_is_prefix<1> : k_is_prefix<2>;
     hipLaunchKernelGGL(prefix_k, dim3(a.nseg), dim3(IS_W * IS_PARTS), 0, stream, a);
-    e = scan_exclusive(a.bucket_count, const_cast<uint32_t*>(a.bucket_start), n_buckets, scan_partials, bucket_total,
-                       stream);
-    if (e != hipSuccess) return e;
+    return hipGetLastError();
+}
+
+hipError_t launch_interval_scatter(IsArgs a, int level, hipStream_t stream) {
+    a.nseg = is_segments(a.cams, level);
+    if (a.nseg == 0) return hipSuccess;
+    const uint32_t grid = (uint32_t)(a.mat_chunks < 1024 ? a.mat_chunks : 1024);
     auto scatter_k = level == 1 ? k_is_chunks<1, 1> : k_is_chunks<2, 1>;
     hipLaunchKernelGGL(scatter_k, dim3(grid), dim3(IS_THREADS), 0, stream, a);
     return hipGetLastError();
 }
 
-hipError_t launch_ranges_from_counts(const uint32_t* counts, const uint32_t* starts, uint64_t total_tiles,
-                                     const uint32_t* listed, uint32_t* ranges, hipStream_t stream) {
-    if (total_tiles == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_ranges_from_counts, grid_for(total_tiles), dim3(256), 0, stream, counts, starts, total_tiles,
-                       listed, ranges);
-    return hipGetLastError();
-}
-
-hipError_t launch_set_counters(uint32_t* counters, uint64_t m_cap, hipStream_t stream) {
-    hipLaunchKernelGGL(k_set_counters, dim3(1), dim3(64), 0, stream, counters, m_cap);
-    return hipGetLastError();
+hipError_t launch_tile_lists(const TileListArgs& a, hipStream_t stream) {
+    const uint32_t T = (uint32_t)a.total_tiles;
+    if (T == 0) return hipSuccess;
+    if (T <= 16384u) {
+        auto k = T <= 1024u ? k_tile_lists_small<1> : (T <= 4096u ? k_tile_lists_small<4> : k_tile_lists_small<16>);
+        hipLaunchKernelGGL(k, dim3(1), dim3(1024), 0, stream, a.counts, a.starts, T, a.total, a.listed, a.work, a.ranges,
+                           a.worklist);
+        return hipGetLastError();
+    }
+    hipError_t e = scan_exclusive(a.counts, a.starts, T, a.sort.scan_partials, a.total, stream);
+    if (e != hipSuccess) return e;
+    // two 8-bit passes: keys_b -> a -> (keys_b, worklist)
+    hipLaunchKernelGGL(k_ranges_from_counts, grid_for(T), dim3(256), 0, stream, a.counts, a.starts, (uint64_t)T, a.listed,
+                       a.work, a.ranges, a.sort.keys_b);
+    SortBuffers b = a.sort;
+    b.vals_b = a.worklist;
+    bool in_b = false;
+    return radix_sort(b.keys_b, nullptr, T, nullptr, 16, 8, b, &in_b, stream);
 }
 
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, uint64_t count, hipStream_t stream) {
     if (count == 0) return hipSuccess;
     hipLaunchKernelGGL(k_fill_u32, grid_for(count), dim3(256), 0, stream, p, value, count);
-    return hipGetLastError();
-}
-
-hipError_t launch_worklist_keys(const uint32_t* ranges, const uint32_t* work, uint64_t total_tiles, uint32_t* keys,
-                                hipStream_t stream) {
-    if (total_tiles == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_worklist_keys, grid_for(total_tiles), dim3(256), 0, stream, ranges, work, total_tiles, keys);
     return hipGetLastError();
 }
 

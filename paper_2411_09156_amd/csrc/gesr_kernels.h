@@ -112,12 +112,16 @@ constexpr int SORT_THREADS = 256;
 constexpr int SORT_ITEMS = 16;
 constexpr int SORT_TILE = SORT_THREADS * SORT_ITEMS;  // keys per sort block
 constexpr int SCAN_TILE = 4096;                       // items per scan block
-constexpr int SCAN_TOP_MAX = 32768;                   // max blocks of a two-level scan
+constexpr int SCAN_TOP_MAX = 32768;                   // max blocks of a scan
 
 // Exclusive scan of `count` uint32 values; the grand total goes to *total
-// (device, nullable).  `partials` needs ceil(count / SCAN_TILE) entries.
+// (device, nullable), with cap != 0 followed by total > cap and min(total, cap).
+// `partials` needs ceil(count / SCAN_TILE) entries.  One block takes up to
+// SCAN_ONE_BLOCK values (11 us); more take a reduction, a scan of the block sums and a
+// second pass (three launches of 4.5 us).
+constexpr uint64_t SCAN_ONE_BLOCK = 32768;
 hipError_t scan_exclusive(const uint32_t* in, uint32_t* out, uint64_t count, uint32_t* partials, uint32_t* total,
-                          hipStream_t stream);
+                          hipStream_t stream, uint64_t cap = 0);
 
 // Stable LSD radix sort of `count_static` (or *count_dev when non-null, which
 // must not exceed count_static) 32-bit keys over bits [0, key_bits) carrying
@@ -137,6 +141,14 @@ hipError_t radix_sort(const uint32_t* keys_in, const uint32_t* vals_in, uint64_t
                       const uint32_t* count_dev, int key_bits, int radix_bits, const SortBuffers& b,
                       bool* result_in_b, hipStream_t stream, uint32_t view_n = 0);
 int radix_passes(int key_bits, int radix_bits);
+
+// Pairs in (view, depth key, pair) order: *order (one of b's value buffers) gets the
+// [V * n] pair indices.  keys_a, vals_a, keys_b, vals_b: [V * n]; b.block_hist:
+// depth_sort_hist_words words; b.scan_partials as for a scan of 256 V ceil(n / 4096)
+// values.
+hipError_t depth_sort(const uint32_t* keys, uint32_t n, uint32_t V, const SortBuffers& b, uint32_t** order,
+                      hipStream_t stream);
+uint64_t depth_sort_hist_words(uint64_t n, uint64_t V);
 
 // Binning helper kernels.
 // out[k] = the rectangle in pair order[k]'s record (x = 0xFFFFFFFF when the pair touches no tile);
@@ -175,16 +187,24 @@ uint32_t is_segments(const DevCams& cams, int level);
 // Upper bound on the chunks of a level (level2_items: capacity of the row lists).
 uint64_t is_chunk_bound(const DevCams& cams, int level, int n, uint64_t level2_items);
 uint32_t is_window();
-// seg_chunks: [segments + 1] scratch.  Writes bucket_count, bucket_start and
-// the bucket total (*bucket_total, device) and scatters the items.
-hipError_t launch_interval_scatter(IsArgs a, int level, uint32_t n_buckets, uint32_t* bucket_total,
-                                   uint32_t* seg_chunks, uint32_t* scan_partials, hipStream_t stream);
-hipError_t launch_ranges_from_counts(const uint32_t* counts, const uint32_t* starts, uint64_t total_tiles,
-                                     const uint32_t* listed, uint32_t* ranges, hipStream_t stream);
-hipError_t launch_set_counters(uint32_t* counters, uint64_t m_cap, hipStream_t stream);
+// A level's chunk plan, per-chunk bucket counts and bucket totals (bucket_count); the
+// caller scans those into bucket_start before the scatter.
+hipError_t launch_interval_lists(IsArgs a, int level, hipStream_t stream);
+hipError_t launch_interval_scatter(IsArgs a, int level, hipStream_t stream);
+// Tile list starts (scan of the counts, the sum to *total), ranges and worklist.
+struct TileListArgs {
+    uint64_t total_tiles;
+    const uint32_t* counts;
+    uint32_t* starts;
+    uint32_t* total;         // device
+    const uint32_t* listed;  // device: instances within the capacity
+    const uint32_t* work;    // nullable: order by it instead of by list length
+    uint32_t* ranges;
+    uint32_t* worklist;
+    SortBuffers sort;        // [T] keys_a, vals_a, keys_b; block_hist, scan_partials
+};
+hipError_t launch_tile_lists(const TileListArgs& a, hipStream_t stream);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, uint64_t count, hipStream_t stream);
-hipError_t launch_worklist_keys(const uint32_t* ranges, const uint32_t* work, uint64_t total_tiles, uint32_t* keys,
-                                hipStream_t stream);
 // Photometric loss of Eq. 8 (gesr_loss.hip).
 struct LossView {
     int W, H;

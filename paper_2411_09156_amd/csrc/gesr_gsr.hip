@@ -5,11 +5,11 @@
 // Neighbour lists (knn[j][0] = j, then the k - 1 nearest other centres by
 // squared distance, ties by index) come from a uniform grid over the centres'
 // bounding box: the centres are radix-sorted by the Morton code of their
-// cell, and each query (one
-// thread, in cell order so that a wave's queries share cells) scans shells of
-// cells around its own until the (k-1)-th distance is below the distance to
-// any unscanned cell.  The cell order is kept: the regulariser runs its
-// samples in it.  The inverse lists (for every splat, the entries p * k + s,
+// cell, and each query (one thread, in cell order so that a wave's queries
+// share cells) scans shells of cells around its own until the (k-1)-th
+// distance is below the distance to any unscanned cell; the candidates lie in
+// row order of the cells, so that a row of a shell is one run.  The cell order
+// is kept: the regulariser runs its samples in it.  The inverse lists (for every splat, the entries p * k + s,
 // p a position in the cell order, that name it) are a stable sort of the
 // entries by neighbour.
 //
@@ -38,16 +38,8 @@ namespace {
 constexpr float kGsrFloor = 1e-30f;
 
 // ---------------------------------------------------------------- grid
-// Per-block min / max of the centres.
-__global__ __launch_bounds__(256) void k_knn_bounds(const float* mean, int n, float* part) {
-    __shared__ float s[6][256];
-    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < (uint32_t)n; i += gridDim.x * 256u)
-        for (int a = 0; a < 3; ++a) {
-            const float v = mean[(size_t)a * n + i];
-            lo[a] = fminf(lo[a], v);
-            hi[a] = fmaxf(hi[a], v);
-        }
+// Box of a block's 256 boxes, in s[..][0].
+__device__ __forceinline__ void block_box(float (*s)[256], const float lo[3], const float hi[3]) {
     for (int a = 0; a < 3; ++a) {
         s[a][threadIdx.x] = lo[a];
         s[3 + a][threadIdx.x] = hi[a];
@@ -61,19 +53,40 @@ __global__ __launch_bounds__(256) void k_knn_bounds(const float* mean, int n, fl
             }
         __syncthreads();
     }
+}
+
+// Per-block min / max of the centres.
+__global__ __launch_bounds__(256) void k_knn_bounds(const float* mean, int n, float* part) {
+    __shared__ float s[6][256];
+    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < (uint32_t)n; i += gridDim.x * 256u)
+        for (int a = 0; a < 3; ++a) {
+            const float v = mean[(size_t)a * n + i];
+            lo[a] = fminf(lo[a], v);
+            hi[a] = fmaxf(hi[a], v);
+        }
+    block_box(s, lo, hi);
     if (threadIdx.x < 6) part[blockIdx.x * 6 + threadIdx.x] = s[threadIdx.x][0];
 }
 
 // Grid over the box: cubic cells of side cs, about two centres per cell of
-// the box's volume, at most 256 cells per axis and `cell_cap` cells in all.
-__global__ void k_knn_grid(const float* part, int nparts, int n, uint32_t cell_cap, KnnGrid* g) {
-    if (threadIdx.x != 0) return;
+// the box's volume, at most 256 cells per axis and `cell_cap` cells in all.  The
+// blocks' boxes are read by a whole workgroup (1,024 of them: 10 us, by one lane 133).
+__global__ __launch_bounds__(256) void k_knn_grid(const float* part, int nparts, int n, uint32_t cell_cap,
+                                                  KnnGrid* g) {
+    __shared__ float s[6][256];
     float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int b = 0; b < nparts; ++b)
+    for (int b = threadIdx.x; b < nparts; b += 256)
         for (int a = 0; a < 3; ++a) {
             lo[a] = fminf(lo[a], part[b * 6 + a]);
             hi[a] = fmaxf(hi[a], part[b * 6 + 3 + a]);
         }
+    block_box(s, lo, hi);
+    if (threadIdx.x != 0) return;
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = s[a][0];
+        hi[a] = s[3 + a][0];
+    }
     float ext[3], emax = 0.f;
     for (int a = 0; a < 3; ++a) {
         ext[a] = fmaxf(hi[a] - lo[a], 0.f);
@@ -132,100 +145,148 @@ __global__ __launch_bounds__(256) void k_knn_cells(const float* mean, int n, con
     keys[i] = spread3((uint32_t)c[0]) | (spread3((uint32_t)c[1]) << 1) | (spread3((uint32_t)c[2]) << 2);
 }
 
-// [start, end) of every cell (indexed x + X (y + Y z)) in the Morton-sorted
-// order (cells start empty).
+// Index x + X (y + Y z) of the cell of a Morton code.
+__device__ __forceinline__ uint32_t row_cell(uint32_t m, const KnnGrid* g) {
+    return compact3(m) + (uint32_t)g->dim[0] * (compact3(m >> 1) + (uint32_t)g->dim[1] * compact3(m >> 2));
+}
+
+// [start, end) of every cell in the Morton-sorted order (end starts as 0; an empty
+// cell's start is not written).
 __global__ __launch_bounds__(256) void k_knn_ranges(const uint32_t* keys, int n, const KnnGrid* g, uint32_t* start,
                                                     uint32_t* end) {
     const uint32_t p = blockIdx.x * 256u + threadIdx.x;
     if (p >= (uint32_t)n) return;
     const uint32_t m = keys[p];
-    const uint32_t c = compact3(m) + (uint32_t)g->dim[0] * (compact3(m >> 1) + (uint32_t)g->dim[1] * compact3(m >> 2));
+    const uint32_t c = row_cell(m, g);
     if (p == 0 || keys[p - 1] != m) start[c] = p;
     if (p + 1 == (uint32_t)n || keys[p + 1] != m) end[c] = p + 1;
 }
+__global__ __launch_bounds__(256) void k_knn_counts(const uint32_t* start, uint32_t* end, uint32_t cells) {
+    const uint32_t c = blockIdx.x * 256u + threadIdx.x;
+    if (c >= cells) return;
+    const uint32_t e = end[c];
+    if (e != 0u) end[c] = e - start[c];
+}
 
-// Centres in the sorted order, (x, y, z, index bits): a cell's centres are
-// one contiguous run of 16-byte records.
+// Centres as (x, y, z, index bits) in the sorted order (the queries) and in the cells'
+// row order (the candidates: first[c] is a cell's first), where the cells of a row lie
+// one behind the other.
 __global__ __launch_bounds__(256) void k_knn_sorted_pos(const float* mean, int n, const uint32_t* order,
-                                                        float4* pos) {
+                                                        const uint32_t* keys, const KnnGrid* g, const uint32_t* start,
+                                                        const uint32_t* first, float4* pos, float4* row_pos) {
     const uint32_t p = blockIdx.x * 256u + threadIdx.x;
     if (p >= (uint32_t)n) return;
     const uint32_t i = order[p];
-    pos[p] = make_float4(mean[i], mean[(size_t)n + i], mean[2 * (size_t)n + i], __uint_as_float(i));
+    const float4 v = make_float4(mean[i], mean[(size_t)n + i], mean[2 * (size_t)n + i], __uint_as_float(i));
+    pos[p] = v;
+    const uint32_t c = row_cell(keys[p], g);
+    row_pos[first[c] + (p - start[c])] = v;
 }
 
-// Scans one cell's centres into the sorted candidate list (d2, index) of
-// WANT entries.
+// The WANT nearest of a query's candidates, each one word: squared distance (float
+// bits) << 32 | index.  Distances are never negative and their bits stay below a
+// double's infinity, so the words order alike as integers and as doubles, and one
+// entry's place costs a 64-bit minimum and maximum.
+// b = max(below, min(b, c)) in place; kept in order (volatile), since moved about the
+// old and new entries of the list would both be held.
+__device__ __forceinline__ void place_f64(double& b, double below, double c) {
+    asm volatile("v_min_f64 %0, %0, %2\n\tv_max_f64 %0, %1, %0" : "+v"(b) : "v"(below), "v"(c));
+}
+__device__ __forceinline__ void place_f64(double& b, double c) { asm volatile("v_min_f64 %0, %0, %1" : "+v"(b) : "v"(c)); }
+constexpr int KNN_PEND = 8;  // candidates a query keeps for the next insertion
 template <int WANT>
-__device__ __forceinline__ void scan_cell(uint32_t c, const uint32_t* start, const uint32_t* end,
-                                          const float4* pos, uint32_t self, float px, float py, float pz, float* bd,
-                                          uint32_t* bi, int& have) {
-    const uint32_t e = end[c];
-    for (uint32_t q = start[c]; q < e; ++q) {
-        const float4 v = pos[q];
-        const uint32_t j = __float_as_uint(v.w);
-        if (j == self) continue;
+struct Nearest {
+    double b[WANT];       // ascending
+    float worst;          // the distance of b[WANT - 1]
+    uint32_t n_pend;
+    uint2* pend;          // [KNN_PEND][256] in LDS, this thread's column
+
+    __device__ __forceinline__ void init(uint2* column) {
+#pragma unroll
+        for (int s = 0; s < WANT; ++s) b[s] = __hiloint2double(0x7F800000, -1);  // infinity, no index
+        worst = INFINITY;
+        n_pend = 0;
+        pend = column;
+    }
+    __device__ __forceinline__ void flush() {
+#pragma unroll
+        for (uint32_t k = 0; k < (uint32_t)KNN_PEND; ++k) {
+            const uint2 w = pend[k * 256u];
+            const double c = __hiloint2double(k < n_pend ? (int)w.y : 0x7FE00000, (int)w.x);
+#pragma unroll
+            for (int s = WANT - 1; s > 0; --s) place_f64(b[s], b[s - 1], c);
+            place_f64(b[0], c);
+        }
+        n_pend = 0;
+        worst = __int_as_float(__double2hiint(b[WANT - 1]));
+    }
+    // a centre that is no farther than the farthest kept; a NaN distance is none
+    __device__ __forceinline__ void offer(float4 v, bool valid, uint32_t self, float px, float py, float pz) {
         const float dx = v.x - px, dy = v.y - py, dz = v.z - pz;
         const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-        if (d2 > bd[WANT - 1] || (d2 == bd[WANT - 1] && j >= bi[WANT - 1])) continue;
-        // insert (d2, j), shifting the larger entries up
-        float cd = d2;
-        uint32_t ci = j;
-#pragma unroll
-        for (int s = 0; s < WANT; ++s) {
-            const bool less = cd < bd[s] || (cd == bd[s] && ci < bi[s]);
-            const float td = bd[s];
-            const uint32_t ti = bi[s];
-            bd[s] = less ? cd : bd[s];
-            bi[s] = less ? ci : bi[s];
-            cd = less ? td : cd;
-            ci = less ? ti : ci;
+        if (valid && d2 <= worst && __float_as_uint(v.w) != self) {
+            pend[n_pend * 256u] = make_uint2(__float_as_uint(v.w), __float_as_uint(d2));
+            ++n_pend;
         }
-        have = min(have + 1, WANT);
     }
-}
+    // The run [q, e) of every lane's own, two centres at a time so that their loads are
+    // in flight together.  All lanes stay in the loop: left one by one, it would hold
+    // the list twice (150 registers instead of 76).
+    __device__ __forceinline__ void scan(uint32_t q, uint32_t e, bool settle, const float4* pos, uint32_t last,
+                                         uint32_t self, float px, float py, float pz) {
+        bool more;
+        do {
+            const float4 v0 = pos[min(q, last)], v1 = pos[min(q + 1u, last)];
+            offer(v0, q < e, self, px, py, pz);
+            offer(v1, q + 1u < e, self, px, py, pz);
+            q += 2;
+            more = __any(q < e);
+            if (__any(n_pend > KNN_PEND - 2) || (settle && !more)) flush();
+        } while (more);
+    }
+};
 
-// One query per thread, in cell order.  bd/bi hold the K - 1 nearest others
-// sorted by (distance^2, index).
+// One query per thread, in cell order.  Bound by the candidates' instructions: a wave
+// runs as many steps as its longest lane and an insertion whenever one lane has one, so
+// the rows are single runs and insertions wait until some lane has KNN_PEND - 1 of
+// them.  500,000 centres, k = 16:
+// 291 us (829 with each insertion at once and a loop per cell).
 template <int K>
-__global__ __launch_bounds__(256) void k_knn_query(const float4* pos, int n, const KnnGrid* gp,
-                                                   const uint32_t* start, const uint32_t* end, uint32_t* knn) {
-    const uint32_t p = blockIdx.x * 256u + threadIdx.x;
-    if (p >= (uint32_t)n) return;
+__global__ __launch_bounds__(256, 6) void k_knn_query(const float4* pos, const float4* row_pos, int n, const KnnGrid* gp,
+                                                   const uint32_t* first, uint32_t* knn) {
+    __shared__ uint2 s_pend[KNN_PEND * 256];
+    const uint32_t p = blockIdx.x * 256u + threadIdx.x, last = (uint32_t)n - 1u;
     const KnnGrid g = *gp;
-    const float4 me = pos[p];
+    const float4 me = pos[min(p, last)];
     const uint32_t i = __float_as_uint(me.w);
     const float px = me.x, py = me.y, pz = me.z;
     const int cx = cell_coord(px, g.lo[0], g.inv_cs, g.dim[0]);
     const int cy = cell_coord(py, g.lo[1], g.inv_cs, g.dim[1]);
     const int cz = cell_coord(pz, g.lo[2], g.inv_cs, g.dim[2]);
-    constexpr int want = K - 1;
-    float bd[want];
-    uint32_t bi[want];
-#pragma unroll
-    for (int s = 0; s < want; ++s) {
-        bd[s] = INFINITY;
-        bi[s] = 0xFFFFFFFFu;
-    }
-    int have = 0;
+    Nearest<K - 1> best;
+    best.init(s_pend + threadIdx.x);
+    bool done = p > last;
     const int rmax = max(g.dim[0], max(g.dim[1], g.dim[2]));
-    for (int r = 0; r <= rmax; ++r) {
-        const int z0 = max(cz - r, 0), z1 = min(cz + r, g.dim[2] - 1);
-        const int y0 = max(cy - r, 0), y1 = min(cy + r, g.dim[1] - 1);
-        const int x0 = max(cx - r, 0), x1 = min(cx + r, g.dim[0] - 1);
-        for (int z = z0; z <= z1; ++z)
-            for (int y = y0; y <= y1; ++y) {
-                const uint32_t row = (uint32_t)g.dim[0] * ((uint32_t)y + (uint32_t)g.dim[1] * (uint32_t)z);
-                if (r == 0 || abs(z - cz) == r || abs(y - cy) == r) {
-                    for (int x = x0; x <= x1; ++x)
-                        scan_cell<want>(row + (uint32_t)x, start, end, pos, i, px, py, pz, bd, bi, have);
-                } else {  // inner rows of the shell: its two end cells
-                    if (cx - r >= 0)
-                        scan_cell<want>(row + (uint32_t)(cx - r), start, end, pos, i, px, py, pz, bd, bi, have);
-                    if (cx + r < g.dim[0])
-                        scan_cell<want>(row + (uint32_t)(cx + r), start, end, pos, i, px, py, pz, bd, bi, have);
-                }
-            }
+    // shell r, row (dz, dy) of it; of an inner row first one, then the other end cell
+    for (int r = 0, dz = 0, dy = 0, other = 0;;) {
+        const int z = cz + dz, y = cy + dy;
+        const uint32_t row = (uint32_t)g.dim[0] * ((uint32_t)y + (uint32_t)g.dim[1] * (uint32_t)z);
+        const bool whole = max(abs(dz), abs(dy)) == r;
+        const int xa = whole ? max(cx - r, 0) : (other ? cx + r : cx - r);
+        const int xb = whole ? min(cx + r, g.dim[0] - 1) : xa;
+        uint32_t q = 0, e = 0;
+        if (!done && z >= 0 && z < g.dim[2] && y >= 0 && y < g.dim[1] && xa >= 0 && xb < g.dim[0]) {
+            q = first[row + (uint32_t)xa];
+            e = first[row + (uint32_t)xb + 1u];
+        }
+        other = !whole && !other;
+        if (!other && ++dy > r) {
+            dy = -r;
+            ++dz;
+        }
+        const bool settle = dz > r;
+        best.scan(q, e, settle, row_pos, last, i, px, py, pz);
+        if (!settle) continue;
         // every unscanned centre lies outside the cube of cells within r
         float bound = INFINITY;
         if (cx - r > 0) bound = fminf(bound, px - (g.lo[0] + (float)(cx - r) * g.cs));
@@ -234,15 +295,18 @@ __global__ __launch_bounds__(256) void k_knn_query(const float4* pos, int n, con
         if (cy + r < g.dim[1] - 1) bound = fminf(bound, g.lo[1] + (float)(cy + r + 1) * g.cs - py);
         if (cz - r > 0) bound = fminf(bound, pz - (g.lo[2] + (float)(cz - r) * g.cs));
         if (cz + r < g.dim[2] - 1) bound = fminf(bound, g.lo[2] + (float)(cz + r + 1) * g.cs - pz);
-        if (bound == INFINITY) break;  // the whole grid is scanned
+        done |= bound == INFINITY;  // the whole grid is scanned
         // a centre's cell comes from a rounded (v - lo) / cs: keep a margin
         bound = fmaxf(bound - 1e-4f * g.cs, 0.f);
-        if (have == want && bd[want - 1] < bound * bound) break;
+        done |= best.worst < bound * bound;  // infinite until the list is full
+        if (++r > rmax || !__any(!done)) break;
+        dz = dy = -r;
     }
+    if (p > last) return;
     uint32_t* out = knn + (size_t)i * K;
     out[0] = i;
 #pragma unroll
-    for (int s = 0; s < want; ++s) out[1 + s] = s < have ? bi[s] : 0xFFFFFFFFu;
+    for (int s = 0; s < K - 1; ++s) out[1 + s] = (uint32_t)__double2loint(best.b[s]);
 }
 
 // k = 1: the list is the splat itself.
@@ -277,14 +341,28 @@ __global__ __launch_bounds__(256) void k_inv_offsets(const uint32_t* keys, uint6
     }
 }
 
+// Workgroups are dealt to the eight XCDs round robin; renumber them so that
+// each XCD (with its own L2) takes one contiguous range of the work.
+__device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t nblocks) {
+    const uint32_t per = (nblocks + 7u) / 8u;
+    const uint32_t xcd = b % 8u, slot = b / 8u;
+    const uint32_t full = nblocks % 8u == 0 ? 8u : nblocks % 8u;  // XCDs that get `per` blocks
+    const uint32_t base = xcd < full ? xcd * per : full * per + (xcd - full) * (per - 1u);
+    return base + slot;
+}
+
 // Position of every valid entry in the inverse order: the regulariser writes
 // the partial of entry e to record inv_slot[e], so that each splat's records
-// are contiguous for the gather.
+// are contiguous for the gather.  Bound by the scattered 4-byte writes: 16 lanes take
+// a splat's list, the splats in cell order, so that the lists that share a line of
+// inv_slot are close in time and on one XCD.  8 million entries:
+// 38 us (99 with a thread an entry, in the order of the lists).
 __global__ __launch_bounds__(256) void k_inv_slots(const uint32_t* inv_entries, const uint32_t* inv_offsets,
-                                                   uint32_t n, uint32_t* inv_slot) {
-    const uint32_t pos = blockIdx.x * 256u + threadIdx.x;
-    if (pos >= inv_offsets[n]) return;
-    inv_slot[inv_entries[pos]] = pos;
+                                                   const uint32_t* order, uint32_t n, uint32_t* inv_slot) {
+    const uint32_t p = xcd_block(blockIdx.x, gridDim.x) * 16u + threadIdx.x / 16u;
+    if (p >= n) return;
+    const uint32_t v = order[p], end = inv_offsets[v + 1u];
+    for (uint32_t pos = inv_offsets[v] + threadIdx.x % 16u; pos < end; pos += 16u) inv_slot[inv_entries[pos]] = pos;
 }
 
 // ---------------------------------------------------------------- loss
@@ -396,16 +474,6 @@ __device__ __forceinline__ void rot_adjoint(const GFrame& f, const float G[9], f
     out[1] = (g[1] - x * dot) * f.inv_q;
     out[2] = (g[2] - y * dot) * f.inv_q;
     out[3] = (g[3] - z * dot) * f.inv_q;
-}
-
-// Workgroups are dealt to the eight XCDs round robin; renumber them so that
-// each XCD (with its own L2) takes one contiguous range of the work.
-__device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t nblocks) {
-    const uint32_t per = (nblocks + 7u) / 8u;
-    const uint32_t xcd = b % 8u, slot = b / 8u;
-    const uint32_t full = nblocks % 8u == 0 ? 8u : nblocks % 8u;  // XCDs that get `per` blocks
-    const uint32_t base = xcd < full ? xcd * per : full * per + (xcd - full) * (per - 1u);
-    return base + slot;
 }
 
 // Samples run in the cell order of the neighbour lists, so that the
@@ -748,10 +816,10 @@ KnnLayout knn_layout(int n, int k) {
     L.o_vb = take(sort_n);
     L.o_hist = take(256ull * ((sort_n + SORT_TILE - 1) / SORT_TILE));
     const uint64_t hist_n = 256ull * ((sort_n + SORT_TILE - 1) / SORT_TILE);
-    L.o_scan = take((std::max<uint64_t>(hist_n, sort_n) + SCAN_TILE - 1) / SCAN_TILE + 64);
+    L.o_scan = take((std::max<uint64_t>(std::max<uint64_t>(hist_n, sort_n), L.cell_cap) + SCAN_TILE - 1) / SCAN_TILE + 64);
     L.o_pos = take(4 * n1);
     L.o_start = take(L.cell_cap);
-    L.o_end = take(L.cell_cap);
+    L.o_end = take((uint64_t)L.cell_cap + 1);
     L.words = off;
     return L;
 }
@@ -769,7 +837,7 @@ hipError_t launch_knn(const float* mean, int n, int k, uint32_t* knn, uint32_t* 
     KnnGrid* grid = reinterpret_cast<KnnGrid*>(ws + L.o_grid);
     float* parts = reinterpret_cast<float*>(ws + L.o_parts);
     hipLaunchKernelGGL(k_knn_bounds, dim3(L.bound_parts), dim3(256), 0, stream, mean, n, parts);
-    hipLaunchKernelGGL(k_knn_grid, dim3(1), dim3(64), 0, stream, parts, (int)L.bound_parts, n, L.cell_cap, grid);
+    hipLaunchKernelGGL(k_knn_grid, dim3(1), dim3(256), 0, stream, parts, (int)L.bound_parts, n, L.cell_cap, grid);
     hipLaunchKernelGGL(k_knn_cells, dim3(blocks(n, 256)), dim3(256), 0, stream, mean, n, grid, ws + L.o_keys);
     // three 8-bit passes over the 24-bit Morton keys end in the "a" buffers:
     // the sorted values land in order_out
@@ -780,19 +848,22 @@ hipError_t launch_knn(const float* mean, int n, int k, uint32_t* knn, uint32_t* 
     if (in_b) return hipErrorInvalidValue;  // not reached with an odd number of passes
     const uint32_t* skeys = sb.keys_a;
     const uint32_t* order = order_out;
-    e = launch_fill_u32(ws + L.o_start, 0u, L.cell_cap, stream);
+    // the cells' ranges, then (in place of their ends) the first of each in row order
+    uint32_t *start = ws + L.o_start, *first = ws + L.o_end;
+    e = launch_fill_u32(first, 0u, L.cell_cap, stream);
     if (e != hipSuccess) return e;
-    e = launch_fill_u32(ws + L.o_end, 0u, L.cell_cap, stream);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_knn_ranges, dim3(blocks(n, 256)), dim3(256), 0, stream, skeys, n, grid, ws + L.o_start,
-                       ws + L.o_end);
     const dim3 qg(blocks(n, 256)), qb(256);
-    const uint32_t *cs0 = ws + L.o_start, *ce0 = ws + L.o_end;
+    hipLaunchKernelGGL(k_knn_ranges, qg, qb, 0, stream, skeys, n, grid, start, first);
+    hipLaunchKernelGGL(k_knn_counts, dim3(blocks(L.cell_cap, 256)), qb, 0, stream, start, first, L.cell_cap);
+    e = scan_exclusive(first, first, L.cell_cap, ws + L.o_scan, first + L.cell_cap, stream);
+    if (e != hipSuccess) return e;
     float4* pos = reinterpret_cast<float4*>(ws + L.o_pos);
-    hipLaunchKernelGGL(k_knn_sorted_pos, qg, qb, 0, stream, mean, n, order, pos);
+    float4* row_pos = reinterpret_cast<float4*>(ws + L.o_kb);  // 2 n k words; no list for k = 1
+    if (k >= 2)
+        hipLaunchKernelGGL(k_knn_sorted_pos, qg, qb, 0, stream, mean, n, order, skeys, grid, start, first, pos, row_pos);
     switch (k) {
 #define GESR_KNN_CASE(KK) \
-    case KK: hipLaunchKernelGGL(k_knn_query<KK>, qg, qb, 0, stream, pos, n, grid, cs0, ce0, knn); break;
+    case KK: hipLaunchKernelGGL(k_knn_query<KK>, qg, qb, 0, stream, pos, row_pos, n, grid, first, knn); break;
         GESR_KNN_CASE(2) GESR_KNN_CASE(3) GESR_KNN_CASE(4) GESR_KNN_CASE(5) GESR_KNN_CASE(6) GESR_KNN_CASE(7)
         GESR_KNN_CASE(8) GESR_KNN_CASE(9) GESR_KNN_CASE(10) GESR_KNN_CASE(11) GESR_KNN_CASE(12)
         GESR_KNN_CASE(13) GESR_KNN_CASE(14) GESR_KNN_CASE(15) GESR_KNN_CASE(16)
@@ -813,7 +884,7 @@ hipError_t launch_knn(const float* mean, int n, int k, uint32_t* knn, uint32_t* 
     const uint32_t* ikeys = in_b ? ib.keys_b : ib.keys_a;
     hipLaunchKernelGGL(k_inv_offsets, dim3(blocks(total + 1, 256)), dim3(256), 0, stream, ikeys, total, (uint32_t)n,
                        inv_offsets);
-    hipLaunchKernelGGL(k_inv_slots, dim3(blocks(total, 256)), dim3(256), 0, stream, inv_entries, inv_offsets,
+    hipLaunchKernelGGL(k_inv_slots, dim3(blocks(n, 16)), dim3(256), 0, stream, inv_entries, inv_offsets, order,
                        (uint32_t)n, inv_slot);
     return hipGetLastError();
 }

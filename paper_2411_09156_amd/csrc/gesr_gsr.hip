@@ -400,14 +400,10 @@ __global__ __launch_bounds__(256) void k_gsr_frames(GsrArgs a) {
         dst[c] = make_float4(f[4 * c], f[4 * c + 1], f[4 * c + 2], f[4 * c + 3]);
 }
 
-__device__ __forceinline__ GFrame load_gframe(const float* frames, uint32_t i, float rho) {
-    const float4* s = reinterpret_cast<const float4*>(frames + (size_t)i * GSR_FRAME_FLOATS);
-    float f[GSR_FRAME_FLOATS];
-#pragma unroll
-    for (int c = 0; c < GSR_FRAME_FLOATS / 4; ++c) {
-        const float4 v = s[c];
-        f[4 * c] = v.x; f[4 * c + 1] = v.y; f[4 * c + 2] = v.z; f[4 * c + 3] = v.w;
-    }
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ GFrame unpack_gframe(f32x4 r0, f32x4 r1, f32x4 r2, f32x4 r3, float rho) {
+    const float f[GSR_FRAME_FLOATS] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w,
+                                       r2.x, r2.y, r2.z, r2.w, r3.x, r3.y, r3.z, r3.w};
     GFrame g;
     const float w = f[0], x = f[1], y = f[2], z = f[3];
     g.R[0] = 1.f - 2.f * (y * y + z * z); g.R[1] = 2.f * (x * y - w * z); g.R[2] = 2.f * (x * z + w * y);
@@ -429,6 +425,48 @@ __device__ __forceinline__ GFrame load_gframe(const float* frames, uint32_t i, f
     g.io = g.o > 0.f ? __builtin_amdgcn_rcpf(g.o) : 0.f;
     return g;
 }
+
+__device__ __forceinline__ GFrame load_gframe(const float* frames, uint32_t i, float rho) {
+    const f32x4* s = reinterpret_cast<const f32x4*>(frames + (size_t)i * GSR_FRAME_FLOATS);
+    return unpack_gframe(s[0], s[1], s[2], s[3], rho);
+}
+
+// LDS written by a wave is read by its other lanes, or the other way round.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The 64-byte records that a wave's lanes each want, by four neighbouring lanes
+// together: load q takes lane 4 g + q's record, lane 4 g + t its quarter t ^ q, so a
+// load touches 16 lines where a lane by itself would touch 64, and the caches serve
+// four lanes of a line at once.  The quarters change hands in LDS (4 KB a wave); with
+// t ^ q neither side meets its banks twice.
+struct QuadRecord {
+    f32x4 v0, v1, v2, v3;
+    // idx: the records of lanes 4 g .. 4 g + 3
+    __device__ __forceinline__ void load(const float* base, uint4 idx, uint32_t last) {
+        const f32x4* b = reinterpret_cast<const f32x4*>(base);
+        const uint32_t t = __lane_id() & 3u;
+        v0 = b[(size_t)min(idx.x, last) * 4u + t];
+        v1 = b[(size_t)min(idx.y, last) * 4u + (t ^ 1u)];
+        v2 = b[(size_t)min(idx.z, last) * 4u + (t ^ 2u)];
+        v3 = b[(size_t)min(idx.w, last) * 4u + (t ^ 3u)];
+    }
+    __device__ __forceinline__ GFrame own(f32x4* stage, float rho) const {
+        const uint32_t l = __lane_id(), q = l & 3u;
+        stage[l] = v0;
+        stage[64u + l] = v1;
+        stage[128u + l] = v2;
+        stage[192u + l] = v3;
+        wave_lds_fence();
+        const f32x4* s = stage + q * 64u + (l & ~3u);
+        const GFrame f = unpack_gframe(s[q], s[1u ^ q], s[2u ^ q], s[3u ^ q], rho);
+        wave_lds_fence();
+        return f;
+    }
+};
 
 // One Eq. 9 term at x: the Mahalanobis vector a = diag(1/sig) R^T (x - mu),
 // q = |a|^2, T = o exp(-kappa q^(beta/2)), c = dT/dq * 2 = -kappa beta q^(beta/2-1) T.
@@ -479,43 +517,37 @@ __device__ __forceinline__ void rot_adjoint(const GFrame& f, const float G[9], f
 // Samples run in the cell order of the neighbour lists, so that the
 // neighbours a wave (and an XCD's L2) gathers overlap; partials are stored at
 // the sample's position in that order (the inverse lists refer to these
-// positions).  A sample's list is staged in LDS.
+// positions).  A sample's list is staged in LDS.  Bound by the frames' gathers (pass 1)
+// and by writing the records (pass 2).  500,000 samples, k = 16: 295 us, 88 of them
+// pass 1; with a lane gathering its own frames and writing its own record 395 and 102,
+// with four lanes together but ordinary stores (which push the frames out of the
+// caches) 330.
 __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
-    __shared__ uint32_t s_nb[GESR_KNN_MAX][128];
-    __shared__ uint32_t s_slot[GESR_KNN_MAX][128];
+    __shared__ __attribute__((aligned(16))) uint32_t s_nb[GESR_KNN_MAX][128];
+    __shared__ f32x4 s_rec[128 * 4];
     const uint32_t p = xcd_block(blockIdx.x, gridDim.x) * 128u + threadIdx.x;
-    if (p >= (uint32_t)a.n) return;
-    const uint32_t j = a.order[p];
+    const bool in = p < (uint32_t)a.n;
+    const uint32_t j = a.order[in ? p : 0u];
     const int K = a.k;
     {
         const uint32_t* row = a.knn + (size_t)j * K;
-        for (int s = 0; s < K; ++s) s_nb[s][threadIdx.x] = row[s];
-        if (a.partials) {
-            const uint32_t* srow = a.inv_slot + (size_t)p * K;
-            for (int s = 0; s < K; ++s) s_slot[s][threadIdx.x] = srow[s];
-        }
+        const uint32_t none = in ? 0u : 0xFFFFFFFFu;
+#pragma unroll 8
+        for (int s = 0; s < K; ++s) s_nb[s][threadIdx.x] = row[s] | none;
     }
-    // each thread reads back only its own column: no barrier needed
+    wave_lds_fence();  // four lanes read each other's columns
     const uint32_t* nbl = &s_nb[0][threadIdx.x];
-    const uint32_t* sll = &s_slot[0][threadIdx.x];
 #define nb_at(s) nbl[(s) * 128]
-    // the partial of slot s goes to record inv_slot[p * k + s]: each splat's
-    // records end up contiguous, in inverse-list order
-#define rec_at(s) (a.partials + (size_t)sll[(s) * 128] * GSR_PARTIAL_STRIDE)
+#define quad_at(s) (*reinterpret_cast<const uint4*>(&s_nb[s][threadIdx.x & ~3u]))
+    f32x4* stage = s_rec + (threadIdx.x & ~63u) * 4u;
+    const uint32_t last = (uint32_t)a.n - 1u;
     const bool with_part = a.partials != nullptr;
-    const bool on = a.mask == nullptr || a.mask[j] != 0;
-    if (!on) {
-        if (with_part)
-            for (int s = 0; s < K; ++s) {
-                if (nb_at(s) >= (uint32_t)a.n) continue;  // padding slots have no record
-                for (int c = 0; c < GSR_PARTIAL_STRIDE / 4; ++c)
-                    reinterpret_cast<float4*>(rec_at(s))[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-            }
+    const bool on = in && (a.mask == nullptr || a.mask[j] != 0);
+    if (in && !on) {
         a.sample_out[(size_t)j * 4 + 0] = 0.f;
         a.sample_out[(size_t)j * 4 + 1] = 0.f;
         a.sample_out[(size_t)j * 4 + 2] = -1.f;
         a.sample_out[(size_t)j * 4 + 3] = 0.f;
-        return;
     }
     const float kappa = a.kappa;
     const GFrame f0 = load_gframe(a.frames, j, a.rho);
@@ -530,15 +562,13 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
     float d = 0.f, gd[3] = {0.f, 0.f, 0.f}, best = -1.f;
     int gs = 0;
     // the next neighbour's frame is loaded while this one is evaluated
-    // (padding slots, n < k, load slot 0's frame and are skipped)
-    GFrame fn = load_gframe(a.frames, j, a.rho);
+    // (padding slots, n < k, load some frame and are skipped)
+    QuadRecord next;
+    next.load(a.frames, quad_at(0), last);
     for (int s = 0; s < K; ++s) {
         const uint32_t i = nb_at(s);
-        const GFrame f = fn;
-        if (s + 1 < K) {
-            const uint32_t i1 = nb_at(s + 1);
-            fn = load_gframe(a.frames, i1 < (uint32_t)a.n ? i1 : j, a.rho);
-        }
+        const GFrame f = next.own(stage, a.rho);
+        if (s + 1 < K) next.load(a.frames, quad_at(s + 1), last);
         if (i >= (uint32_t)a.n) continue;
         const Term t = eval_term(f, f0.mu, d0, kappa);
         d += t.T;
@@ -550,7 +580,7 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
         }
     }
     // SDF terms of g* (Eq. 10-13)
-    const GFrame fg = load_gframe(a.frames, nb_at(gs), a.rho);
+    const GFrame fg = load_gframe(a.frames, on ? nb_at(gs) : j, a.rho);
     int ks = 0;
     if (fg.sig[1] < fg.sig[ks]) ks = 1;
     if (fg.sig[2] < fg.sig[ks]) ks = 2;
@@ -590,10 +620,7 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
                 l_nor += e * e;
             }
     }
-    a.sample_out[(size_t)j * 4 + 0] = l_sdf;
-    a.sample_out[(size_t)j * 4 + 1] = l_nor;
-    a.sample_out[(size_t)j * 4 + 2] = (float)gs;
-    a.sample_out[(size_t)j * 4 + 3] = d;
+    if (on) *reinterpret_cast<float4*>(a.sample_out + (size_t)j * 4) = make_float4(l_sdf, l_nor, (float)gs, d);
     if (!with_part) return;
 
     // adjoints of the sample's loss w_sdf l_sdf + w_nor l_nor
@@ -617,19 +644,14 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
     float gx[3] = {L_h * nrm[0], L_h * nrm[1], L_h * nrm[2]};  // dl / dx
 
     // pass 2, slot 0 last (it also carries the sample point's dependence)
-    {
-        const uint32_t il = nb_at(K - 1);
-        fn = load_gframe(a.frames, il < (uint32_t)a.n ? il : j, a.rho);
-    }
+    next.load(a.frames, quad_at(K - 1), last);
     for (int s = K - 1; s >= 0; --s) {
         const uint32_t i = nb_at(s);
-        const GFrame f = fn;
-        if (s > 0) {
-            const uint32_t i1 = nb_at(s - 1);
-            fn = load_gframe(a.frames, i1 < (uint32_t)a.n ? i1 : j, a.rho);
-        }
-        if (i >= (uint32_t)a.n) continue;  // padding slot: no record
-        float* ps = rec_at(s);
+        const GFrame f = next.own(stage, a.rho);
+        if (s > 0) next.load(a.frames, quad_at(s - 1), last);
+        // the partial of slot s goes to record inv_slot[p * k + s]: each splat's
+        // records end up contiguous, in inverse-list order (padding slots have none)
+        const uint32_t slot = i < (uint32_t)a.n ? a.inv_slot[(size_t)p * K + s] : 0xFFFFFFFFu;
         const Term t = eval_term(f, f0.mu, d0, kappa);
         // b = diag(1/sig) R^T u, scaled by gmax like u
         float b[3];
@@ -685,56 +707,77 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
         g_beta += dphi * (f.sig[0] * g_sig[0] + f.sig[1] * g_sig[1] + f.sig[2] * g_sig[2]);
         float g_q[4];
         rot_adjoint(f, G, g_q);
-        float4* o4 = reinterpret_cast<float4*>(ps);
-        o4[0] = make_float4(g_mu[0], g_mu[1], g_mu[2], f.phi * g_sig[0]);
-        o4[1] = make_float4(f.phi * g_sig[1], f.phi * g_sig[2], g_q[0], g_q[1]);
-        o4[2] = make_float4(g_q[2], g_q[3], g_o, g_beta);
-        // the whole 64-byte record, so that the cache takes the write without
-        // reading the line first
-        o4[3] = make_float4(0.f, 0.f, 0.f, 0.f);
+        // A lane's own record would be four stores to a line of its own each: four
+        // neighbouring lanes write four records, a whole 64-byte line a store (whole, so
+        // that the cache takes it without reading the line first).  The record's
+        // unused quarter carries its place through LDS; the quarters are rotated by the
+        // lane so that neither side meets its banks twice.
+        const uint32_t l4 = threadIdx.x & 3u, rot = (threadIdx.x >> 2) & 3u;
+        f32x4* mine = stage + __lane_id() * 4u;
+        mine[rot] = on ? f32x4{g_mu[0], g_mu[1], g_mu[2], f.phi * g_sig[0]} : f32x4{0.f, 0.f, 0.f, 0.f};
+        mine[1u ^ rot] =
+            on ? f32x4{f.phi * g_sig[1], f.phi * g_sig[2], g_q[0], g_q[1]} : f32x4{0.f, 0.f, 0.f, 0.f};
+        mine[2u ^ rot] = on ? f32x4{g_q[2], g_q[3], g_o, g_beta} : f32x4{0.f, 0.f, 0.f, 0.f};
+        mine[3u ^ rot] = f32x4{__uint_as_float(slot), 0.f, 0.f, 0.f};
+        wave_lds_fence();
+        const f32x4* quad = stage + (__lane_id() & ~3u) * 4u;
+#pragma unroll
+        for (uint32_t q = 0; q < 4u; ++q) {
+            const uint32_t r = q ^ rot;
+            const uint32_t to = __float_as_uint(quad[r * 4u + (3u ^ rot)].x);
+            f32x4 v = quad[r * 4u + (l4 ^ rot)];
+            if (l4 == 3u) v.x = 0.f;
+            if (to != 0xFFFFFFFFu)
+                __builtin_nontemporal_store(
+                    v, reinterpret_cast<f32x4*>(a.partials + (size_t)to * GSR_PARTIAL_STRIDE) + l4);
+        }
+        wave_lds_fence();
     }
 }
 #undef nb_at
-#undef rec_at
+#undef quad_at
 
 // Gradient of each splat: the sum of its records, which the loss kernel wrote
-// contiguously in inverse-list order, added into the gradients.  Four
-// records per step keep several loads in flight; the sum runs in order.
+// contiguously in inverse-list order, added into the gradients.  Bound by reading
+// them: four lanes take a splat, a quarter of each record and so a whole line a load
+// (the last quarter is empty), four records in flight; the sum runs in order.
+// 8 million records, 512 MB: 115 us (138 with a lane a splat).
 __global__ __launch_bounds__(256) void k_gsr_gather(GsrArgs a) {
-    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-    if (i >= (uint32_t)a.n) return;
-    float acc[GSR_PARTIAL_FLOATS];
-#pragma unroll
-    for (int c = 0; c < GSR_PARTIAL_FLOATS; ++c) acc[c] = 0.f;
+    const uint32_t i = blockIdx.x * 64u + threadIdx.x / 4u, l4 = threadIdx.x & 3u;
+    if (i >= (uint32_t)a.n || l4 == 3u) return;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     const uint32_t e0 = a.inv_offsets[i], e1 = a.inv_offsets[i + 1];
+    const f32x4* rec = reinterpret_cast<const f32x4*>(a.partials) + l4;
     for (uint32_t e = e0; e < e1; e += 4) {
-        float4 v[4][3];
+        f32x4 v[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            if (e + t < e1) {
-                const float4* p = reinterpret_cast<const float4*>(a.partials + (size_t)(e + t) * GSR_PARTIAL_STRIDE);
-                v[t][0] = p[0];
-                v[t][1] = p[1];
-                v[t][2] = p[2];
-            } else {
-                v[t][0] = v[t][1] = v[t][2] = make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-        }
+        for (uint32_t t = 0; t < 4u; ++t)
+            v[t] = e + t < e1 ? rec[(size_t)(e + t) * (GSR_PARTIAL_STRIDE / 4)] : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            acc[0] += v[t][0].x; acc[1] += v[t][0].y; acc[2] += v[t][0].z; acc[3] += v[t][0].w;
-            acc[4] += v[t][1].x; acc[5] += v[t][1].y; acc[6] += v[t][1].z; acc[7] += v[t][1].w;
-            acc[8] += v[t][2].x; acc[9] += v[t][2].y; acc[10] += v[t][2].z; acc[11] += v[t][2].w;
+        for (uint32_t t = 0; t < 4u; ++t) {
+            acc.x += v[t].x;
+            acc.y += v[t].y;
+            acc.z += v[t].z;
+            acc.w += v[t].w;
         }
     }
     const size_t n = (size_t)a.n;
-    for (int c = 0; c < 3; ++c) {
-        a.g_mean[c * n + i] += acc[c];
-        a.g_scale[c * n + i] += acc[3 + c];
+    if (l4 == 0u) {
+        a.g_mean[i] += acc.x;
+        a.g_mean[n + i] += acc.y;
+        a.g_mean[2 * n + i] += acc.z;
+        a.g_scale[i] += acc.w;
+    } else if (l4 == 1u) {
+        a.g_scale[n + i] += acc.x;
+        a.g_scale[2 * n + i] += acc.y;
+        a.g_quat[i] += acc.z;
+        a.g_quat[n + i] += acc.w;
+    } else {
+        a.g_quat[2 * n + i] += acc.x;
+        a.g_quat[3 * n + i] += acc.y;
+        a.g_opacity[i] += acc.z;
+        a.g_beta[i] += acc.w;
     }
-    for (int c = 0; c < 4; ++c) a.g_quat[c * n + i] += acc[6 + c];
-    a.g_opacity[i] += acc[10];
-    a.g_beta[i] += acc[11];
 }
 
 // Sums of the per-sample losses in a fixed order: each block adds
@@ -896,7 +939,7 @@ hipError_t launch_gsr(GsrArgs a, hipStream_t stream) {
     }
     hipLaunchKernelGGL(k_gsr_frames, dim3(blocks(a.n, 256)), dim3(256), 0, stream, a);
     hipLaunchKernelGGL(k_gsr_loss, dim3(blocks(a.n, 128)), dim3(128), 0, stream, a);
-    if (a.partials) hipLaunchKernelGGL(k_gsr_gather, dim3(blocks(a.n, 256)), dim3(256), 0, stream, a);
+    if (a.partials) hipLaunchKernelGGL(k_gsr_gather, dim3(blocks(a.n, 64)), dim3(256), 0, stream, a);
     if (a.losses) {
         const unsigned nparts = blocks(a.n, GSR_SUM_BLOCK);
         hipLaunchKernelGGL(k_gsr_sum_blocks, dim3(nparts), dim3(256), 0, stream, a.sample_out, a.n, a.sum_parts);

@@ -255,4 +255,54 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
     return l == 0 ? 0ull : ((~0ull) >> (64 - l));
 }
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// LDS written by a wave is read by its other lanes, or the other way round.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// x of lanes 4 g .. 4 g + 3 (all lanes active).
+__device__ __forceinline__ uint4 quad_all(uint32_t x) {
+    const int v = (int)x;
+    return make_uint4((uint32_t)__builtin_amdgcn_mov_dpp(v, 0x00, 0xF, 0xF, true),
+                      (uint32_t)__builtin_amdgcn_mov_dpp(v, 0x55, 0xF, 0xF, true),
+                      (uint32_t)__builtin_amdgcn_mov_dpp(v, 0xAA, 0xF, 0xF, true),
+                      (uint32_t)__builtin_amdgcn_mov_dpp(v, 0xFF, 0xF, 0xF, true));
+}
+
+// The 64-byte records that a wave's lanes each want, by four neighbouring lanes
+// together: load q takes lane 4 g + q's record, lane 4 g + t its quarter t ^ q, so a
+// load touches 16 lines where a lane by itself would touch 64, and the caches serve
+// four lanes of a line at once.  The quarters change hands in LDS (4 KB a wave); with
+// t ^ q neither side meets its banks twice.
+struct QuadRecord {
+    f32x4 v0, v1, v2, v3;
+    // idx: the records of lanes 4 g .. 4 g + 3
+    __device__ __forceinline__ void load(const float* base, uint4 idx, uint32_t last) {
+        const f32x4* b = reinterpret_cast<const f32x4*>(base);
+        const uint32_t t = __lane_id() & 3u;
+        v0 = b[(size_t)min(idx.x, last) * 4u + t];
+        v1 = b[(size_t)min(idx.y, last) * 4u + (t ^ 1u)];
+        v2 = b[(size_t)min(idx.z, last) * 4u + (t ^ 2u)];
+        v3 = b[(size_t)min(idx.w, last) * 4u + (t ^ 3u)];
+    }
+    __device__ __forceinline__ void own(f32x4* stage, f32x4& r0, f32x4& r1, f32x4& r2, f32x4& r3) const {
+        const uint32_t l = __lane_id(), q = l & 3u;
+        stage[l] = v0;
+        stage[64u + l] = v1;
+        stage[128u + l] = v2;
+        stage[192u + l] = v3;
+        wave_lds_fence();
+        const f32x4* s = stage + q * 64u + (l & ~3u);
+        r0 = s[q];
+        r1 = s[1u ^ q];
+        r2 = s[2u ^ q];
+        r3 = s[3u ^ q];
+        wave_lds_fence();
+    }
+};
+
 }  // namespace gesr

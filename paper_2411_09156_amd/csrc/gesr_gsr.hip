@@ -400,7 +400,6 @@ __global__ __launch_bounds__(256) void k_gsr_frames(GsrArgs a) {
         dst[c] = make_float4(f[4 * c], f[4 * c + 1], f[4 * c + 2], f[4 * c + 3]);
 }
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ GFrame unpack_gframe(f32x4 r0, f32x4 r1, f32x4 r2, f32x4 r3, float rho) {
     const float f[GSR_FRAME_FLOATS] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w,
                                        r2.x, r2.y, r2.z, r2.w, r3.x, r3.y, r3.z, r3.w};
@@ -430,43 +429,6 @@ __device__ __forceinline__ GFrame load_gframe(const float* frames, uint32_t i, f
     const f32x4* s = reinterpret_cast<const f32x4*>(frames + (size_t)i * GSR_FRAME_FLOATS);
     return unpack_gframe(s[0], s[1], s[2], s[3], rho);
 }
-
-// LDS written by a wave is read by its other lanes, or the other way round.
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// The 64-byte records that a wave's lanes each want, by four neighbouring lanes
-// together: load q takes lane 4 g + q's record, lane 4 g + t its quarter t ^ q, so a
-// load touches 16 lines where a lane by itself would touch 64, and the caches serve
-// four lanes of a line at once.  The quarters change hands in LDS (4 KB a wave); with
-// t ^ q neither side meets its banks twice.
-struct QuadRecord {
-    f32x4 v0, v1, v2, v3;
-    // idx: the records of lanes 4 g .. 4 g + 3
-    __device__ __forceinline__ void load(const float* base, uint4 idx, uint32_t last) {
-        const f32x4* b = reinterpret_cast<const f32x4*>(base);
-        const uint32_t t = __lane_id() & 3u;
-        v0 = b[(size_t)min(idx.x, last) * 4u + t];
-        v1 = b[(size_t)min(idx.y, last) * 4u + (t ^ 1u)];
-        v2 = b[(size_t)min(idx.z, last) * 4u + (t ^ 2u)];
-        v3 = b[(size_t)min(idx.w, last) * 4u + (t ^ 3u)];
-    }
-    __device__ __forceinline__ GFrame own(f32x4* stage, float rho) const {
-        const uint32_t l = __lane_id(), q = l & 3u;
-        stage[l] = v0;
-        stage[64u + l] = v1;
-        stage[128u + l] = v2;
-        stage[192u + l] = v3;
-        wave_lds_fence();
-        const f32x4* s = stage + q * 64u + (l & ~3u);
-        const GFrame f = unpack_gframe(s[q], s[1u ^ q], s[2u ^ q], s[3u ^ q], rho);
-        wave_lds_fence();
-        return f;
-    }
-};
 
 // One Eq. 9 term at x: the Mahalanobis vector a = diag(1/sig) R^T (x - mu),
 // q = |a|^2, T = o exp(-kappa q^(beta/2)), c = dT/dq * 2 = -kappa beta q^(beta/2-1) T.
@@ -567,7 +529,9 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
     next.load(a.frames, quad_at(0), last);
     for (int s = 0; s < K; ++s) {
         const uint32_t i = nb_at(s);
-        const GFrame f = next.own(stage, a.rho);
+        f32x4 r0, r1, r2, r3;
+        next.own(stage, r0, r1, r2, r3);
+        const GFrame f = unpack_gframe(r0, r1, r2, r3, a.rho);
         if (s + 1 < K) next.load(a.frames, quad_at(s + 1), last);
         if (i >= (uint32_t)a.n) continue;
         const Term t = eval_term(f, f0.mu, d0, kappa);
@@ -647,7 +611,9 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
     next.load(a.frames, quad_at(K - 1), last);
     for (int s = K - 1; s >= 0; --s) {
         const uint32_t i = nb_at(s);
-        const GFrame f = next.own(stage, a.rho);
+        f32x4 r0, r1, r2, r3;
+        next.own(stage, r0, r1, r2, r3);
+        const GFrame f = unpack_gframe(r0, r1, r2, r3, a.rho);
         if (s > 0) next.load(a.frames, quad_at(s - 1), last);
         // the partial of slot s goes to record inv_slot[p * k + s]: each splat's
         // records end up contiguous, in inverse-list order (padding slots have none)

@@ -252,9 +252,18 @@ __device__ __forceinline__ void view_dir(const float* mean, const DevView& w, fl
 template <int DEG>
 __global__ __launch_bounds__(256) void k_project(ProjectArgs a) {
     constexpr int K = (DEG + 1) * (DEG + 1);
+    // Bound by writing the records.  A wave's records of a view are 4 KB in one piece:
+    // they are turned in LDS so that each store is 1 KB of it; the quarters are rotated
+    // so that neither side meets its banks twice.  3 million splats, 16 views: 893 us,
+    // 1,368 with a lane writing its own record (four stores to 64 lines each).
+    __shared__ f32x4 s_rec[4 * 256];
     const int n = a.n;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    const int i0 = blockIdx.x * blockDim.x + threadIdx.x;
+    const bool live = i0 < n;
+    const int i = live ? i0 : n - 1;
+    const uint32_t lane = __lane_id(), rot = (lane >> 2) & 3u;
+    f32x4* stage = s_rec + (threadIdx.x & ~63u) * 4u;
+    f32x4* mine = stage + lane * 4u;
     float mean[3], s[3], q[4];
     for (int k = 0; k < 3; ++k) {
         mean[k] = a.mean[k * n + i];
@@ -305,27 +314,37 @@ __global__ __launch_bounds__(256) void k_project(ProjectArgs a) {
         float chk = vp.u + vp.v + vp.L00 + vp.L10 + vp.L11 + op + beta + rgb[0] + rgb[1] + rgb[2] + qmax + vp.a +
                     vp.c + vp.det;
         keep = keep && isfinite(chk);
-        float4* rec = reinterpret_cast<float4*>(a.rec + vi * GESR_REC_FLOATS);
+        f32x4 r0 = {0.f, 0.f, 0.f, 0.f}, r1 = r0, r2 = r0, r3 = r0;
+        uint2 rc = make_uint2(0xFFFFFFFFu, 0u);  // culled: no rectangle
+        uint32_t touched = 0u, key = 0xFFFFFFFFu;
         if (keep) {
             int x0 = (int)fx0, x1 = (int)fx1, y0 = (int)fy0, y1 = (int)fy1;
             int tx0 = x0 / st.tile_w, tx1 = x1 / st.tile_w, ty0 = y0 / st.tile_h, ty1 = y1 / st.tile_h;
-            const uint2 rc = make_uint2((uint32_t)tx0 | ((uint32_t)ty0 << 16), (uint32_t)tx1 | ((uint32_t)ty1 << 16));
-            rec[0] = make_float4(vp.u, vp.v, vp.L00, vp.L10);
-            rec[1] = make_float4(vp.L11, op, beta, qmax);
-            rec[2] = make_float4(rgb[0], rgb[1], rgb[2], vp.p[2]);
-            rec[3] = make_float4(__uint_as_float(rc.x), __uint_as_float(rc.y), 0.f, 0.f);
-            a.tiles_touched[vi] = (uint32_t)((tx1 - tx0 + 1) * (ty1 - ty0 + 1));
+            rc = make_uint2((uint32_t)tx0 | ((uint32_t)ty0 << 16), (uint32_t)tx1 | ((uint32_t)ty1 << 16));
+            r0 = f32x4{vp.u, vp.v, vp.L00, vp.L10};
+            r1 = f32x4{vp.L11, op, beta, qmax};
+            r2 = f32x4{rgb[0], rgb[1], rgb[2], vp.p[2]};
+            touched = (uint32_t)((tx1 - tx0 + 1) * (ty1 - ty0 + 1));
+            key = __float_as_uint(vp.p[2]);
+        }
+        r3.x = __uint_as_float(rc.x);
+        r3.y = __uint_as_float(rc.y);
+        mine[rot] = r0;
+        mine[1u ^ rot] = r1;
+        mine[2u ^ rot] = r2;
+        mine[3u ^ rot] = r3;
+        wave_lds_fence();
+        f32x4* rec = reinterpret_cast<f32x4*>(a.rec) + ((size_t)v * n + (i0 - (int)lane)) * 4u;
+#pragma unroll
+        for (uint32_t c = 0; c < 4u; ++c) {
+            const uint32_t w = c * 64u + lane, r = w >> 2;
+            if (i0 - (int)lane + (int)r < n) rec[w] = stage[r * 4u + ((lane & 3u) ^ ((r >> 2) & 3u))];
+        }
+        wave_lds_fence();
+        if (live) {
+            a.tiles_touched[vi] = touched;
             reinterpret_cast<uint2*>(a.rect)[vi] = rc;
-            a.depth_key[vi] = __float_as_uint(vp.p[2]);
-        } else {
-            float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-            rec[0] = zero;
-            rec[1] = zero;
-            rec[2] = zero;
-            rec[3] = make_float4(__uint_as_float(0xFFFFFFFFu), 0.f, 0.f, 0.f);
-            a.tiles_touched[vi] = 0u;
-            reinterpret_cast<uint2*>(a.rect)[vi] = make_uint2(0xFFFFFFFFu, 0u);  // culled: no rectangle
-            a.depth_key[vi] = 0xFFFFFFFFu;
+            a.depth_key[vi] = key;
         }
     }
 }
@@ -515,16 +534,18 @@ __global__ __launch_bounds__(256) void k_project_bwd(ProjectBwdArgs a) {
 // Segmented sum of the visited partials per (view, splat).  The pair's
 // instance slots are contiguous (inst_base[vi] + j) and are taken in blocks of
 // 32 (one word of visited bits); within a block the set bits' partials are
-// added in ascending slot order.  A pair of at most kSegSmall instances is
-// summed by one lane (a sum per block, the two added at the end); a larger
+// added in ascending slot order.  A pair of at most kSegSmall instances has
+// a sum per block, the two added at the end; a larger
 // pair by an aligned group of kSegLanes lanes, lane l taking the blocks l,
 // l + kSegLanes, ... in ascending order, then a fixed DPP tree over the group;
 // a pair of more than kSegHuge instances likewise by the whole wave (a DPP
 // tree per 16-lane row, then the four row totals in row order).  The order
 // depends only on the pair's own instance count, so a batch of views and
-// views rendered one at a time give identical sums.  One thread per pair: the
-// small pairs (most of them) keep every lane busy, then each wave sums its
-// huge pairs one at a time and hands the other large ones to its eight
+// views rendered one at a time give identical sums.  One thread per pair looks
+// up its bits; the small pairs (most of them) that have any are then summed 16 at
+// a time, four lanes a pair and a quarter of the partial each (bound by the scattered
+// partials: 1,028 us on 3M splats x 16 views, 1,400 with a lane a pair), then each
+// wave sums its huge pairs one at a time and hands the other large ones to its eight
 // groups, eight at a time (the longest pairs, thousands of instances, would
 // otherwise serialise hundreds of dependent loads on eight lanes).
 // A pair that no tile reached (four of five on 3M splats x 16 views) gets a clear bit
@@ -545,6 +566,30 @@ __device__ __forceinline__ uint32_t seg_bits(const SegReduceArgs& a, uint64_t ba
     uint32_t bits = sh != 0u ? (w0 >> sh) | (w1 << (32u - sh)) : w0;
     if (cnt - j0 < 32u) bits &= (1u << (cnt - j0)) - 1u;
     return bits;
+}
+
+// Adds a quarter of the partials of the set bits (instances from slot s0) to acc.
+__device__ __forceinline__ void seg_quarter(const f32x4* src, uint64_t s0, uint32_t bits, f32x4& acc) {
+    // up to four visited partials in flight, then added in ascending order
+    while (bits != 0u) {
+        f32x4 v[4];
+        bool have[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            have[u] = bits != 0u;
+            const uint32_t b = have[u] ? (uint32_t)__builtin_ctz(bits) : 0u;
+            bits &= bits - 1u;
+            v[u] = have[u] ? src[(s0 + b) * (kPartialStride / 4)] : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (have[u]) {
+                acc.x += v[u].x;
+                acc.y += v[u].y;
+                acc.z += v[u].z;
+                acc.w += v[u].w;
+            }
+    }
 }
 
 // Adds the partials of the set bits (instances from slot s0) to acc.
@@ -592,21 +637,34 @@ __global__ __launch_bounds__(256) void k_seg_reduce(SegReduceArgs a) {
     const uint64_t base = valid ? a.inst_base[vi] : 0u;
     const uint64_t nwords = (a.m_cap + 31) / 32;
     const bool small = cnt <= kSegSmall;
-    bool reached = false;
+    // the small pairs with a visited slot, 16 of the wave's at a time, a quarter of each
+    // partial by one of four lanes
+    __shared__ uint8_t s_pick[256];
+    uint8_t* pick_of = s_pick + (threadIdx.x & ~63u);
+    uint32_t w0 = 0u, w1 = 0u;
     if (valid && small) {
-        const uint32_t b0 = cnt > 0 ? seg_bits(a, base, cnt, 0u, nwords) : 0u;
-        const uint32_t b1 = cnt > 32 ? seg_bits(a, base, cnt, 32u, nwords) : 0u;
-        reached = (b0 | b1) != 0u;
-        if (reached || a.all_rows) {
-            float acc0[NP], acc1[NP];
-#pragma unroll
-            for (int k = 0; k < NP; ++k) acc0[k] = acc1[k] = 0.f;
-            seg_block<NP>(a, base, b0, acc0);
-            seg_block<NP>(a, base + 32u, b1, acc1);
-#pragma unroll
-            for (int k = 0; k < NP; ++k) acc0[k] += acc1[k];
-            seg_write<NP>(a, vi, acc0);
-        }
+        w0 = cnt > 0 ? seg_bits(a, base, cnt, 0u, nwords) : 0u;
+        w1 = cnt > 32 ? seg_bits(a, base, cnt, 32u, nwords) : 0u;
+    }
+    const bool reached = (w0 | w1) != 0u;
+    const uint64_t todo = __ballot(valid && small && (reached || a.all_rows));
+    const uint32_t n_todo = (uint32_t)__popcll(todo);
+    if (todo >> lane & 1ull) pick_of[__popcll(todo & lanemask_lt())] = (uint8_t)lane;
+    wave_lds_fence();
+    for (uint32_t k = lane / 4u; k - lane / 4u < n_todo; k += 16u) {
+        const uint32_t pick = k < n_todo ? pick_of[k] : lane;
+        const uint32_t b0 = (uint32_t)__shfl((int)w0, (int)pick, 64), b1 = (uint32_t)__shfl((int)w1, (int)pick, 64);
+        const uint64_t first = (uint64_t)(uint32_t)__shfl((int)(uint32_t)base, (int)pick, 64);
+        if (k >= n_todo || lane % 4u == 3u) continue;
+        const f32x4* src = reinterpret_cast<const f32x4*>(a.partials) + lane % 4u;
+        f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+        seg_quarter(src, first, b0, acc0);
+        seg_quarter(src, first + 32u, b1, acc1);
+        acc0.x += acc1.x;
+        acc0.y += acc1.y;
+        acc0.z += acc1.z;
+        acc0.w += acc1.w;
+        reinterpret_cast<f32x4*>(a.grad2d + (size_t)(vi - lane + pick) * GESR_GRAD2D_FLOATS)[lane % 4u] = acc0;
     }
     uint64_t nonzero = __ballot(reached);
     const uint64_t wave0 = vi - lane;

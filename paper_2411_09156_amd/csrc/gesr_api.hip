@@ -422,7 +422,9 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
     uint32_t* order_vd = nullptr;
     if (st->radix_bits == 8) {
         db.block_hist = reinterpret_cast<uint32_t*>(s.sell);
-        GESR_TRY(hip_check(ctx, depth_sort(proj->depth_key, (uint32_t)n, (uint32_t)V, db, &order_vd, strm), "depth sort"));
+        GESR_TRY(hip_check(ctx, depth_sort(proj->depth_key, (uint32_t)n, (uint32_t)V, db, proj->rec, &order_vd, s.srect,
+                                          s.sell, strm),
+                           "depth sort"));
     } else {
         bool in_b = false;
         const int vbits = bits_for((uint64_t)V);
@@ -448,7 +450,8 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
     }
     // 3. row lists: every pair in the rows its rectangle covers (level 1), each
     //    entry with the columns its ellipse reaches in that row
-    GESR_TRY(hip_check(ctx, launch_gather_rects(order_vd, proj->rec, g.vn, s.srect, s.sell, strm), "rectangles"));
+    if (st->radix_bits != 8 || (uint32_t)n > DEPTH_SORT_SMALL)
+        GESR_TRY(hip_check(ctx, launch_gather_rects(order_vd, proj->rec, g.vn, s.srect, s.sell, strm), "rectangles"));
     IsArgs ia;
     memset(&ia, 0, sizeof ia);
     ia.n = n;
@@ -469,11 +472,6 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
     l1.item_ell = s.sell;  // each row entry carries its own row's columns
     l1.tile_w = st->tile_w;
     l1.tile_h = st->tile_h;
-    GESR_TRY(hip_check(ctx, launch_interval_lists(l1, 1, strm), "row list counts"));
-    GESR_TRY(hip_check(ctx, scan_exclusive(s.row_count, s.row_start, g.total_rows, s.scan_partials, s.counters, strm,
-                                           bins->m_cap),
-                       "row list starts"));
-    GESR_TRY(hip_check(ctx, launch_interval_scatter(l1, 1, strm), "row lists"));
     // 4. tile lists: every row-list entry in the tiles of its columns (level 2)
     IsArgs l2 = ia;
     l2.items = s.rowlist;
@@ -486,7 +484,9 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
     l2.out_vals = bins->val_sorted;
     l2.out_keys = bins->tile_sorted;
     l2.out_cap = bins->m_cap;
-    GESR_TRY(hip_check(ctx, launch_interval_lists(l2, 2, strm), "tile list counts"));
+    plan_interval_levels(&l1, &l2);
+    GESR_TRY(hip_check(ctx, launch_row_lists(l1, l2, (uint32_t)g.total_rows, s.counters, strm), "row lists"));
+    GESR_TRY(hip_check(ctx, launch_tile_counts(l2, strm), "tile list counts"));
     // 5. list starts, ranges, and the worklist: tiles by decreasing list length, or by
     //    decreasing work of a previous forward (the positions each tile evaluated
     //    before terminating)
@@ -501,7 +501,7 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
     tl.worklist = bins->worklist;
     tl.sort = SortBuffers{s.w_keys_a, s.w_vals_a, s.w_keys_b, nullptr, s.block_hist, s.scan_partials};
     GESR_TRY(hip_check(ctx, launch_tile_lists(tl, strm), "tile list starts"));
-    GESR_TRY(hip_check(ctx, launch_interval_scatter(l2, 2, strm), "tile lists"));
+    GESR_TRY(hip_check(ctx, launch_tile_scatter(l2, strm), "tile lists"));
     ctx->err.clear();
     return GESR_OK;
 }

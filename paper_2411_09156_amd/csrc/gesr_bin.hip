@@ -390,6 +390,53 @@ __device__ __forceinline__ void lds_sort(uint32_t* s_key, uint32_t* s_pay, uint3
     }
 }
 
+// ----------------------------------------------------------------- binning
+// The footprint ellipse of a projected record, q = (L00 dx + L10 dy)^2 +
+// (L11 dy)^2 <= Q, with Q its bound qmax widened by 2^-8 (so that float32
+// rounding can only widen what follows), and the two row-independent
+// quantities of its per-row extents: ym = sqrt(Q) / L11, the half-height, and
+// dyr = -L10 sqrt(Q) / (L11 sqrt(L10^2 + L11^2)), the dy of its rightmost
+// point (the leftmost is at -dyr).  Stored per item as (u, v, L00, L10),
+// (L11, Q, ym, dyr).  Square roots (sqrtf) and quotients (__fdiv_rn) are
+// correctly rounded, so the values are reproducible.
+__device__ __forceinline__ void row_ellipse(f32x4 a, f32x4 b, f32x4& e0, f32x4& e1) {
+    const float l10 = a.w, l11 = b.x;
+    const float Q = b.w + b.w * 0.00390625f;
+    const float sq = sqrtf(Q);
+    const float rr = sqrtf(l10 * l10 + l11 * l11);
+    e0 = a;
+    e1 = f32x4{l11, Q, __fdiv_rn(sq, l11), __fdiv_rn(-(l10 * sq), l11 * rr)};
+}
+
+// The rectangle and the ellipse of item k from its record's quarters 0, 1 and 3.
+// Culled pairs carry the rectangle (0xFFFFFFFF, 0), which no rectangle has
+// (its corners are tile indices below 2^16).
+__device__ __forceinline__ void write_rect(f32x4 r0, f32x4 r1, f32x4 r3, uint64_t k, uint2* out, float4* ell) {
+    const uint2 r = make_uint2(__float_as_uint(r3.x), __float_as_uint(r3.y));
+    out[k] = r;
+    f32x4 e0 = {0.f, 0.f, 0.f, 0.f}, e1 = e0;
+    if (r.x != 0xFFFFFFFFu) row_ellipse(r0, r1, e0, e1);
+    reinterpret_cast<f32x4*>(ell)[2 * k] = e0;
+    reinterpret_cast<f32x4*>(ell)[2 * k + 1] = e1;
+}
+
+// The rectangle is read from the pair's record (its fourth 16-byte word), so a
+// pair costs one gathered line: the ellipse terms sit in the same 64 bytes.
+// Bound by the gathered lines, which four
+// lanes take together: 48 million pairs GATHER_A us, 4 million GATHER_B.
+__global__ __launch_bounds__(256) void k_gather_rects(const uint32_t* order, const float* rec, uint64_t count,
+                                                      uint2* out, float4* ell) {
+    __shared__ f32x4 s_stage[4 * 256];
+    const uint64_t k = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    const uint32_t p = order[k < count ? k : count - 1];
+    QuadRecord q;
+    q.load(rec, quad_all(p), 0xFFFFFFFFu);
+    f32x4 r0, r1, r2, r3;
+    q.own(s_stage + (threadIdx.x & ~63u) * 4u, r0, r1, r2, r3);
+    if (k >= count) return;
+    write_rect(r0, r1, r3, k, out, ell);
+}
+
 // -------------------------------------------------------- (view, depth) sort
 // The pairs come view by view (pair = view * n + splat), so the (view, depth) order
 // is each view's pairs by their 32 depth bits: blocks of keys never straddle a view
@@ -397,9 +444,11 @@ __device__ __forceinline__ void lds_sort(uint32_t* s_key, uint32_t* s_pay, uint3
 
 // n <= 4,096: one workgroup per view sorts in LDS.  Bound by its four serial digit
 // passes; 2,000 pairs take 13 us, where the launches of four passes over memory
-// (counts, scan and scatter) took 60.
+// (counts, scan and scatter) took 60.  The items' rectangles are gathered at the end,
+// which saves a launch.
 template <int ITEMS>
-__global__ __launch_bounds__(1024) void k_depth_sort_small(const uint32_t* keys, uint32_t n, uint32_t* order) {
+__global__ __launch_bounds__(1024) void k_depth_sort_small(const uint32_t* keys, uint32_t n, uint32_t* order,
+                                                           const float* rec, uint2* rect, float4* ell) {
     __shared__ uint32_t s_key[1024 * ITEMS], s_pay[1024 * ITEMS], s_hist[16][256], s_start[256], s_wave[17];
     const uint32_t first = blockIdx.x * n;
     for (uint32_t i = threadIdx.x; i < n; i += 1024u) {
@@ -408,7 +457,12 @@ __global__ __launch_bounds__(1024) void k_depth_sort_small(const uint32_t* keys,
     }
     __syncthreads();
     lds_sort<ITEMS, true>(s_key, s_pay, n, 0, 32, s_hist, s_start, s_wave);
-    for (uint32_t i = threadIdx.x; i < n; i += 1024u) order[first + i] = s_pay[i];
+    for (uint32_t i = threadIdx.x; i < n; i += 1024u) {
+        const uint32_t p = s_pay[i];
+        const f32x4* r = reinterpret_cast<const f32x4*>(rec + (size_t)p * GESR_REC_FLOATS);
+        order[first + i] = p;
+        write_rect(r[0], r[1], r[3], first + i, rect, ell);
+    }
 }
 
 // Longer views: four passes of 8-bit digits.  Bound by the launches and the ranking's
@@ -526,24 +580,6 @@ hipError_t depth_pass(const DepthPass& a, uint32_t V, uint32_t* scan_partials, h
     return hipGetLastError();
 }
 
-// ----------------------------------------------------------------- binning
-// The footprint ellipse of a projected record, q = (L00 dx + L10 dy)^2 +
-// (L11 dy)^2 <= Q, with Q its bound qmax widened by 2^-8 (so that float32
-// rounding can only widen what follows), and the two row-independent
-// quantities of its per-row extents: ym = sqrt(Q) / L11, the half-height, and
-// dyr = -L10 sqrt(Q) / (L11 sqrt(L10^2 + L11^2)), the dy of its rightmost
-// point (the leftmost is at -dyr).  Stored per item as (u, v, L00, L10),
-// (L11, Q, ym, dyr).  Square roots (sqrtf) and quotients (__fdiv_rn) are
-// correctly rounded, so the values are reproducible.
-__device__ __forceinline__ void row_ellipse(f32x4 a, f32x4 b, f32x4& e0, f32x4& e1) {
-    const float l10 = a.w, l11 = b.x;
-    const float Q = b.w + b.w * 0.00390625f;
-    const float sq = sqrtf(Q);
-    const float rr = sqrtf(l10 * l10 + l11 * l11);
-    e0 = a;
-    e1 = f32x4{l11, Q, __fdiv_rn(sq, l11), __fdiv_rn(-(l10 * sq), l11 * rr)};
-}
-
 // Columns of tile row ty that the ellipse (e0, e1) can reach: the x-extent of
 // the ellipse over the row's band [ty th, (ty + 1) th) (continuous, a superset
 // of its pixel centres), as tile columns clamped to [tx0, tx1]; tx0 | tx1 << 16
@@ -577,31 +613,6 @@ __device__ __forceinline__ uint32_t row_columns(const float4& e0, const float4& 
     return (uint32_t)c0 | ((uint32_t)c1 << 16);
 }
 
-// The rectangle is read from the pair's record (its fourth 16-byte word), so a
-// pair costs one gathered line: the ellipse terms sit in the same 64 bytes.
-// Culled pairs carry the rectangle (0xFFFFFFFF, 0), which no rectangle has
-// (its corners are tile indices below 2^16).  Bound by the gathered lines, which four
-// lanes take together: 48 million pairs GATHER_A us, 4 million GATHER_B.
-__global__ __launch_bounds__(256) void k_gather_rects(const uint32_t* order, const float* rec, uint64_t count,
-                                                      uint2* out, float4* ell) {
-    __shared__ f32x4 s_stage[4 * 256];
-    const uint64_t k = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    const uint32_t p = order[k < count ? k : count - 1];
-    QuadRecord q;
-    q.load(rec, quad_all(p), 0xFFFFFFFFu);
-    f32x4 r0, r1, r2, r3;
-    q.own(s_stage + (threadIdx.x & ~63u) * 4u, r0, r1, r2, r3);
-    if (k >= count) return;
-    const uint2 r = make_uint2(__float_as_uint(r3.x), __float_as_uint(r3.y));
-    out[k] = r;
-    if (ell != nullptr) {
-        f32x4 e0 = {0.f, 0.f, 0.f, 0.f}, e1 = e0;
-        if (r.x != 0xFFFFFFFFu) row_ellipse(r0, r1, e0, e1);
-        reinterpret_cast<f32x4*>(ell)[2 * k] = e0;
-        reinterpret_cast<f32x4*>(ell)[2 * k + 1] = e1;
-    }
-}
-
 // ------------------------------------------------- interval scatter (lists)
 // A tile's list is every pair whose footprint reaches it, in (depth, pair)
 // order: within its tile rectangle, a pair covers in each row one interval of
@@ -615,8 +626,9 @@ __global__ __launch_bounds__(256) void k_gather_rects(const uint32_t* order, con
 // Each level is split into segments: an ordered item list and a window of at
 // most IS_W consecutive buckets (level 1: a view's rows 128k..128k+127; level
 // 2: a row's tiles 128k..128k+127).  A segment's items are cut into chunks of
-// IS_CHUNK (two items per lane of 16 waves; wave w holds items 128 w .. 128 w +
-// 127, the second 64 in its second word).  Per-(chunk, bucket) counts are
+// at most IS_CHUNK (two items per lane of 16 waves; wave w holds items 128 w .. 128 w +
+// 127, the second 64 in its second word); at level 1, where every segment is a whole
+// view, of fewer where that gives too few chunks (is_chunk_items).  Per-(chunk, bucket) counts are
 // scanned over a segment's chunks, bucket totals over all buckets, and the
 // scatter writes a chunk's entries of bucket b from b's start + the chunk
 // prefix in chunk-item order, read off a (bucket, item) membership bitmap, so
@@ -638,7 +650,7 @@ struct Seg {
 // Segment s of a level: level 1 enumerates (view, row block), level 2
 // (view, row, column block), both view-major.
 template <int LEVEL>
-__device__ __forceinline__ Seg locate_segment(const IsArgs& a, uint32_t s) {
+__device__ __forceinline__ Seg locate_segment(const IsArgs& a, uint32_t s, uint32_t listed) {
     Seg g;
     uint32_t row_base = 0;
     for (int v = 0; v < a.cams.V; ++v) {
@@ -663,7 +675,6 @@ __device__ __forceinline__ Seg locate_segment(const IsArgs& a, uint32_t s) {
                 g.width = min(IS_W, w.tiles_x - g.lo_off);
                 g.bucket0 = w.tile_base + ty * (uint32_t)w.tiles_x + (uint32_t)g.lo_off;
                 const uint32_t r = row_base + ty;
-                const uint32_t listed = *a.items_listed;
                 const uint32_t b0 = a.row_start[r], b1 = b0 + a.row_count[r];
                 g.begin = b0 < listed ? b0 : listed;
                 g.end = b1 < listed ? b1 : listed;
@@ -678,6 +689,11 @@ __device__ __forceinline__ Seg locate_segment(const IsArgs& a, uint32_t s) {
     g.lo_off = 0;
     g.width = 0;
     return g;
+}
+
+template <int LEVEL>
+__device__ __forceinline__ Seg locate_segment(const IsArgs& a, uint32_t s) {
+    return locate_segment<LEVEL>(a, s, LEVEL == 2 ? *a.items_listed : 0u);
 }
 
 // Item idx of a segment: its value and its bucket interval [a0, a1] (empty when
@@ -748,30 +764,6 @@ __device__ __forceinline__ uint32_t chunk_segment(const uint32_t* chunk_off, uin
     return lo;
 }
 
-// First chunk of every segment (nseg + 1 entries) and the number of chunks, by one
-// block: one launch of 4.6 us instead of three of 4 (counts, end marker, scan).
-template <int LEVEL>
-__global__ __launch_bounds__(1024) void k_is_plan(IsArgs a) {
-    __shared__ uint32_t s_wave[17];
-    uint32_t run = 0;
-    for (uint32_t base = 0; base < a.nseg; base += 1024u) {
-        const uint32_t s = base + threadIdx.x;
-        uint32_t c = 0;
-        if (s < a.nseg) {
-            const Seg g = locate_segment<LEVEL>(a, s);
-            c = (g.end - g.begin + IS_CHUNK - 1) / IS_CHUNK;
-        }
-        uint32_t tot;
-        const uint32_t ex = run + block_exclusive_scan(c, s_wave, &tot);
-        if (s < a.nseg) a.chunk_off[s] = ex;
-        run += tot;
-    }
-    if (threadIdx.x == 0) {
-        a.chunk_off[a.nseg] = run;
-        *a.chunk_total = run;
-    }
-}
-
 // Inclusive prefix over the IS_W entries row[0..IS_W) by one wave (two per
 // lane), for entries in [-OFF, 2^BITS / 2 - OFF): the lane sums (offset to be
 // non-negative) are prefixed by one ballot per bit (no cross-lane shuffles).
@@ -827,18 +819,23 @@ __global__ __launch_bounds__(IS_THREADS) __attribute__((amdgpu_waves_per_eu(8)))
     const uint32_t item0 = wave * (64 * IS_IPL) + lane;  // chunk-local index of this lane's first item
     // a contiguous share of the chunks per block: the segment is looked up once
     // and the next chunk's items are loaded while the current one is processed
-    const uint32_t total = min<uint64_t>(*a.chunk_total, a.mat_chunks);
+    const uint32_t total = LEVEL == 1 ? a.nseg * a.seg_chunks : min<uint64_t>(*a.chunk_total, a.mat_chunks);
+    const uint32_t items = LEVEL == 1 ? a.chunk_items : (uint32_t)IS_CHUNK;
     const uint32_t per = (total + gridDim.x - 1) / gridDim.x;
     const uint32_t cbeg = blockIdx.x * per, cend = min(cbeg + per, total);
     if (cbeg >= cend) return;
-    uint32_t s = chunk_segment(a.chunk_off, a.nseg, cbeg);
-    uint32_t s_first = a.chunk_off[s], s_next = a.chunk_off[s + 1];
+    // end of the items of the chunk in which this lane's first item is idx
+    auto chunk_end = [&](uint32_t idx, uint32_t seg_end) { return LEVEL == 1 ? min(seg_end, idx - item0 + items) : seg_end; };
+    uint32_t s = LEVEL == 1 ? cbeg / a.seg_chunks : chunk_segment(a.chunk_off, a.nseg, cbeg);
+    uint32_t s_first = LEVEL == 1 ? s * a.seg_chunks : a.chunk_off[s];
+    uint32_t s_next = LEVEL == 1 ? s_first + a.seg_chunks : a.chunk_off[s + 1];
     Seg g = locate_segment<LEVEL>(a, s);
-    uint32_t idx = g.begin + (cbeg - s_first) * IS_CHUNK + item0;
+    uint32_t idx = g.begin + (cbeg - s_first) * items + item0;
     uint32_t p[IS_IPL], cols[IS_IPL];
     int a0[IS_IPL], a1[IS_IPL];
 #pragma unroll
-    for (int u = 0; u < IS_IPL; ++u) load_item<LEVEL>(a, idx + 64 * u, g.end, p[u], a0[u], a1[u], cols[u]);
+    for (int u = 0; u < IS_IPL; ++u)
+        load_item<LEVEL>(a, idx + 64 * u, chunk_end(idx, g.end), p[u], a0[u], a1[u], cols[u]);
     for (uint32_t cg = cbeg; cg < cend;) {
         // bucket bases of this chunk (scatter) are independent of the LDS work below
         uint32_t gb = 0;
@@ -853,7 +850,7 @@ __global__ __launch_bounds__(IS_THREADS) __attribute__((amdgpu_waves_per_eu(8)))
             any[u] = lo[u] <= hi[u];
         }
         const bool same = cg + 1 < cend && cg + 1 < s_next;
-        const uint32_t idx_n = idx + IS_CHUNK;
+        const uint32_t idx_n = idx + items;
         // the next chunk's items are loaded now, except by the level-1 scatter,
         // whose gathers in the copy-out need the registers (it loads them last)
         constexpr bool EARLY = !(LEVEL == 1 && MODE == 1);
@@ -862,7 +859,8 @@ __global__ __launch_bounds__(IS_THREADS) __attribute__((amdgpu_waves_per_eu(8)))
         if (EARLY) {
 #pragma unroll
             for (int u = 0; u < IS_IPL; ++u)
-                load_item<LEVEL>(a, idx_n + 64 * u, same ? g.end : 0u, p_n[u], a0_n[u], a1_n[u], cols_n[u]);
+                load_item<LEVEL>(a, idx_n + 64 * u, same ? chunk_end(idx_n, g.end) : 0u, p_n[u], a0_n[u], a1_n[u],
+                                 cols_n[u]);
         }
         if constexpr (MODE == 0) {
             for (int j = threadIdx.x; j < IS_WAVES * (IS_W + 1); j += IS_THREADS) (&s_cnt[0][0])[j] = 0;
@@ -1040,52 +1038,107 @@ __global__ __launch_bounds__(IS_THREADS) __attribute__((amdgpu_waves_per_eu(8)))
                 }
             } else {
 #pragma unroll
-                for (int u = 0; u < IS_IPL; ++u) load_item<LEVEL>(a, idx + 64 * u, g.end, p[u], a0[u], a1[u], cols[u]);
+                for (int u = 0; u < IS_IPL; ++u)
+                    load_item<LEVEL>(a, idx + 64 * u, chunk_end(idx, g.end), p[u], a0[u], a1[u], cols[u]);
             }
         } else {
             while (cg >= s_next) {
                 ++s;
                 s_first = s_next;
-                s_next = a.chunk_off[s + 1];
+                s_next = LEVEL == 1 ? s_first + a.seg_chunks : a.chunk_off[s + 1];
             }
             g = locate_segment<LEVEL>(a, s);
-            idx = g.begin + (cg - s_first) * IS_CHUNK + item0;
+            idx = g.begin + (cg - s_first) * items + item0;
 #pragma unroll
-            for (int u = 0; u < IS_IPL; ++u) load_item<LEVEL>(a, idx + 64 * u, g.end, p[u], a0[u], a1[u], cols[u]);
+            for (int u = 0; u < IS_IPL; ++u)
+                load_item<LEVEL>(a, idx + 64 * u, chunk_end(idx, g.end), p[u], a0[u], a1[u], cols[u]);
         }
     }
 }
 
 // Per (segment, bucket): exclusive scan of the chunk counts over the
 // segment's chunks (in place) and the bucket total.  Eight threads per bucket
-// each take a contiguous share of the chunks.
+// each take a contiguous share of the chunks, eight counts in flight (16 segments of
+// 1,465 chunks: 41 us, one count at a time 108).
 constexpr int IS_PARTS = 8;
 
 template <int LEVEL>
-__global__ __launch_bounds__(IS_W * IS_PARTS) void k_is_prefix(IsArgs a) {
-    __shared__ uint32_t s_part[IS_PARTS][IS_W];
-    const uint32_t s = blockIdx.x, b = threadIdx.x % IS_W, part = threadIdx.x / IS_W;
+__device__ __forceinline__ void segment_prefix(const IsArgs& a, uint32_t s, uint32_t (*s_part)[IS_W]) {
+    const uint32_t b = threadIdx.x % IS_W, part = threadIdx.x / IS_W;
     const Seg g = locate_segment<LEVEL>(a, s);
-    const uint32_t c0 = a.chunk_off[s];
-    const uint32_t c1 = min<uint64_t>(a.chunk_off[s + 1], a.mat_chunks);
+    const uint32_t c0 = LEVEL == 1 ? s * a.seg_chunks : a.chunk_off[s];
+    const uint32_t c1 = LEVEL == 1 ? c0 + a.seg_chunks : min<uint64_t>(a.chunk_off[s + 1], a.mat_chunks);
     const uint32_t nch = c1 > c0 ? c1 - c0 : 0u;
     const uint32_t per = (nch + IS_PARTS - 1) / IS_PARTS;
     const uint32_t r0 = c0 + min(part * per, nch), r1 = c0 + min((part + 1) * per, nch);
     const bool live = (int)b < g.width;
     uint32_t sum = 0;
+    // eight counts in flight
+    uint32_t x[8];
     if (live)
-        for (uint32_t c = r0; c < r1; ++c) sum += a.mat[(uint64_t)c * IS_W + b];
+        for (uint32_t c = r0; c < r1; c += 8u) {
+#pragma unroll
+            for (uint32_t k = 0; k < 8u; ++k) x[k] = c + k < r1 ? a.mat[(uint64_t)(c + k) * IS_W + b] : 0u;
+#pragma unroll
+            for (uint32_t k = 0; k < 8u; ++k) sum += x[k];
+        }
     s_part[part][b] = sum;
     __syncthreads();
     if (!live) return;
     uint32_t acc = 0;
     for (uint32_t q = 0; q < part; ++q) acc += s_part[q][b];
-    for (uint32_t c = r0; c < r1; ++c) {
-        const uint32_t x = a.mat[(uint64_t)c * IS_W + b];
-        a.mat[(uint64_t)c * IS_W + b] = acc;
-        acc += x;
+    for (uint32_t c = r0; c < r1; c += 8u) {
+#pragma unroll
+        for (uint32_t k = 0; k < 8u; ++k) x[k] = c + k < r1 ? a.mat[(uint64_t)(c + k) * IS_W + b] : 0u;
+#pragma unroll
+        for (uint32_t k = 0; k < 8u; ++k) {
+            if (c + k < r1) a.mat[(uint64_t)(c + k) * IS_W + b] = acc;
+            acc += x[k];
+        }
     }
     if (part == IS_PARTS - 1) a.bucket_count[g.bucket0 + b] = acc;
+}
+template <int LEVEL>
+__global__ __launch_bounds__(IS_W * IS_PARTS) void k_is_prefix(IsArgs a) {
+    __shared__ uint32_t s_part[IS_PARTS][IS_W];
+    segment_prefix<LEVEL>(a, blockIdx.x, s_part);
+}
+
+// Between the levels, by one block: with few level-1 segments their prefixes, the row
+// lists' starts (a scan of the counts; the entries and their capacity words to
+// `counters`), and the first chunk of every level-2 segment (nseg + 1 entries) with the
+// number of chunks.  One launch of 5.6 us on 2,000 splats, where four took 18; with more
+// than ROWS_SEGMENTS segments a block each does the prefixes (a segment of 391 chunks
+// takes 7 us here, and a launch 4.5).
+constexpr uint32_t ROWS_SEGMENTS = 2;
+__global__ __launch_bounds__(1024) void k_is_rows(IsArgs a, uint32_t prefix_segs, uint32_t rows, uint32_t* counters) {
+    __shared__ uint32_t s_tile[4096 + 128], s_wave[17], s_part[IS_PARTS][IS_W];
+    static_assert(IS_PARTS * IS_W == 1024, "one block does a segment's prefix");
+    for (uint32_t s = 0; s < prefix_segs; ++s) {
+        segment_prefix<1>(a, s, s_part);
+        __syncthreads();
+    }
+    const uint32_t m = scan_by_block(a.bucket_count, a.bucket_start, rows, s_tile, s_wave);
+    if (threadIdx.x == 0) write_total(counters, m, a.out_cap);
+    __syncthreads();
+    const uint32_t listed = (uint32_t)min<uint64_t>(m, a.out_cap);
+    uint32_t run = 0;
+    for (uint32_t base = 0; base < a.nseg; base += 1024u) {
+        const uint32_t s = base + threadIdx.x;
+        uint32_t c = 0;
+        if (s < a.nseg) {
+            const Seg g = locate_segment<2>(a, s, listed);
+            c = (g.end - g.begin + IS_CHUNK - 1) / IS_CHUNK;
+        }
+        uint32_t tot;
+        const uint32_t ex = run + block_exclusive_scan(c, s_wave, &tot);
+        if (s < a.nseg) a.chunk_off[s] = ex;
+        run += tot;
+    }
+    if (threadIdx.x == 0) {
+        a.chunk_off[a.nseg] = run;
+        *a.chunk_total = run;
+    }
 }
 
 // ranges[t] = [start, start + count), clamped to the instances actually listed
@@ -1209,15 +1262,15 @@ hipError_t radix_sort(const uint32_t* keys_in, const uint32_t* vals_in, uint64_t
     return hipSuccess;
 }
 
-hipError_t depth_sort(const uint32_t* keys, uint32_t n, uint32_t V, const SortBuffers& b, uint32_t** order,
-                      hipStream_t stream) {
+hipError_t depth_sort(const uint32_t* keys, uint32_t n, uint32_t V, const SortBuffers& b, const float* rec,
+                      uint32_t** order, uint2* rect, float4* ell, hipStream_t stream) {
     *order = b.vals_b;
     if (n == 0 || V == 0) return hipSuccess;
-    if (n <= 4096u) {
+    if (n <= DEPTH_SORT_SMALL) {
         const dim3 grid(V), block(1024);
-        if (n <= 1024u) hipLaunchKernelGGL(k_depth_sort_small<1>, grid, block, 0, stream, keys, n, b.vals_b);
-        else if (n <= 2048u) hipLaunchKernelGGL(k_depth_sort_small<2>, grid, block, 0, stream, keys, n, b.vals_b);
-        else hipLaunchKernelGGL(k_depth_sort_small<4>, grid, block, 0, stream, keys, n, b.vals_b);
+        if (n <= 1024u) hipLaunchKernelGGL(k_depth_sort_small<1>, grid, block, 0, stream, keys, n, b.vals_b, rec, rect, ell);
+        else if (n <= 2048u) hipLaunchKernelGGL(k_depth_sort_small<2>, grid, block, 0, stream, keys, n, b.vals_b, rec, rect, ell);
+        else hipLaunchKernelGGL(k_depth_sort_small<4>, grid, block, 0, stream, keys, n, b.vals_b, rec, rect, ell);
         return hipGetLastError();
     }
     // keys per block: as few as keep a view's rows of counts within what a block sums
@@ -1242,7 +1295,7 @@ hipError_t depth_sort(const uint32_t* keys, uint32_t n, uint32_t V, const SortBu
     }
     return hipSuccess;
 }
-uint64_t depth_sort_hist_words(uint64_t n, uint64_t V) { return n <= 4096u ? 0u : V * 256u * ((n + 1023) / 1024); }
+uint64_t depth_sort_hist_words(uint64_t n, uint64_t V) { return n <= DEPTH_SORT_SMALL ? 0u : V * 256u * ((n + 1023) / 1024); }
 
 hipError_t launch_gather_rects(const uint32_t* order, const float* rec, uint64_t count, uint2* out, float4* ell,
                                hipStream_t stream) {
@@ -1261,10 +1314,19 @@ uint32_t is_segments(const DevCams& cams, int level) {
     return s;
 }
 
+// Items of a level-1 chunk: 2,048, halved down to 256 while that leaves fewer than 256
+// chunks, one for each compute unit (100,000 pairs: 391 chunks are scattered in 18 us, 49 in 37).
+static uint32_t is_chunk_items(const DevCams& cams, int n) {
+    uint32_t items = IS_CHUNK;
+    while (items > 256u && (uint64_t)is_segments(cams, 1) * (((uint64_t)n + items - 1) / items) < 256u) items /= 2u;
+    return items;
+}
+
 uint64_t is_chunk_bound(const DevCams& cams, int level, int n, uint64_t level2_items) {
     uint64_t c = 0;
     if (level == 1) {
-        c = (uint64_t)is_segments(cams, 1) * (((uint64_t)n + IS_CHUNK - 1) / IS_CHUNK);
+        const uint64_t items = is_chunk_items(cams, n);
+        c = (uint64_t)is_segments(cams, 1) * (((uint64_t)n + items - 1) / items);
     } else {
         uint32_t nb_max = 1;
         for (int v = 0; v < cams.V; ++v) {
@@ -1278,25 +1340,42 @@ uint64_t is_chunk_bound(const DevCams& cams, int level, int n, uint64_t level2_i
 
 uint32_t is_window() { return IS_W; }
 
-hipError_t launch_interval_lists(IsArgs a, int level, hipStream_t stream) {
-    a.nseg = is_segments(a.cams, level);
-    if (a.nseg == 0) return hipSuccess;
-    const uint32_t grid = (uint32_t)(a.mat_chunks < 1024 ? a.mat_chunks : 1024);
-    auto plan_k = level == 1 ? k_is_plan<1> : k_is_plan<2>;
-    hipLaunchKernelGGL(plan_k, dim3(1), dim3(1024), 0, stream, a);
-    auto count_k = level == 1 ? k_is_chunks<1, 0> : k_is_chunks<2, 0>;
-    hipLaunchKernelGGL(count_k, dim3(grid), dim3(IS_THREADS), 0, stream, a);
-    auto prefix_k = level == 1 ? k_is_prefix<1> : k_is_prefix<2>;
-    hipLaunchKernelGGL(prefix_k, dim3(a.nseg), dim3(IS_W * IS_PARTS), 0, stream, a);
+void plan_interval_levels(IsArgs* l1, IsArgs* l2) {
+    l1->nseg = is_segments(l1->cams, 1);
+    l2->nseg = is_segments(l2->cams, 2);
+    l1->chunk_items = is_chunk_items(l1->cams, l1->n);
+    l1->seg_chunks = ((uint32_t)l1->n + l1->chunk_items - 1) / l1->chunk_items;
+}
+
+static dim3 is_grid(const IsArgs& a, int level) {
+    const uint64_t chunks = level == 1 ? (uint64_t)a.nseg * a.seg_chunks : a.mat_chunks;
+    return dim3((uint32_t)(chunks < 1024 ? chunks : 1024));
+}
+
+hipError_t launch_row_lists(const IsArgs& l1, const IsArgs& l2, uint32_t rows, uint32_t* counters, hipStream_t stream) {
+    const bool few = l1.nseg <= ROWS_SEGMENTS;
+    if (l1.seg_chunks != 0u)
+        hipLaunchKernelGGL((k_is_chunks<1, 0>), is_grid(l1, 1), dim3(IS_THREADS), 0, stream, l1);
+    if (!few) hipLaunchKernelGGL(k_is_prefix<1>, dim3(l1.nseg), dim3(IS_W * IS_PARTS), 0, stream, l1);
+    // level 2's segments, with level 1's chunks and buckets
+    IsArgs a = l2;
+    a.seg_chunks = l1.seg_chunks;
+    a.bucket_count = l1.bucket_count;
+    a.bucket_start = l1.bucket_start;
+    hipLaunchKernelGGL(k_is_rows, dim3(1), dim3(1024), 0, stream, a, few ? l1.nseg : 0u, rows, counters);
+    if (l1.seg_chunks != 0u)
+        hipLaunchKernelGGL((k_is_chunks<1, 1>), is_grid(l1, 1), dim3(IS_THREADS), 0, stream, l1);
     return hipGetLastError();
 }
 
-hipError_t launch_interval_scatter(IsArgs a, int level, hipStream_t stream) {
-    a.nseg = is_segments(a.cams, level);
-    if (a.nseg == 0) return hipSuccess;
-    const uint32_t grid = (uint32_t)(a.mat_chunks < 1024 ? a.mat_chunks : 1024);
-    auto scatter_k = level == 1 ? k_is_chunks<1, 1> : k_is_chunks<2, 1>;
-    hipLaunchKernelGGL(scatter_k, dim3(grid), dim3(IS_THREADS), 0, stream, a);
+hipError_t launch_tile_counts(const IsArgs& l2, hipStream_t stream) {
+    hipLaunchKernelGGL((k_is_chunks<2, 0>), is_grid(l2, 2), dim3(IS_THREADS), 0, stream, l2);
+    hipLaunchKernelGGL(k_is_prefix<2>, dim3(l2.nseg), dim3(IS_W * IS_PARTS), 0, stream, l2);
+    return hipGetLastError();
+}
+
+hipError_t launch_tile_scatter(const IsArgs& l2, hipStream_t stream) {
+    hipLaunchKernelGGL((k_is_chunks<2, 1>), is_grid(l2, 2), dim3(IS_THREADS), 0, stream, l2);
     return hipGetLastError();
 }
 

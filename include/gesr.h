@@ -87,13 +87,14 @@ typedef struct {
     int32_t tile_w, tile_h; /* supported: 16x16, 32x16, 32x32, 8x8 */
     int32_t batch;          /* splats staged per LDS round in the renderers: 0 (= 64), 32,
                                64 or 128 (128 only for the four-wave 16x16 and the 32x16
-                               backward; the 16x16 forward without counts always stages
-                               64; other kernels clamp to what their tile holds) */
+                               backward; the 16x16 forward without counts and the
+                               variant-0 backward always stage 64; other kernels clamp to what their tile holds) */
     int32_t radix_bits;     /* digit width of the (view, depth) sort of the (view, splat) pairs, 4..8 */
     int32_t variant;        /* 16x16 renderers: 0 = one wave per tile (4 px per lane), the
-                               forward's longest-running tiles (all of them where tiles
-                               are few) by four waves; 1 = one workgroup of four waves
-                               per tile.  Images do not depend on it */
+                               longest-running tiles (all of them where tiles are few)
+                               by four waves, the backward's by eight where they are
+                               fewer still; 1 = one workgroup of four waves per tile.
+                               Images do not depend on it */
     int32_t reserved[3];
 } gesr_settings;
 

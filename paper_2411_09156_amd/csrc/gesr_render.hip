@@ -998,6 +998,184 @@ __device__ __forceinline__ void bwd_split_tile(const RenderArgs& a, uint32_t t, 
     }
 }
 
+// The same tile by eight waves: the first four do phase 1 of a round while the other
+// four do phase 2 of the round before (terms, records and sums are held twice), so a
+// round lasts as long as the longer phase.  Bound by the phases' serial chains: 112 us
+// on 64 tiles (2,000 splats, 128x128), 147 with four waves and the phases in turn, 124
+// with the falloffs of four records side by side (most are off).
+template <bool EXT>
+struct BwdPipe {
+    BwdStage<EXT> s[2];
+    float4 v0[2][4][4][64];  // as BwdSplit, of even and odd rounds
+    float2 v1[2][4][4][64];
+    uint64_t live[2][4];
+    uint32_t maxnc[4];
+};
+
+template <bool EXT>
+__global__ __launch_bounds__(512) void k_render_bwd16_pipe(RenderArgs a) {
+    constexpr int NP = GESR_PARTIAL_FLOATS;
+    constexpr uint32_t R = 4, GRP = 2;                // as bwd_split_tile
+    constexpr uint32_t kRounds = kBwdBatch / R;       // rounds of a full batch
+    __shared__ BwdPipe<EXT> S;
+    const uint32_t t = a.worklist[blockIdx.x];
+    const uint32_t w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = w8 & 3u;
+    const bool first = w8 < 4u;  // phase 1
+    const DevSettings& st = a.st;
+    const float amax = st.alpha_max, nk = in_vgpr(st.neg_kappa_log2e);
+    const float c2 = -0.5f * kLn2 * st.kappa;
+    const uint32_t lane = __lane_id();
+    const TilePlace tp = place_tile(a, t);
+    const uint32_t r0 = tp.r0;
+    const float pxb = (float)(tp.tx * 16 + (lane & 7)) + 0.5f, pyb = (float)(tp.ty * 16 + (lane >> 3)) + 0.5f;
+    const float qx = (float)(tp.tx * 16 + (wave & 1) * 8) + 0.5f, qy = (float)(tp.ty * 16 + (wave >> 1) * 8) + 0.5f;
+    const float px = pxb + (float)((wave & 1) * 8), py = pyb + (float)((wave >> 1) * 8);
+    PixelUp up[4], mine{};
+    PixelAdjoint pa = behind_all(st, 0.f);
+    uint32_t nc = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int x = (int)tp.tx * 16 + (q & 1) * 8 + (int)(lane & 7);
+        const int y = (int)tp.ty * 16 + (q >> 1) * 8 + (int)(lane >> 3);
+        up[q] = PixelUp{};
+        if (x < tp.w->W && y < tp.w->H && (!first || q == (int)wave)) {
+            const uint32_t local = (uint32_t)y * (uint32_t)tp.w->W + (uint32_t)x;
+            const uint32_t pix = tp.w->pix_base + local;
+            up[q] = load_up<EXT>(a, pix, 3u * tp.w->pix_base + local, tp.ch);
+            if (first) {
+                pa.T = a.final_T[pix];
+                nc = a.n_contrib[pix];
+                mine = up[q];
+            }
+        }
+    }
+    const uint32_t wmax = __builtin_amdgcn_readfirstlane(wave_max_u32(nc));  // this quadrant's deepest position
+    if (first && lane == 0) S.maxnc[wave] = wmax;
+    __syncthreads();
+    const uint32_t total = __builtin_amdgcn_readfirstlane(max(max(S.maxnc[0], S.maxnc[1]), max(S.maxnc[2], S.maxnc[3])));
+    const int slot = lane < 16 ? wave_sum10_slot(lane) : NP;
+    const uint32_t top = r0 + total;  // positions top - 1 .. r0, batch k from top - 64 k
+
+    // the first wave stages: a batch's records are stored while the one before is
+    // taken, loaded while the one before that is, its splat ids before that
+    BwdRecord<EXT> r;
+    uint32_t vi = 0;
+    auto value_at = [&](uint32_t back) { return back + lane < total ? a.val_sorted[top - 1u - back - lane] : 0u; };
+    if (w8 == 0) {
+        vi = value_at(0);
+        if (lane < total) {
+            r.load(a, vi);
+            r.store(a, S.s[0], lane, tp.tx, tp.ty);
+        }
+        vi = value_at(kBwdBatch);
+        if (kBwdBatch + lane < total) r.load(a, vi);
+        vi = value_at(2 * kBwdBatch);
+    }
+    __syncthreads();
+    const uint32_t rounds = (total + R - 1) / R;
+    uint64_t live = 0, live_of[4] = {0, 0, 0, 0};
+    for (uint32_t i = 0; i <= rounds; ++i) {
+        if (first) {
+            const uint32_t k = i / kRounds, b = i % kRounds * R;
+            BwdStage<EXT>& s = S.s[k & 1];
+            const uint32_t hi = top - k * kBwdBatch;  // not used past the last round
+            if (i < rounds) {
+                if (b == 0) {
+                    bool can = false;
+                    if (lane < hi - r0 && hi - 1u - lane - r0 < wmax) {
+                        const float4 la = s.a[lane];
+                        can = !quad_misses(la, s.b[lane], qx - la.x, (qx + 7.0f) - la.x, qy - la.y, (qy + 7.0f) - la.y);
+                    }
+                    live = __ballot(can);
+                    if (lane == 0) S.live[k & 1][wave] = live;
+                }
+                uint32_t m = (uint32_t)(live >> b) & ((1u << R) - 1u);
+                while (m != 0u) {
+                    uint32_t e[GRP];
+                    bool have[GRP];
+#pragma unroll
+                    for (uint32_t u = 0; u < GRP; ++u) {  // past the last record: that one again, off
+                        have[u] = m != 0u;
+                        e[u] = have[u] ? (uint32_t)__builtin_ctz(m) : e[u > 0 ? u - 1 : 0];
+                        m = have[u] ? m & (m - 1) : 0u;
+                    }
+                    Fragment f[GRP];
+                    bool on[GRP];
+#pragma unroll
+                    for (uint32_t u = 0; u < GRP; ++u) {
+                        const float4 rb = s.b[b + e[u]];
+                        const float qq = ges_q(s.a[b + e[u]], rb.x, px, py, f[u]);
+                        on[u] = (int)(hi - 1u - (b + e[u]) - r0 < nc) & (int)!(qq > rb.w) & (int)have[u];
+                        // q = 1 where the fragment is not the pixel's: its terms are exact zeros
+                        ges_alpha(on[u] ? qq : 1.0f, rb.z, rb.y, nk, amax, f[u]);
+                    }
+#pragma unroll
+                    for (uint32_t u = 0; u < GRP; ++u) {
+                        const float4 rc = s.c[b + e[u]];
+                        float aT, dl;
+                        pixel_step<EXT, false>(f[u], on[u], rc, EXT ? s.z[b + e[u]] : 0.0f, st, mine, pa, aT, dl);
+                        if (have[u]) {
+                            const FragmentTerms v = fragment_terms(f[u], rc.w, aT, dl);
+                            S.v0[i & 1][e[u]][wave][lane] = make_float4(v.aT, v.dl, v.G, v.xl);
+                            S.v1[i & 1][e[u]][wave][lane] = make_float2(v.tq, v.wq);
+                        }
+                    }
+                }
+            }
+            // the stage's last use, by batch k - 1, ended with the step before
+            if (w8 == 0 && b == 2u * R && (k + 1u) * kBwdBatch < total) {
+                if ((k + 1u) * kBwdBatch + lane < total) r.store(a, S.s[(k + 1u) & 1u], lane, tp.tx, tp.ty);
+                if ((k + 2u) * kBwdBatch + lane < total) r.load(a, vi);
+                vi = value_at((k + 3u) * kBwdBatch);
+            }
+        } else {
+            if (i > 0u) {
+                const uint32_t p = i - 1u, k = p / kRounds, b = p % kRounds * R;
+                BwdStage<EXT>& s = S.s[k & 1];
+                if (b == 0) {
+                    const uint64_t own = S.live[k & 1][lane & 3];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) live_of[q] = read_lane(own, q);
+                }
+                const uint32_t j = b + wave;
+                if (k * kBwdBatch + j >= total) {
+                } else if (((live_of[0] | live_of[1] | live_of[2] | live_of[3]) >> j & 1u) == 0u) {
+                    if ((int)lane < (EXT ? NP + 1 : NP)) s.red[j][lane] = 0.f;
+                } else {
+                    const float2 uv = make_float2(s.a[j].x, s.a[j].y);
+                    float gr[NP], gz = 0.0f;
+                    // all reads in flight together (a quadrant without the record holds stale terms: not added)
+                    float4 v0[4];
+                    float2 v1[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        v0[q] = S.v0[p & 1][wave][q][lane];
+                        v1[q] = S.v1[p & 1][wave][q][lane];
+                    }
+#pragma unroll
+                    for (int n = 0; n < NP; n += 2) opaque_zero2(gr[n], gr[n + 1]);
+                    if (EXT) gz = opaque_zero();
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        if (!(live_of[q] >> j & 1u)) continue;
+                        add_terms<EXT>(FragmentTerms{v0[q].x, v0[q].y, v0[q].z, v0[q].w, v1[q].x, v1[q].y},
+                                       (pxb + (float)((q & 1) * 8)) - uv.x, (pyb + (float)((q >> 1) * 8)) - uv.y, c2,
+                                       up[q], gr, gz);
+                    }
+                    reduce_record(s, j, gr, gz, lane, slot);
+                }
+            }
+            // batch k - 1's last round was summed in the step before
+            if (w8 == 4 && i % kRounds == 1u && i > kRounds) write_batch(a, S.s[(i / kRounds - 1u) & 1u], lane, kBwdBatch);
+        }
+        __syncthreads();
+    }
+    if (w8 == 4 && rounds != 0u) {
+        const uint32_t k = (rounds - 1u) / kRounds;
+        write_batch(a, S.s[k & 1], lane, total - k * kBwdBatch);
+    }
+}
+
 // Adjoint of 16x16 tiles: the first a.n_split workgroups take one tile each, the
 // others four (a tile per wave).
 template <bool EXT>
@@ -1050,15 +1228,19 @@ hipError_t bwd_shape(const RenderArgs& a, hipStream_t s) {
 // from LDS for 64 pixels instead of 256.
 uint32_t fwd_split_tiles(uint32_t n_items) { return n_items <= 8192u ? n_items : 1024u; }
 
-// The 16x16 adjoint's tiles with four waves each: all of them up to 4,096 (one wave
+// The 16x16 adjoint's tiles with eight waves each: all of them up to 2,048, where four
+// would leave SIMDs idle or with one serial chain each (147 -> 112 us on 64 tiles, 236
+// -> 174 on 1,024, 214 -> 207 on 1,936; 2,500 tiles would take 262 us instead of 234,
+// 3,024 321 instead of 231).  With four waves each: all of them up to 4,096 (one wave
 // takes 300 ns per list position and the chip's wave slots would be filled once or
-// less: 270 -> 147 us on 64 tiles, 360 -> 218 us on 3,024; 6,048 tiles would take 475
-// us instead of 410), the worklist's first 256 up to 32,768 (2,000 -> 1,826 us on
-// 24,842 tiles of views at 1/8 .. 1 of 1600x1064, where the longest list alone took
-// the whole time, 510 -> 346 us on 8,487, 403 against 410 us on 6,048).  Above that a
-// wave slot takes six tiles or more and no list sets the end: one-wave
-// workgroups, whose slots free up singly, take 1,790 us on 33,948 tiles and 5.55 ms
-// on 130,560 against 1,890 us and 5.77 ms with four waves to a workgroup.
+// less: 360 -> 218 us on 3,024; 6,048 tiles would take 475 us instead of 410), the
+// worklist's first 256 up to 32,768 (2,000 -> 1,826 us on 24,842 tiles of views at 1/8
+// .. 1 of 1600x1064, where the longest list alone took the whole time, 510 -> 346 us on
+// 8,487, 403 against 410 us on 6,048).  Above that a wave slot takes six tiles or more
+// and no list sets the end: one-wave workgroups, whose slots free up singly, take 1,790
+// us on 33,948 tiles and 5.55 ms on 130,560 against 1,890 us and 5.77 ms with four
+// waves to a workgroup.
+constexpr uint32_t kBwdPipeMax = 2048u;
 constexpr uint32_t kBwdMixedMax = 32768u;
 uint32_t bwd_split_tiles(uint32_t n_items) { return n_items <= 4096u ? n_items : 256u; }
 
@@ -1102,6 +1284,12 @@ hipError_t launch_render_bwd(const RenderArgs& a, int tw, int th, int batch, hip
         if (a.st.variant == 1)  // one workgroup of 4 waves per tile
             return batch >= 128 ? bwd_shape<16, 16, 128>(a, s) : bwd_shape<16, 16, 64>(a, s);
         const bool ext = a.dL_ddepth || a.dL_dalpha;
+        if (a.n_items <= kBwdPipeMax) {
+            const dim3 grid(a.n_items), block(512);
+            if (ext) hipLaunchKernelGGL((k_render_bwd16_pipe<true>), grid, block, 0, s, a);
+            else hipLaunchKernelGGL((k_render_bwd16_pipe<false>), grid, block, 0, s, a);
+            return hipGetLastError();
+        }
         if (a.n_items > kBwdMixedMax) {
             const dim3 grid(a.n_items), block(64);
             if (ext) hipLaunchKernelGGL((k_render_bwd16_wave<true>), grid, block, 0, s, a);

@@ -2,6 +2,7 @@
 
 The forward takes a tile with four waves (one 8x8 quadrant each, only the
 records that can reach it) or with one; the counting forward always with one.
+The adjoint takes a tile with eight waves, four or one.
 Tile counts on both sides of the dispatch rules, ragged and one-pixel views,
 thin splats (the quadrant's footprint test at its most sheared), beta below 2,
 lists that end mid-batch and pixels that terminate."""
@@ -79,9 +80,10 @@ def test_forward_paths_agree_bitwise(name, channels):
 @pytest.mark.parametrize("name", [k for k in SCENES if k != "wide"])
 @pytest.mark.parametrize("channels", [False, True])
 def test_adjoint_paths_agree_bitwise(name, channels):
-    """The adjoint takes every tile with four waves where tiles are few, the
-    worklist's first 256 up to 32,768 tiles and none above: a view's screen-space
-    gradients are the same alone and beside a view that brings the batch to each."""
+    """The adjoint takes every tile with eight waves up to 2,048 tiles, with four up to
+    4,096, the worklist's first 256 with four up to 32,768 and none above: a view's
+    screen-space gradients are the same alone and beside a view that brings the batch
+    to each."""
     import copy
 
     import torch
@@ -92,7 +94,7 @@ def test_adjoint_paths_agree_bitwise(name, channels):
     P = scene.n_pixels
     up = [torch.randn(k, generator=gen, device="cuda") for k in (3 * P, P, P)]
     ref, tiles = None, []
-    for pad in (None, (1500, 1100), (4200, 2200)):
+    for pad in (None, (768, 720), (1500, 1100), (4200, 2200)):
         s = copy.copy(scene)
         s.cameras = list(scene.cameras) + ([gi.look_at((0.0, 0.0, -4.0), width=pad[0], height=pad[1])] if pad else [])
         rast = _rast(s)
@@ -113,7 +115,9 @@ def test_adjoint_paths_agree_bitwise(name, channels):
             ref = g
             assert np.abs(g).max() > 0
         np.testing.assert_array_equal(g, ref, err_msg=str(pad))
-    assert 4096 < tiles[1] <= 32768 < tiles[2]
+    assert 2048 < tiles[1] and 4096 < tiles[2] <= 32768 < tiles[3]
+    if tiles[0] <= 1900:
+        assert tiles[1] <= 4096
 
 
 def _giant():

@@ -225,8 +225,9 @@ gesr_status gesr_project(gesr_ctx* ctx, const gesr_splats* splats, const gesr_ca
  * entries into the tiles of their columns) without sorting instances.
  * Instance slots (inst_base, the backward's partials) keep the rectangle
  * layout.  With GESR_BIN_SYNC the call
- * synchronises `stream` once after counting; if M > m_cap it returns
- * GESR_ERR_CAPACITY with *m_out = M and leaves the sorted lists undefined.
+ * waits once for the count (the lists are enqueued meanwhile); if M > m_cap it
+ * returns GESR_ERR_CAPACITY with *m_out = M, the stream drained, and leaves the
+ * sorted lists undefined.
  * Without it the call never synchronises (capturable in a HIP graph): lists
  * are truncated to m_cap and counters[1] is set.  *m_out (nullable) receives
  * M only with GESR_BIN_SYNC. */

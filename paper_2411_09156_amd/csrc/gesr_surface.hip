@@ -12,12 +12,11 @@
 // linear interpolation, and the normal is -grad d / |grad d| (the direction of
 // grad f for the SDF of Eq. 11).
 //
-// Eight lanes per ray (eight rays per wave) stride over the tile list.  Along the ray each
-// candidate's Mahalanobis vector is affine in the ray parameter, y(s) = a + s b
-// (a = M^-1 (x0 - mu), b = M^-1 w, s = t - t0), so a sample costs two
-// multiply-adds plus the falloff.  Each lane keeps its partial density of every
-// sample in registers; the partials meet in LDS and are summed per sample in
-// lane order (fixed order, reproducible).
+// Four waves take eight rays, 32 lanes a ray, which share the tile list's entries.
+// Along the ray each candidate's Mahalanobis vector is affine in the ray parameter,
+// y(s) = a + s b (a = M^-1 (x0 - mu), b = M^-1 w, s = t - t0), so a sample costs two
+// multiply-adds plus the falloff.  Partial densities meet in LDS and are summed per
+// sample in a fixed order (reproducible).
 
 #include "gesr_device.h"
 #include "gesr_kernels.h"
@@ -161,7 +160,6 @@ __device__ __forceinline__ float ray_sum(float x) {
     for (int m = kLanesPerRay / 2; m >= 1; m >>= 1) x += __shfl_xor(x, m * kRaysPerWave, 64);
     return x;
 }
-
 
 // Four waves share a group of eight rays.  Pass 1 (an exact maximum) takes every
 // fourth set of list entries per wave; in pass 2 each wave takes a quarter of the

@@ -147,3 +147,27 @@ def test_gradients_with_and_without_all_rows(name):
     for k in out[0]:
         assert np.isfinite(out[0][k]).all(), k
         np.testing.assert_array_equal(out[0][k], out[1][k], err_msg=k)
+
+
+def test_sums_agree_on_both_sides_of_the_pair_count():
+    """Above 262,144 pairs a wave of the segmented sum looks 64 of them up, below 16:
+    a batch of three views (270,000 pairs) gives each view's rows as the view alone."""
+    import copy
+
+    import torch
+    rng = np.random.default_rng([402, 0])
+    cams = [gi.look_at((0.4 * i, 0.1, -4.0), width=w, height=h) for i, (w, h) in enumerate([(190, 150), (64, 48), (33, 90)])]
+    scene = gi._uniform_cube_scene("pairs", rng, 90_000, cams)
+    scene.scales[::9] *= 6.0  # pairs over hundreds of instance slots
+    sp = splats_of(scene)
+    outs = []
+    for views in ([0, 1, 2], [0], [1], [2]):
+        s = copy.copy(scene)
+        s.cameras = [cams[v] for v in views]
+        rast = _rast(s)
+        f = rast.forward(sp)
+        dL = torch.cat([torch.full((3 * cams[v].width * cams[v].height,), 0.1 * (v + 1), device="cuda") for v in views])
+        g = rast.render_bwd(sp, f["proj"], f["bins"], f["final_T"], f["n_contrib"], dL, want_grad2d=True)
+        outs.append(g["grad2d"][:len(views) * sp.n * 12].cpu().numpy())
+    assert np.abs(outs[0]).max() > 0
+    np.testing.assert_array_equal(outs[0], np.concatenate(outs[1:]))

@@ -628,7 +628,8 @@ __device__ __forceinline__ uint32_t row_columns(const float4& e0, const float4& 
 // 2: a row's tiles 128k..128k+127).  A segment's items are cut into chunks of
 // at most IS_CHUNK (two items per lane of 16 waves; wave w holds items 128 w .. 128 w +
 // 127, the second 64 in its second word); at level 1, where every segment is a whole
-// view, of fewer where that gives too few chunks (is_chunk_items).  Per-(chunk, bucket) counts are
+// view, of fewer where that gives too few chunks
+// (plan_interval_levels).  Per-(chunk, bucket) counts are
 // scanned over a segment's chunks, bucket totals over all buckets, and the
 // scatter writes a chunk's entries of bucket b from b's start + the chunk
 // prefix in chunk-item order, read off a (bucket, item) membership bitmap, so
@@ -1314,19 +1315,10 @@ uint32_t is_segments(const DevCams& cams, int level) {
     return s;
 }
 
-// Items of a level-1 chunk: 2,048, halved down to 256 while that leaves fewer than 256
-// chunks, one for each compute unit (100,000 pairs: 391 chunks are scattered in 18 us, 49 in 37).
-static uint32_t is_chunk_items(const DevCams& cams, int n) {
-    uint32_t items = IS_CHUNK;
-    while (items > 256u && (uint64_t)is_segments(cams, 1) * (((uint64_t)n + items - 1) / items) < 256u) items /= 2u;
-    return items;
-}
-
 uint64_t is_chunk_bound(const DevCams& cams, int level, int n, uint64_t level2_items) {
     uint64_t c = 0;
     if (level == 1) {
-        const uint64_t items = is_chunk_items(cams, n);
-        c = (uint64_t)is_segments(cams, 1) * (((uint64_t)n + items - 1) / items);
+        c = (uint64_t)is_segments(cams, 1) * (((uint64_t)n + IS_CHUNK - 1) / IS_CHUNK);
     } else {
         uint32_t nb_max = 1;
         for (int v = 0; v < cams.V; ++v) {
@@ -1340,11 +1332,19 @@ uint64_t is_chunk_bound(const DevCams& cams, int level, int n, uint64_t level2_i
 
 uint32_t is_window() { return IS_W; }
 
+// Items of a level-1 chunk: 2,048, halved down to 256 while that leaves fewer than 256
+// chunks, one for each compute unit (100,000 pairs: 391 chunks are scattered in 18 us, 49
+// in 37), and while the scratch, which is sized for level 2 and chunks of 2,048, has room
+// for their counts.
 void plan_interval_levels(IsArgs* l1, IsArgs* l2) {
     l1->nseg = is_segments(l1->cams, 1);
     l2->nseg = is_segments(l2->cams, 2);
-    l1->chunk_items = is_chunk_items(l1->cams, l1->n);
-    l1->seg_chunks = ((uint32_t)l1->n + l1->chunk_items - 1) / l1->chunk_items;
+    const auto seg_chunks = [&](uint32_t items) { return ((uint64_t)l1->n + items - 1) / items; };
+    uint32_t items = IS_CHUNK;
+    while (items > 256u && l1->nseg * seg_chunks(items) < 256u && l1->nseg * seg_chunks(items / 2u) <= l1->mat_chunks)
+        items /= 2u;
+    l1->chunk_items = items;
+    l1->seg_chunks = (uint32_t)seg_chunks(items);
 }
 
 static dim3 is_grid(const IsArgs& a, int level) {

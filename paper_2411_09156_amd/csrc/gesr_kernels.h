@@ -183,7 +183,7 @@ struct IsArgs {
     uint32_t* out_keys;             // nullable: bucket id of every entry
     uint32_t* out_cols;             // level 1: columns of every entry (tx0 | tx1 << 16)
     uint64_t out_cap;
-    const float4* item_ell;         // level 1 (nullable): per item, the footprint ellipse; each entry
+    const float4* item_ell;         // level 1: per item, the footprint ellipse; each entry
     int tile_w, tile_h;             //   then carries the columns it reaches in the entry's row
     DevCams cams;
 };

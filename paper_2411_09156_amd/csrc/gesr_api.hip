@@ -470,11 +470,12 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
                        "instance slots"));
     // The count is read back behind the scan, but waited for only when the lists are
     // enqueued too, so that the GPU does not idle meanwhile (100,000 splats, 1008x756:
-    // the forward takes 253 us, 280 when the wait came first); lists beyond m_cap are
-    // truncated, as without the flag.  A call that may not allocate, or whose stream is
+    // the forward takes 253 us, 280 when the wait came first); when M exceeds m_cap the
+    // lists' passes see it and end.  A call that may not allocate, or whose stream is
     // being captured (where the wait is an error), copies and waits here.
     const bool wait = (flags & GESR_BIN_SYNC) != 0;
     const bool later = wait && may_allocate && can_read_later(ctx, strm);
+    const uint32_t* skip = later ? bins->counters + 1 : nullptr;  // the call will be refused
     auto check_m = [&](uint32_t m) -> gesr_status {
         if (m_out) *m_out = m;
         if ((uint64_t)m > bins->m_cap)
@@ -495,7 +496,7 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
     // 3. row lists: every pair in the rows its rectangle covers (level 1), each
     //    entry with the columns its ellipse reaches in that row
     if (st->radix_bits != 8 || (uint32_t)n > DEPTH_SORT_SMALL)
-        GESR_TRY(hip_check(ctx, launch_gather_rects(order_vd, proj->rec, g.vn, s.srect, s.sell, strm), "rectangles"));
+        GESR_TRY(hip_check(ctx, launch_gather_rects(order_vd, proj->rec, g.vn, s.srect, s.sell, skip, strm), "rectangles"));
     IsArgs ia;
     memset(&ia, 0, sizeof ia);
     ia.n = n;
@@ -505,6 +506,7 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
     ia.mat = s.mat;
     ia.mat_chunks = s.mat_chunks;
     ia.cams = dc;
+    ia.skip = skip;
     IsArgs l1 = ia;
     l1.items = order_vd;
     l1.item_rect = s.srect;

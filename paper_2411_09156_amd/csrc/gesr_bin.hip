@@ -425,8 +425,9 @@ __device__ __forceinline__ void write_rect(f32x4 r0, f32x4 r1, f32x4 r3, uint64_
 // Bound by the gathered lines, which four lanes take together: 48 million pairs
 // 1,248 us (a lane by itself 1,439), 4 million 107 (131).
 __global__ __launch_bounds__(256) void k_gather_rects(const uint32_t* order, const float* rec, uint64_t count,
-                                                      uint2* out, float4* ell) {
+                                                      uint2* out, float4* ell, const uint32_t* skip) {
     __shared__ f32x4 s_stage[4 * 256];
+    if (skip && *skip != 0u) return;
     const uint64_t k = (uint64_t)blockIdx.x * 256 + threadIdx.x;
     const uint32_t p = order[k < count ? k : count - 1];
     QuadRecord q;
@@ -837,6 +838,7 @@ __global__ __launch_bounds__(IS_THREADS) __attribute__((amdgpu_waves_per_eu(8)))
     // the chunk's item values (level 1: and rectangle columns)
     __shared__ uint32_t s_item_p[MODE == 1 ? IS_CHUNK : 1];
     __shared__ uint32_t s_item_c[LEVEL == 1 && MODE == 1 ? IS_CHUNK : 1];
+    if (a.skip && *a.skip != 0u) return;
     const uint32_t lane = __lane_id(), wave = threadIdx.x / 64;
     const uint32_t item0 = wave * (64 * IS_IPL) + lane;  // chunk-local index of this lane's first item
     // a contiguous share of the chunks per block: the segment is looked up once
@@ -1322,9 +1324,9 @@ hipError_t depth_sort(const uint32_t* keys, uint32_t n, uint32_t V, const SortBu
 uint64_t depth_sort_hist_words(uint64_t n, uint64_t V) { return n <= DEPTH_SORT_SMALL ? 0u : V * 256u * ((n + 1023) / 1024); }
 
 hipError_t launch_gather_rects(const uint32_t* order, const float* rec, uint64_t count, uint2* out, float4* ell,
-                               hipStream_t stream) {
+                               const uint32_t* skip, hipStream_t stream) {
     if (count == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gather_rects, grid_for(count), dim3(256), 0, stream, order, rec, count, out, ell);
+    hipLaunchKernelGGL(k_gather_rects, grid_for(count), dim3(256), 0, stream, order, rec, count, out, ell, skip);
     return hipGetLastError();
 }
 

@@ -155,8 +155,9 @@ uint64_t depth_sort_hist_words(uint64_t n, uint64_t V);
 // Binning helper kernels.
 // out[k] = the rectangle in pair order[k]'s record (x = 0xFFFFFFFF when the pair touches no tile);
 // ell[2 count]: the pair's footprint ellipse and its per-row constants.
+// Nothing when *skip (device, nullable) is set.
 hipError_t launch_gather_rects(const uint32_t* order, const float* rec, uint64_t count, uint2* out, float4* ell,
-                               hipStream_t stream);
+                               const uint32_t* skip, hipStream_t stream);
 
 // Interval scatter (tile lists from rectangles, see gesr_bin.hip).  Level 1
 // writes each pair into the row lists of the rows its rectangle covers; level
@@ -185,6 +186,7 @@ struct IsArgs {
     uint64_t out_cap;
     const float4* item_ell;         // level 1: per item, the footprint ellipse; each entry
     int tile_w, tile_h;             //   then carries the columns it reaches in the entry's row
+    const uint32_t* skip;           // nullable, device: set, the chunks are left out
     DevCams cams;
 };
 uint32_t is_segments(const DevCams& cams, int level);

@@ -1000,24 +1000,25 @@ __device__ __forceinline__ void bwd_split_tile(const RenderArgs& a, uint32_t t, 
 
 // The same tile by eight waves: the first four do phase 1 of a round while the other
 // four do phase 2 of the round before (terms, records and sums are held twice), so a
-// round lasts as long as the longer phase.  Bound by the phases' serial chains: 112 us
-// on 64 tiles (2,000 splats, 128x128), 147 with four waves and the phases in turn, 124
-// with the falloffs of four records side by side (most are off).
-template <bool EXT>
+// round lasts as long as the longer phase.  Bound by the phases' serial chains: 92 us
+// on 64 tiles (2,000 splats, 128x128) with rounds of eight, 112 with rounds of four, 147
+// with four waves and the phases in turn, 124 with the falloffs of four records side by
+// side (most are off).
+template <bool EXT, uint32_t R>
 struct BwdPipe {
     BwdStage<EXT> s[2];
-    float4 v0[2][4][4][64];  // as BwdSplit, of even and odd rounds
-    float2 v1[2][4][4][64];
+    float4 v0[2][R][4][64];  // as BwdSplit, of even and odd rounds
+    float2 v1[2][R][4][64];
     uint64_t live[2][4];
     uint32_t maxnc[4];
 };
 
-template <bool EXT>
+template <bool EXT, uint32_t R>  // R records per round
 __global__ __launch_bounds__(512) void k_render_bwd16_pipe(RenderArgs a) {
     constexpr int NP = GESR_PARTIAL_FLOATS;
-    constexpr uint32_t R = 4, GRP = 2;                // as bwd_split_tile
+    constexpr uint32_t GRP = 2;                       // side by side in phase 1
     constexpr uint32_t kRounds = kBwdBatch / R;       // rounds of a full batch
-    __shared__ BwdPipe<EXT> S;
+    __shared__ BwdPipe<EXT, R> S;
     const uint32_t t = a.worklist[blockIdx.x];
     const uint32_t w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = w8 & 3u;
     const bool first = w8 < 4u;  // phase 1
@@ -1137,32 +1138,35 @@ __global__ __launch_bounds__(512) void k_render_bwd16_pipe(RenderArgs a) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) live_of[q] = read_lane(own, q);
                 }
-                const uint32_t j = b + wave;
-                if (k * kBwdBatch + j >= total) {
-                } else if (((live_of[0] | live_of[1] | live_of[2] | live_of[3]) >> j & 1u) == 0u) {
-                    if ((int)lane < (EXT ? NP + 1 : NP)) s.red[j][lane] = 0.f;
-                } else {
-                    const float2 uv = make_float2(s.a[j].x, s.a[j].y);
-                    float gr[NP], gz = 0.0f;
-                    // all reads in flight together (a quadrant without the record holds stale terms: not added)
-                    float4 v0[4];
-                    float2 v1[4];
+#pragma unroll 1
+                for (uint32_t c = wave; c < R; c += 4u) {
+                    const uint32_t j = b + c;
+                    if (k * kBwdBatch + j >= total) {
+                    } else if (((live_of[0] | live_of[1] | live_of[2] | live_of[3]) >> j & 1u) == 0u) {
+                        if ((int)lane < (EXT ? NP + 1 : NP)) s.red[j][lane] = 0.f;
+                    } else {
+                        const float2 uv = make_float2(s.a[j].x, s.a[j].y);
+                        float gr[NP], gz = 0.0f;
+                        // all reads in flight together (a quadrant without the record holds stale terms: not added)
+                        float4 v0[4];
+                        float2 v1[4];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        v0[q] = S.v0[p & 1][wave][q][lane];
-                        v1[q] = S.v1[p & 1][wave][q][lane];
+                        for (int q = 0; q < 4; ++q) {
+                            v0[q] = S.v0[p & 1][c][q][lane];
+                            v1[q] = S.v1[p & 1][c][q][lane];
+                        }
+#pragma unroll
+                        for (int n = 0; n < NP; n += 2) opaque_zero2(gr[n], gr[n + 1]);
+                        if (EXT) gz = opaque_zero();
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            if (!(live_of[q] >> j & 1u)) continue;
+                            add_terms<EXT>(FragmentTerms{v0[q].x, v0[q].y, v0[q].z, v0[q].w, v1[q].x, v1[q].y},
+                                           (pxb + (float)((q & 1) * 8)) - uv.x, (pyb + (float)((q >> 1) * 8)) - uv.y, c2,
+                                           up[q], gr, gz);
+                        }
+                        reduce_record(s, j, gr, gz, lane, slot);
                     }
-#pragma unroll
-                    for (int n = 0; n < NP; n += 2) opaque_zero2(gr[n], gr[n + 1]);
-                    if (EXT) gz = opaque_zero();
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        if (!(live_of[q] >> j & 1u)) continue;
-                        add_terms<EXT>(FragmentTerms{v0[q].x, v0[q].y, v0[q].z, v0[q].w, v1[q].x, v1[q].y},
-                                       (pxb + (float)((q & 1) * 8)) - uv.x, (pyb + (float)((q >> 1) * 8)) - uv.y, c2,
-                                       up[q], gr, gz);
-                    }
-                    reduce_record(s, j, gr, gz, lane, slot);
                 }
             }
             // batch k - 1's last round was summed in the step before
@@ -1229,7 +1233,7 @@ hipError_t bwd_shape(const RenderArgs& a, hipStream_t s) {
 uint32_t fwd_split_tiles(uint32_t n_items) { return n_items <= 8192u ? n_items : 1024u; }
 
 // The 16x16 adjoint's tiles with eight waves each: all of them up to 2,048, where four
-// would leave SIMDs idle or with one serial chain each (147 -> 112 us on 64 tiles, 236
+// would leave SIMDs idle or with one serial chain each (147 -> 92 us on 64 tiles, 236
 // -> 174 on 1,024, 214 -> 207 on 1,936; 2,500 tiles would take 262 us instead of 234,
 // 3,024 321 instead of 231).  With four waves each: all of them up to 4,096 (one wave
 // takes 300 ns per list position and the chip's wave slots would be filled once or
@@ -1240,7 +1244,10 @@ uint32_t fwd_split_tiles(uint32_t n_items) { return n_items <= 8192u ? n_items :
 // and no list sets the end: one-wave workgroups, whose slots free up singly, take 1,790
 // us on 33,948 tiles and 5.55 ms on 130,560 against 1,890 us and 5.77 ms with four
 // waves to a workgroup.
-constexpr uint32_t kBwdPipeMax = 2048u;
+// Rounds of eight records, half the barriers for twice the LDS and so one workgroup on
+// a CU, pay up to 512 tiles (112 -> 92 us on 64, 190 -> 161 on 256, 109 -> 93 on 484;
+// 179 -> 197 on 1,024).
+constexpr uint32_t kBwdPipeMax = 2048u, kBwdPipe8Max = 512u;
 constexpr uint32_t kBwdMixedMax = 32768u;
 uint32_t bwd_split_tiles(uint32_t n_items) { return n_items <= 4096u ? n_items : 256u; }
 
@@ -1286,8 +1293,13 @@ hipError_t launch_render_bwd(const RenderArgs& a, int tw, int th, int batch, hip
         const bool ext = a.dL_ddepth || a.dL_dalpha;
         if (a.n_items <= kBwdPipeMax) {
             const dim3 grid(a.n_items), block(512);
-            if (ext) hipLaunchKernelGGL((k_render_bwd16_pipe<true>), grid, block, 0, s, a);
-            else hipLaunchKernelGGL((k_render_bwd16_pipe<false>), grid, block, 0, s, a);
+            if (a.n_items <= kBwdPipe8Max) {
+                if (ext) hipLaunchKernelGGL((k_render_bwd16_pipe<true, 8>), grid, block, 0, s, a);
+                else hipLaunchKernelGGL((k_render_bwd16_pipe<false, 8>), grid, block, 0, s, a);
+            } else {
+                if (ext) hipLaunchKernelGGL((k_render_bwd16_pipe<true, 4>), grid, block, 0, s, a);
+                else hipLaunchKernelGGL((k_render_bwd16_pipe<false, 4>), grid, block, 0, s, a);
+            }
             return hipGetLastError();
         }
         if (a.n_items > kBwdMixedMax) {

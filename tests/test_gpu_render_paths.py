@@ -80,7 +80,8 @@ def test_forward_paths_agree_bitwise(name, channels):
 @pytest.mark.parametrize("name", [k for k in SCENES if k != "wide"])
 @pytest.mark.parametrize("channels", [False, True])
 def test_adjoint_paths_agree_bitwise(name, channels):
-    """The adjoint takes every tile with eight waves up to 2,048 tiles, with four up to
+    """The adjoint takes every tile with eight waves up to 2,048 tiles (rounds of eight
+    records up to 512, of four beyond), with four up to
     4,096, the worklist's first 256 with four up to 32,768 and none above: a view's
     screen-space gradients are the same alone and beside a view that brings the batch
     to each."""
@@ -94,7 +95,7 @@ def test_adjoint_paths_agree_bitwise(name, channels):
     P = scene.n_pixels
     up = [torch.randn(k, generator=gen, device="cuda") for k in (3 * P, P, P)]
     ref, tiles = None, []
-    for pad in (None, (768, 720), (1500, 1100), (4200, 2200)):
+    for pad in (None, (480, 480), (768, 720), (1500, 1100), (4200, 2200)):
         s = copy.copy(scene)
         s.cameras = list(scene.cameras) + ([gi.look_at((0.0, 0.0, -4.0), width=pad[0], height=pad[1])] if pad else [])
         rast = _rast(s)
@@ -115,9 +116,9 @@ def test_adjoint_paths_agree_bitwise(name, channels):
             ref = g
             assert np.abs(g).max() > 0
         np.testing.assert_array_equal(g, ref, err_msg=str(pad))
-    assert 2048 < tiles[1] and 4096 < tiles[2] <= 32768 < tiles[3]
-    if tiles[0] <= 1900:
-        assert tiles[1] <= 4096
+    assert 512 < tiles[1] and 2048 < tiles[2] and 4096 < tiles[3] <= 32768 < tiles[4]
+    if tiles[0] <= 1100:
+        assert tiles[1] <= 2048 and tiles[2] <= 4096
 
 
 def _giant():

@@ -524,7 +524,7 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
     float d = 0.f, gd[3] = {0.f, 0.f, 0.f}, best = -1.f;
     int gs = 0;
     // the next neighbour's frame is loaded while this one is evaluated
-    // (padding slots, n < k, load some frame and are skipped)
+    // (padding slots, n < k, load some frame and are skipped here and in pass 2)
     QuadRecord next;
     next.load(a.frames, quad_at(0), last);
     for (int s = 0; s < K; ++s) {
@@ -616,8 +616,10 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
         const GFrame f = unpack_gframe(r0, r1, r2, r3, a.rho);
         if (s > 0) next.load(a.frames, quad_at(s - 1), last);
         // the partial of slot s goes to record inv_slot[p * k + s]: each splat's
-        // records end up contiguous, in inverse-list order (padding slots have none)
-        const uint32_t slot = i < (uint32_t)a.n ? a.inv_slot[(size_t)p * K + s] : 0xFFFFFFFFu;
+        // records end up contiguous, in inverse-list order (padding slots have none, and
+        // their frame's terms stay out of the sample point's gradient)
+        const bool valid = i < (uint32_t)a.n;
+        const uint32_t slot = valid ? a.inv_slot[(size_t)p * K + s] : 0xFFFFFFFFu;
         const Term t = eval_term(f, f0.mu, d0, kappa);
         // b = diag(1/sig) R^T u, scaled by gmax like u
         float b[3];
@@ -644,7 +646,7 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
         }
         for (int r2 = 0; r2 < 3; ++r2) {
             const float v = f.R[3 * r2] * sa[0] + f.R[3 * r2 + 1] * sa[1] + f.R[3 * r2 + 2] * sa[2];
-            gx[r2] += v;
+            gx[r2] += valid ? v : 0.f;
             g_mu[r2] = -v;
         }
         for (int k = 0; k < 3; ++k) g_sig[k] = -(t.a[k] * sa[k] + b[k] * sb[k]);

@@ -101,6 +101,13 @@ __device__ __forceinline__ PixelUp load_up(const RenderArgs& a, uint32_t pix, ui
     return u;
 }
 
+// Whether an upstream gradient of the wave's pixels is not finite (or nearly so).
+template <bool EXT>
+__device__ __forceinline__ bool any_odd(const PixelUp& u) {
+    const float s = fabsf(u.g0) + fabsf(u.g1) + fabsf(u.g2) + (EXT ? fabsf(u.gD) : 0.0f);
+    return __builtin_amdgcn_ballot_w64(!(s < INFINITY)) != 0ull;
+}
+
 // The background has no depth and no opacity.
 __device__ __forceinline__ PixelAdjoint behind_all(const DevSettings& st, float T) {
     return PixelAdjoint{T, st.bg[0], st.bg[1], st.bg[2], 0.f, 0.f};
@@ -854,6 +861,9 @@ __device__ __forceinline__ void bwd_wave_tile(const RenderArgs& a, uint32_t t, B
 // are independent chains, only T and the colour behind are serial.  Phase 2: wave w
 // adds the w-th record's terms over the whole tile (4 pixels per lane, quadrants in
 // order) and reduces them.
+// There a pixel that the record did not reach adds zero times its upstream gradient, so
+// a tile with one that is not finite is not taken (false): one wave, which visits a
+// record's own pixels only, has to.
 template <bool EXT>
 struct BwdSplit {
     BwdStage<EXT> s;
@@ -864,7 +874,7 @@ struct BwdSplit {
 };
 
 template <bool EXT>
-__device__ __forceinline__ void bwd_split_tile(const RenderArgs& a, uint32_t t, uint32_t wave, BwdSplit<EXT>& S) {
+__device__ __forceinline__ bool bwd_split_tile(const RenderArgs& a, uint32_t t, uint32_t wave, BwdSplit<EXT>& S) {
     constexpr int NP = GESR_PARTIAL_FLOATS;
     constexpr int R = 4, GRP = 2;  // records per round, and side by side in phase 1
     BwdStage<EXT>& s = S.s;
@@ -880,6 +890,7 @@ __device__ __forceinline__ void bwd_split_tile(const RenderArgs& a, uint32_t t, 
     PixelUp up[4], mine{};
     PixelAdjoint pa = behind_all(st, 0.f);
     uint32_t nc = 0;
+    bool odd = false;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int x = (int)tp.tx * 16 + (q & 1) * 8 + (int)(lane & 7);
@@ -895,7 +906,9 @@ __device__ __forceinline__ void bwd_split_tile(const RenderArgs& a, uint32_t t, 
                 mine = up[q];
             }
         }
+        odd |= any_odd<EXT>(up[q]);
     }
+    if (odd) return false;  // every wave's finding
     const uint32_t wmax = __builtin_amdgcn_readfirstlane(wave_max_u32(nc));  // this quadrant's deepest position
     if (lane == 0) S.maxnc[wave] = wmax;
     __syncthreads();
@@ -996,6 +1009,7 @@ __device__ __forceinline__ void bwd_split_tile(const RenderArgs& a, uint32_t t, 
         if (wave == 0) write_batch(a, s, lane, cnt);
         hi -= cnt;
     }
+    return true;
 }
 
 // The same tile by eight waves: the first four do phase 1 of a round while the other
@@ -1011,6 +1025,7 @@ struct BwdPipe {
     float2 v1[2][R][4][64];
     uint64_t live[2][4];
     uint32_t maxnc[4];
+    bool odd;
 };
 
 template <bool EXT, uint32_t R>  // R records per round
@@ -1034,6 +1049,7 @@ __global__ __launch_bounds__(512) void k_render_bwd16_pipe(RenderArgs a) {
     PixelUp up[4], mine{};
     PixelAdjoint pa = behind_all(st, 0.f);
     uint32_t nc = 0;
+    bool odd = false;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int x = (int)tp.tx * 16 + (q & 1) * 8 + (int)(lane & 7);
@@ -1049,10 +1065,16 @@ __global__ __launch_bounds__(512) void k_render_bwd16_pipe(RenderArgs a) {
                 mine = up[q];
             }
         }
+        odd |= any_odd<EXT>(up[q]);
     }
     const uint32_t wmax = __builtin_amdgcn_readfirstlane(wave_max_u32(nc));  // this quadrant's deepest position
     if (first && lane == 0) S.maxnc[wave] = wmax;
+    if (w8 == 4 && lane == 0) S.odd = odd;  // of the whole tile
     __syncthreads();
+    if (S.odd) {  // see BwdSplit
+        if (w8 == 0) bwd_wave_tile<EXT>(a, t, S.s[0]);
+        return;
+    }
     const uint32_t total = __builtin_amdgcn_readfirstlane(max(max(S.maxnc[0], S.maxnc[1]), max(S.maxnc[2], S.maxnc[3])));
     const int slot = lane < 16 ? wave_sum10_slot(lane) : NP;
     const uint32_t top = r0 + total;  // positions top - 1 .. r0, batch k from top - 64 k
@@ -1189,11 +1211,11 @@ __global__ __launch_bounds__(256, EXT ? 4 : 5) void k_render_bwd16(RenderArgs a)
         BwdSplit<EXT> split;
     } S;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t item = a.n_split + 4u * (blockIdx.x - a.n_split) + wave;
     if (blockIdx.x < a.n_split) {
-        bwd_split_tile<EXT>(a, a.worklist[blockIdx.x], wave, S.split);
-        return;
+        if (bwd_split_tile<EXT>(a, a.worklist[blockIdx.x], wave, S.split) || wave != 0) return;
+        item = blockIdx.x;
     }
-    const uint32_t item = a.n_split + 4u * (blockIdx.x - a.n_split) + wave;
     if (item < a.n_items) bwd_wave_tile<EXT>(a, a.worklist[item], S.wave[wave]);
 }
 

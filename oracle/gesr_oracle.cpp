@@ -1690,7 +1690,7 @@ int orc_knn(int N, const double* means, int K, int32_t* knn) {
     return 0;
 }
 
-// GSR losses and gradients.  knn [N][K] (slot 0 = j); xi [N][3]; mask [N]
+// GSR losses and gradients.  knn [N][K] (slot 0 = j; negative entries are padding); xi [N][3]; mask [N]
 // (nullable: every sample); per sample l_sdf, l_nor, gstar (neighbour slot),
 // margins [N][7]; grads [N][12] (mean 3, scale 3, quat 4, opacity, beta) of
 // sum_j mask_j (w_sdf l_sdf + w_nor l_nor), accumulated when non-null.
@@ -1707,9 +1707,16 @@ int orc_gsr(int N, const double* means, const double* scales, const double* quat
         gstar[j] = -1;
         for (int k = 0; k < 7; ++k) margins[7 * j + k] = 0.0;
         if (mask && !mask[j]) continue;
-        const int32_t* nb = knn + (long)j * K;
-        std::vector<double> mu(3 * K), sc(3 * K), qu(4 * K), op(K), be(K);
-        for (int s = 0; s < K; ++s) {
+        std::vector<int32_t> nb, slot;  // the valid entries and their slots
+        for (int s = 0; s < K; ++s)
+            if (knn[(long)j * K + s] >= 0) {
+                nb.push_back(knn[(long)j * K + s]);
+                slot.push_back(s);
+            }
+        const int L = (int)nb.size();
+        if (L == 0) continue;
+        std::vector<double> mu(3 * L), sc(3 * L), qu(4 * L), op(L), be(L);
+        for (int s = 0; s < L; ++s) {
             long i = nb[s];
             for (int a = 0; a < 3; ++a) { mu[3 * s + a] = means[3 * i + a]; sc[3 * s + a] = scales[3 * i + a]; }
             for (int a = 0; a < 4; ++a) qu[4 * s + a] = quats[4 * i + a];
@@ -1718,25 +1725,25 @@ int orc_gsr(int N, const double* means, const double* scales, const double* quat
         }
         GsrInfo info;
         double ls, ln;
-        gsr_sample<double>(K, reinterpret_cast<const double(*)[3]>(mu.data()),
+        gsr_sample<double>(L, reinterpret_cast<const double(*)[3]>(mu.data()),
                            reinterpret_cast<const double(*)[3]>(sc.data()),
                            reinterpret_cast<const double(*)[4]>(qu.data()), op.data(), be.data(), xi + 3 * j, st, ls,
                            ln, info);
         l_sdf[j] = ls;
         l_nor[j] = ln;
-        gstar[j] = info.gstar;
+        gstar[j] = slot[info.gstar];
         for (int k = 0; k < 7; ++k) margins[7 * j + k] = info.margins[k];
         if (!grads) continue;
         double* g = tg[thread_id()].data();
         using D12 = Dual<12>;
-        std::vector<D12> dm(3 * K), ds(3 * K), dq(4 * K), dop(K), db(K);
-        for (int s = 0; s < K; ++s) {
+        std::vector<D12> dm(3 * L), ds(3 * L), dq(4 * L), dop(L), db(L);
+        for (int s = 0; s < L; ++s) {
             for (int a = 0; a < 3; ++a) { dm[3 * s + a] = D12(mu[3 * s + a]); ds[3 * s + a] = D12(sc[3 * s + a]); }
             for (int a = 0; a < 4; ++a) dq[4 * s + a] = D12(qu[4 * s + a]);
             dop[s] = D12(op[s]);
             db[s] = D12(be[s]);
         }
-        for (int s = 0; s < K; ++s) {
+        for (int s = 0; s < L; ++s) {
             // seed neighbour s's twelve parameters
             for (int a = 0; a < 3; ++a) { dm[3 * s + a].d[a] = 1.0; ds[3 * s + a].d[3 + a] = 1.0; }
             for (int a = 0; a < 4; ++a) dq[4 * s + a].d[6 + a] = 1.0;
@@ -1744,7 +1751,7 @@ int orc_gsr(int N, const double* means, const double* scales, const double* quat
             db[s].d[11] = 1.0;
             GsrInfo di;
             D12 a_sdf, a_nor;
-            gsr_sample<D12>(K, reinterpret_cast<const D12(*)[3]>(dm.data()),
+            gsr_sample<D12>(L, reinterpret_cast<const D12(*)[3]>(dm.data()),
                             reinterpret_cast<const D12(*)[3]>(ds.data()), reinterpret_cast<const D12(*)[4]>(dq.data()),
                             dop.data(), db.data(), xi + 3 * j, st, a_sdf, a_nor, di);
             long i = nb[s];

@@ -255,6 +255,15 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
     return l == 0 ? 0ull : ((~0ull) >> (64 - l));
 }
 
+// Insertion into an ordered list of doubles: the entry's new value.
+// b = max(below, min(b, c)) in place; kept in order (volatile), since moved about the
+// old and new entries of the list would both be held.  b is written before `below` is
+// read: an early clobber, or equal values (a new list's) might share a register.
+__device__ __forceinline__ void place_f64(double& b, double below, double c) {
+    asm volatile("v_min_f64 %0, %0, %2\n\tv_max_f64 %0, %1, %0" : "+&v"(b) : "v"(below), "v"(c));
+}
+__device__ __forceinline__ void place_f64(double& b, double c) { asm volatile("v_min_f64 %0, %0, %1" : "+v"(b) : "v"(c)); }
+
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // LDS written by a wave is read by its other lanes, or the other way round.

@@ -187,12 +187,6 @@ __global__ __launch_bounds__(256) void k_knn_sorted_pos(const float* mean, int n
 // bits) << 32 | index.  Distances are never negative and their bits stay below a
 // double's infinity, so the words order alike as integers and as doubles, and one
 // entry's place costs a 64-bit minimum and maximum.
-// b = max(below, min(b, c)) in place; kept in order (volatile), since moved about the
-// old and new entries of the list would both be held.
-__device__ __forceinline__ void place_f64(double& b, double below, double c) {
-    asm volatile("v_min_f64 %0, %0, %2\n\tv_max_f64 %0, %1, %0" : "+v"(b) : "v"(below), "v"(c));
-}
-__device__ __forceinline__ void place_f64(double& b, double c) { asm volatile("v_min_f64 %0, %0, %1" : "+v"(b) : "v"(c)); }
 constexpr int KNN_PEND = 8;  // candidates a query keeps for the next insertion
 template <int WANT>
 struct Nearest {

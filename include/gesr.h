@@ -226,8 +226,8 @@ gesr_status gesr_project(gesr_ctx* ctx, const gesr_splats* splats, const gesr_ca
  * Instance slots (inst_base, the backward's partials) keep the rectangle
  * layout.  With GESR_BIN_SYNC the call
  * waits once for the count (the lists are enqueued meanwhile); if M > m_cap it
- * returns GESR_ERR_CAPACITY with *m_out = M, the stream drained, and leaves the
- * sorted lists undefined.
+ * returns GESR_ERR_CAPACITY with *m_out = M, the stream drained, and the lists,
+ * ranges and worklist as they were.
  * Without it the call never synchronises (capturable in a HIP graph): lists
  * are truncated to m_cap and counters[1] is set.  *m_out (nullable) receives
  * M only with GESR_BIN_SYNC. */

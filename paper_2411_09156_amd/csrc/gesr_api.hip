@@ -470,8 +470,9 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
                        "instance slots"));
     // The count is read back behind the scan, but waited for only when the lists are
     // enqueued too, so that the GPU does not idle meanwhile (100,000 splats, 1008x756:
-    // the forward takes 253 us, 280 when the wait came first); when M exceeds m_cap the
-    // lists' passes see it and end.  A call that may not allocate, or whose stream is
+    // the forward takes 253 us, 280 when the wait came first); when M exceeds m_cap every
+    // pass behind the scan sees it and ends, so that nothing runs on counts that were not
+    // taken and the caller's lists, ranges and worklist stay as they are.  A call that may not allocate, or whose stream is
     // being captured (where the wait is an error), copies and waits here.
     const bool wait = (flags & GESR_BIN_SYNC) != 0;
     const bool later = wait && may_allocate && can_read_later(ctx, strm);
@@ -543,6 +544,7 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
     tl.total = bins->counters + 3;
     tl.listed = bins->counters + 2;
     tl.work = (flags & GESR_BIN_WORK_ORDER) ? bins->tile_work : nullptr;
+    tl.skip = skip;
     tl.ranges = bins->ranges;
     tl.worklist = bins->worklist;
     tl.sort = SortBuffers{s.w_keys_a, s.w_vals_a, s.w_keys_b, nullptr, s.block_hist, s.scan_partials};

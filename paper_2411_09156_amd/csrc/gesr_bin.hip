@@ -235,8 +235,8 @@ template <int BITS, bool VIEW>
 __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(const uint32_t* keys_in, const uint32_t* vals_in,
                                                                 uint32_t* keys_out, uint32_t* vals_out,
                                                                 uint64_t count_static, const uint32_t* count_dev,
-                                                                int shift, uint32_t view_n,
-                                                                const uint32_t* block_off, uint32_t nblocks) {
+                                                                int shift, uint32_t view_n, const uint32_t* block_off,
+                                                                uint32_t nblocks, const uint32_t* skip) {
     constexpr int RADIX = 1 << BITS;
     __shared__ uint32_t hist[WAVES][RADIX];
     __shared__ uint32_t digit_start[RADIX + 1];
@@ -245,6 +245,7 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(const uint32_t* 
     __shared__ uint32_t s_vals[SORT_TILE];
     __shared__ uint32_t s_wave[WAVES + 1];
 
+    if (skip && *skip != 0u) return;
     const uint32_t n = count_of(count_dev, count_static);
     const uint64_t block_start = (uint64_t)blockIdx.x * SORT_TILE;
     if (block_start >= n) return;  // uniform over the block
@@ -329,10 +330,10 @@ hipError_t sort_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, u
     if (e != hipSuccess) return e;
     if (view_n != 0u)
         hipLaunchKernelGGL((k_radix_scatter<BITS, true>), dim3(nblocks), dim3(SORT_THREADS), 0, stream, kin, vin,
-                           kout, vout, count_static, count_dev, shift, view_n, b.block_hist, nblocks);
+                           kout, vout, count_static, count_dev, shift, view_n, b.block_hist, nblocks, b.skip);
     else
         hipLaunchKernelGGL((k_radix_scatter<BITS, false>), dim3(nblocks), dim3(SORT_THREADS), 0, stream, kin, vin,
-                           kout, vout, count_static, count_dev, shift, view_n, b.block_hist, nblocks);
+                           kout, vout, count_static, count_dev, shift, view_n, b.block_hist, nblocks, b.skip);
     return hipGetLastError();
 }
 
@@ -1127,6 +1128,7 @@ __device__ __forceinline__ void segment_prefix(const IsArgs& a, uint32_t s, uint
 template <int LEVEL>
 __global__ __launch_bounds__(IS_W * IS_PARTS) void k_is_prefix(IsArgs a) {
     __shared__ uint32_t s_part[IS_PARTS][IS_W];
+    if (a.skip && *a.skip != 0u) return;
     segment_prefix<LEVEL>(a, blockIdx.x, s_part);
 }
 
@@ -1140,6 +1142,7 @@ constexpr uint32_t ROWS_SEGMENTS = 2;
 __global__ __launch_bounds__(1024) void k_is_rows(IsArgs a, uint32_t prefix_segs, uint32_t rows, uint32_t* counters) {
     __shared__ uint32_t s_tile[4096 + 128], s_wave[17], s_part[IS_PARTS][IS_W];
     static_assert(IS_PARTS * IS_W == 1024, "one block does a segment's prefix");
+    if (a.skip && *a.skip != 0u) return;
     for (uint32_t s = 0; s < prefix_segs; ++s) {
         segment_prefix<1>(a, s, s_part);
         __syncthreads();
@@ -1183,9 +1186,10 @@ __device__ __forceinline__ uint32_t worklist_key(uint2 r, const uint32_t* work, 
 
 __global__ __launch_bounds__(256) void k_ranges_from_counts(const uint32_t* counts, const uint32_t* starts,
                                                             uint64_t total_tiles, const uint32_t* listed,
-                                                            const uint32_t* work, uint32_t* ranges, uint32_t* keys) {
+                                                            const uint32_t* work, const uint32_t* skip, uint32_t* ranges,
+                                                            uint32_t* keys) {
     const uint64_t t = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= total_tiles) return;
+    if (t >= total_tiles || (skip && *skip != 0u)) return;
     const uint2 r = tile_range(counts[t], starts[t], *listed);
     reinterpret_cast<uint2*>(ranges)[t] = r;
     keys[t] = worklist_key(r, work, t);
@@ -1198,9 +1202,10 @@ __global__ __launch_bounds__(256) void k_ranges_from_counts(const uint32_t* coun
 template <int ITEMS>
 __global__ __launch_bounds__(1024) void k_tile_lists_small(const uint32_t* counts, uint32_t* starts, uint32_t T,
                                                            uint32_t* total, const uint32_t* listed,
-                                                           const uint32_t* work, uint32_t* ranges,
+                                                           const uint32_t* work, const uint32_t* skip, uint32_t* ranges,
                                                            uint32_t* worklist) {
     static_assert(ITEMS <= 16, "tile ids take 16 bits");
+    if (skip && *skip != 0u) return;
     __shared__ uint32_t s_key[1024 * ITEMS > 4096 + 128 ? 1024 * ITEMS : 4096 + 128];
     __shared__ uint32_t s_hist[16][256], s_start[256], s_wave[17];
     const uint32_t run = scan_by_block(counts, starts, T, s_key, s_wave);
@@ -1409,17 +1414,18 @@ hipError_t launch_tile_lists(const TileListArgs& a, hipStream_t stream) {
     if (T == 0) return hipSuccess;
     if (T <= 16384u) {
         auto k = T <= 1024u ? k_tile_lists_small<1> : (T <= 4096u ? k_tile_lists_small<4> : k_tile_lists_small<16>);
-        hipLaunchKernelGGL(k, dim3(1), dim3(1024), 0, stream, a.counts, a.starts, T, a.total, a.listed, a.work, a.ranges,
-                           a.worklist);
+        hipLaunchKernelGGL(k, dim3(1), dim3(1024), 0, stream, a.counts, a.starts, T, a.total, a.listed, a.work, a.skip,
+                           a.ranges, a.worklist);
         return hipGetLastError();
     }
     hipError_t e = scan_exclusive(a.counts, a.starts, T, a.sort.scan_partials, a.total, stream);
     if (e != hipSuccess) return e;
     // two 8-bit passes: keys_b -> a -> (keys_b, worklist)
     hipLaunchKernelGGL(k_ranges_from_counts, grid_for(T), dim3(256), 0, stream, a.counts, a.starts, (uint64_t)T, a.listed,
-                       a.work, a.ranges, a.sort.keys_b);
+                       a.work, a.skip, a.ranges, a.sort.keys_b);
     SortBuffers b = a.sort;
     b.vals_b = a.worklist;
+    b.skip = a.skip;
     bool in_b = false;
     return radix_sort(b.keys_b, nullptr, T, nullptr, 16, 8, b, &in_b, stream);
 }

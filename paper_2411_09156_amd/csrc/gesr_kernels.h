@@ -136,6 +136,7 @@ struct SortBuffers {
     uint32_t *keys_a, *vals_a, *keys_b, *vals_b;
     uint32_t* block_hist;  // 2^radix_bits * ceil(count_static / SORT_TILE)
     uint32_t* scan_partials;
+    const uint32_t* skip = nullptr;  // nullable, device: set, nothing is sorted
 };
 hipError_t radix_sort(const uint32_t* keys_in, const uint32_t* vals_in, uint64_t count_static,
                       const uint32_t* count_dev, int key_bits, int radix_bits, const SortBuffers& b,
@@ -186,7 +187,7 @@ struct IsArgs {
     uint64_t out_cap;
     const float4* item_ell;         // level 1: per item, the footprint ellipse; each entry
     int tile_w, tile_h;             //   then carries the columns it reaches in the entry's row
-    const uint32_t* skip;           // nullable, device: set, the chunks are left out
+    const uint32_t* skip;           // nullable, device: set, the level is left out
     DevCams cams;
 };
 uint32_t is_segments(const DevCams& cams, int level);
@@ -209,6 +210,7 @@ struct TileListArgs {
     uint32_t* total;         // device
     const uint32_t* listed;  // device: instances within the capacity
     const uint32_t* work;    // nullable: order by it instead of by list length
+    const uint32_t* skip;    // nullable, device: set, ranges and worklist are left as they are
     uint32_t* ranges;
     uint32_t* worklist;
     SortBuffers sort;        // [T] keys_a, vals_a, keys_b; block_hist, scan_partials

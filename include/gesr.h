@@ -12,7 +12,9 @@
  * Conventions for every entry point
  *  - Array pointers marked DEVICE are device memory owned by the caller; the
  *    library never allocates, frees or retains them past the call.  HOST
- *    pointers are read during the call only.
+ *    pointers are read during the call only.  (gesr_autotune allocates its
+ *    trials' buffers; a context's first gesr_bin with GESR_BIN_SYNC takes a
+ *    pinned host word and an event, which the library keeps for later contexts.)
  *  - All device work is enqueued on `stream` (a hipStream_t; NULL = default
  *    stream).  Calls return after enqueueing, except where a synchronous
  *    capacity check is requested (gesr_bin with GESR_BIN_SYNC).

@@ -1,6 +1,7 @@
 // C ABI of the GES rasterizer: argument validation, scratch layout and the
 // launch sequence of each entry point.  Host code; device work is enqueued on
-// the caller's stream and nothing is allocated here.
+// the caller's stream and no device memory is allocated here, except by the
+// autotuner's trials.
 
 #include <math.h>
 #include <stdarg.h>
@@ -15,12 +16,76 @@
 #include "gesr_device.h"
 #include "gesr_kernels.h"
 
+namespace {
+
+// Where a synchronous binning reads its instance count back: a pinned word and an event
+// on the device.
+struct CountSlot {
+    int device = -1;
+    uint32_t* host = nullptr;
+    hipEvent_t read = nullptr;
+};
+
+// Slots that no context holds.  A context takes one at its first synchronous binning and
+// gives it back when it is destroyed: to make one takes 50 us, and to free pinned memory
+// waits for the device (a context made for one forward of 100,000 splats: 358 us a call
+// with a slot of its own, 240 with a kept one, 232 for a context that stays).  At most
+// kKept stay, one for each context that a program destroys before it makes the next.
+class CountSlots {
+   public:
+    bool take(int device, CountSlot* out) {
+        {
+            std::lock_guard<std::mutex> lock(mutex_);
+            for (int k = 0; k < n_; ++k)
+                if (free_[k].device == device) {
+                    *out = free_[k];
+                    free_[k] = free_[--n_];
+                    return true;
+                }
+        }
+        // another thread may be capturing, which forbids allocation in the other modes
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        CountSlot s;
+        s.device = device;
+        const bool ok = hipHostMalloc((void**)&s.host, sizeof(uint32_t), hipHostMallocDefault) == hipSuccess &&
+                        hipEventCreateWithFlags(&s.read, hipEventDisableTiming) == hipSuccess;
+        if (!ok) {
+            (void)hipGetLastError();
+            if (s.host) (void)hipHostFree(s.host);
+        }
+        if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (ok) *out = s;
+        return ok;
+    }
+    // s: its last copy has arrived
+    void give(const CountSlot& s) {
+        {
+            std::lock_guard<std::mutex> lock(mutex_);
+            if (n_ < kKept) {
+                free_[n_++] = s;
+                return;
+            }
+        }
+        (void)hipEventDestroy(s.read);
+        (void)hipHostFree(s.host);
+    }
+
+   private:
+    static constexpr int kKept = 16;
+    std::mutex mutex_;
+    CountSlot free_[kKept];
+    int n_ = 0;
+};
+CountSlots g_count_slots;
+
+}  // namespace
+
 struct gesr_ctx {
     int device;
     std::string err;
-    // the instance count's way to the host (GESR_BIN_SYNC; made at its first use)
-    uint32_t* m_host = nullptr;  // pinned
-    hipEvent_t m_read = nullptr;
+    CountSlot slot;           // taken at the first synchronous binning
+    bool slot_busy = false;   // a copy into it was enqueued and not waited for
 };
 
 namespace {
@@ -331,8 +396,8 @@ gesr_status gesr_ctx_create(int device, gesr_ctx** out) {
 
 void gesr_ctx_destroy(gesr_ctx* ctx) {
     if (!ctx) return;
-    if (ctx->m_read) (void)hipEventDestroy(ctx->m_read);
-    if (ctx->m_host) (void)hipHostFree(ctx->m_host);
+    // a slot whose copy may yet arrive (a launch failed behind it) stays out of use
+    if (ctx->slot.host && !ctx->slot_busy) g_count_slots.give(ctx->slot);
     delete ctx;
 }
 
@@ -406,25 +471,13 @@ gesr_status gesr_project(gesr_ctx* ctx, const gesr_splats* splats, const gesr_ca
 
 namespace {
 
-// Whether an instance count can be read back behind later launches: the context's
-// pinned word and event exist (or can be made now) and the stream is not being captured.
-bool can_read_later(gesr_ctx* ctx, hipStream_t strm) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(strm, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return false;
-    }
-    if (!ctx->m_host && hipHostMalloc((void**)&ctx->m_host, sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) {
-        ctx->m_host = nullptr;
-        (void)hipGetLastError();
-        return false;
-    }
-    if (!ctx->m_read && hipEventCreateWithFlags(&ctx->m_read, hipEventDisableTiming) != hipSuccess) {
-        ctx->m_read = nullptr;
-        (void)hipGetLastError();
-        return false;
-    }
-    return true;
+// Whether an instance count can be read back behind later launches: the context holds a
+// slot, or can take one now.
+bool can_read_later(gesr_ctx* ctx) {
+    if (ctx->slot.host && !ctx->slot_busy) return true;
+    ctx->slot_busy = false;
+    ctx->slot = CountSlot();
+    return g_count_slots.take(ctx->device, &ctx->slot);
 }
 
 // The binning pipeline of gesr_bin on a scratch buffer of `scratch_bytes` at
@@ -435,6 +488,13 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
                      size_t scratch_bytes, int flags, uint64_t* m_out, void* stream, bool may_allocate) {
     if ((flags & GESR_BIN_WORK_ORDER) && !bins->tile_work)
         return fail(ctx, GESR_ERR_INVALID, "GESR_BIN_WORK_ORDER needs bins->tile_work");
+    const bool wait = (flags & GESR_BIN_SYNC) != 0;
+    if (wait) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing((hipStream_t)stream, &capture) != hipSuccess) (void)hipGetLastError();
+        if (capture != hipStreamCaptureStatusNone)
+            return fail(ctx, GESR_ERR_HIP, "GESR_BIN_SYNC waits, which a stream that is being captured cannot");
+    }
     const DevCams dc = dev_cams(cams, V, st);
     BinScratch s = carve(scratch, g, dc, n, bins->m_cap);
     if (scratch_bytes < s.bytes)
@@ -472,10 +532,9 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
     // enqueued too, so that the GPU does not idle meanwhile (100,000 splats, 1008x756:
     // the forward takes 253 us, 280 when the wait came first); when M exceeds m_cap every
     // pass behind the scan sees it and ends, so that nothing runs on counts that were not
-    // taken and the caller's lists, ranges and worklist stay as they are.  A call that may not allocate, or whose stream is
-    // being captured (where the wait is an error), copies and waits here.
-    const bool wait = (flags & GESR_BIN_SYNC) != 0;
-    const bool later = wait && may_allocate && can_read_later(ctx, strm);
+    // taken and the caller's lists, ranges and worklist stay as they are.  A call that may
+    // not allocate copies and waits here.
+    const bool later = wait && may_allocate && can_read_later(ctx);
     const uint32_t* skip = later ? bins->counters + 1 : nullptr;  // the call will be refused
     auto check_m = [&](uint32_t m) -> gesr_status {
         if (m_out) *m_out = m;
@@ -485,9 +544,11 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
         return GESR_OK;
     };
     if (later) {
-        GESR_TRY(hip_check(ctx, hipMemcpyAsync(ctx->m_host, bins->counters, sizeof(uint32_t), hipMemcpyDeviceToHost, strm),
+        ctx->slot_busy = true;
+        GESR_TRY(hip_check(ctx, hipMemcpyAsync(ctx->slot.host, bins->counters, sizeof(uint32_t), hipMemcpyDeviceToHost,
+                                               strm),
                            "M copy"));
-        GESR_TRY(hip_check(ctx, hipEventRecord(ctx->m_read, strm), "M event"));
+        GESR_TRY(hip_check(ctx, hipEventRecord(ctx->slot.read, strm), "M event"));
     } else if (wait) {
         uint32_t m = 0;
         GESR_TRY(hip_check(ctx, hipMemcpyAsync(&m, bins->counters, sizeof m, hipMemcpyDeviceToHost, strm), "M copy"));
@@ -551,8 +612,9 @@ gesr_status bin_impl(gesr_ctx* ctx, const gesr_proj* proj, const gesr_camera* ca
     GESR_TRY(hip_check(ctx, launch_tile_lists(tl, strm), "tile list starts"));
     GESR_TRY(hip_check(ctx, launch_tile_scatter(l2, strm), "tile lists"));
     if (later) {
-        GESR_TRY(hip_check(ctx, hipEventSynchronize(ctx->m_read), "M sync"));
-        const gesr_status e = check_m(*ctx->m_host);
+        GESR_TRY(hip_check(ctx, hipEventSynchronize(ctx->slot.read), "M sync"));
+        ctx->slot_busy = false;
+        const gesr_status e = check_m(*ctx->slot.host);
         if (e != GESR_OK) {  // nothing writes the caller's buffers after a refusal
             (void)hipStreamSynchronize(strm);
             return e;

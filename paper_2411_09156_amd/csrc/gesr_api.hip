@@ -238,7 +238,8 @@ struct BinScratch {
     uint32_t *d_keys_a, *d_vals_a, *d_keys_b, *d_vals_b;  // (view, depth) sort, [V*n]
     uint32_t *rowlist, *rowcols;                          // row lists and their columns, [m_cap]
     uint2* srect;                                         // rectangles in (view, depth) order, [V*n]
-    float4* sell;                                         // footprint ellipses in that order, [2 V*n]
+    float4* sell;                                         // footprint ellipses in that order, [2 V*n];
+                                                          //   the depth sort's counts before them
     uint32_t *row_count, *row_start;                      // [total rows]
     uint32_t* chunk_off;                                  // [segments + 1]
     uint32_t* mat;                                        // per-chunk bucket counts
@@ -272,7 +273,8 @@ BinScratch carve(void* base, const Geometry& g, const DevCams& dc, int n, uint64
     s.rowlist = take(m_cap);
     s.rowcols = take(m_cap);
     s.srect = reinterpret_cast<uint2*>(take(2 * vn1));
-    s.sell = reinterpret_cast<float4*>(take(8 * vn1));
+    const uint64_t depth_hist = depth_sort_hist_words((uint32_t)n, (uint32_t)dc.V);  // (at most 2 per pair)
+    s.sell = reinterpret_cast<float4*>(take(std::max(8 * vn1, depth_hist)));
     s.row_count = take(g.total_rows + 1);
     s.row_start = take(g.total_rows + 1);
     s.chunk_off = take(nseg);
@@ -288,7 +290,8 @@ BinScratch carve(void* base, const Geometry& g, const DevCams& dc, int n, uint64
     const uint64_t maxcount = std::max(vn1, T1);
     const uint64_t hist = 256ull * ceil_div(maxcount, SORT_TILE);
     s.block_hist = take(hist);
-    const uint64_t scan_items = std::max(std::max(hist, vn1), std::max(T1, std::max(g.total_rows + 1, nseg)));
+    const uint64_t scan_items =
+        std::max({hist, depth_hist, vn1, T1, (uint64_t)g.total_rows + 1, nseg});
     s.scan_partials = take(ceil_div(scan_items, SCAN_TILE) + 64);
     s.bytes = off;
     return s;

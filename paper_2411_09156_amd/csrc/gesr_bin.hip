@@ -1293,6 +1293,19 @@ hipError_t radix_sort(const uint32_t* keys_in, const uint32_t* vals_in, uint64_t
     return hipSuccess;
 }
 
+// Keys per block of 256 threads: as few as keep a view's rows of counts within what a
+// block sums by itself (more blocks in flight), 4,096 otherwise.
+static uint32_t depth_items(uint32_t n) {
+    return n <= 1024u * DEPTH_INLINE_MAX ? 4u : (n <= 2048u * DEPTH_INLINE_MAX ? 8u : 16u);
+}
+static uint32_t depth_blocks(uint32_t n) {  // per view
+    const uint32_t keys = 256u * depth_items(n);
+    return (n + keys - 1) / keys;
+}
+uint64_t depth_sort_hist_words(uint32_t n, uint32_t V) {
+    return n <= DEPTH_SORT_SMALL ? 0u : (uint64_t)V * depth_blocks(n) * 256u;
+}
+
 hipError_t depth_sort(const uint32_t* keys, uint32_t n, uint32_t V, const SortBuffers& b, const float* rec,
                       uint32_t** order, uint2* rect, float4* ell, hipStream_t stream) {
     *order = b.vals_b;
@@ -1304,12 +1317,10 @@ hipError_t depth_sort(const uint32_t* keys, uint32_t n, uint32_t V, const SortBu
         else hipLaunchKernelGGL(k_depth_sort_small<4>, grid, block, 0, stream, keys, n, b.vals_b, rec, rect, ell);
         return hipGetLastError();
     }
-    // keys per block: as few as keep a view's rows of counts within what a block sums
-    // by itself (more blocks in flight), 4,096 otherwise
-    const int items = n <= 1024u * DEPTH_INLINE_MAX ? 4 : (n <= 2048u * DEPTH_INLINE_MAX ? 8 : 16);
+    const uint32_t items = depth_items(n);
     DepthPass a;
     a.n = n;
-    a.bpv = (n + 256u * items - 1) / (256u * items);
+    a.bpv = depth_blocks(n);
     a.hist = b.block_hist;
     for (int p = 0; p < 4; ++p) {
         a.keys_in = p == 0 ? keys : (p & 1 ? b.keys_a : b.keys_b);
@@ -1326,7 +1337,6 @@ hipError_t depth_sort(const uint32_t* keys, uint32_t n, uint32_t V, const SortBu
     }
     return hipSuccess;
 }
-uint64_t depth_sort_hist_words(uint64_t n, uint64_t V) { return n <= DEPTH_SORT_SMALL ? 0u : V * 256u * ((n + 1023) / 1024); }
 
 hipError_t launch_gather_rects(const uint32_t* order, const float* rec, uint64_t count, uint2* out, float4* ell,
                                const uint32_t* skip, hipStream_t stream) {

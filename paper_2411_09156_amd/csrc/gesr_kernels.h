@@ -146,12 +146,11 @@ int radix_passes(int key_bits, int radix_bits);
 // Pairs in (view, depth key, pair) order: *order (one of b's value buffers) gets the
 // [V * n] pair indices.  Views of at most DEPTH_SORT_SMALL pairs are sorted in LDS, which
 // also writes what launch_gather_rects would (rect, ell).  keys_a, vals_a, keys_b, vals_b: [V * n]; b.block_hist:
-// depth_sort_hist_words words; b.scan_partials as for a scan of 256 V ceil(n / 4096)
-// values.
+// depth_sort_hist_words words; b.scan_partials as for a scan of as many values.
 constexpr uint32_t DEPTH_SORT_SMALL = 4096;
 hipError_t depth_sort(const uint32_t* keys, uint32_t n, uint32_t V, const SortBuffers& b, const float* rec,
                       uint32_t** order, uint2* rect, float4* ell, hipStream_t stream);
-uint64_t depth_sort_hist_words(uint64_t n, uint64_t V);
+uint64_t depth_sort_hist_words(uint32_t n, uint32_t V);
 
 // Binning helper kernels.
 // out[k] = the rectangle in pair order[k]'s record (x = 0xFFFFFFFF when the pair touches no tile);

@@ -304,8 +304,10 @@ __global__ __launch_bounds__(TW * TH) void k_render_fwd(RenderArgs a) {
     }
 }
 
+// 32x32: at most 64 registers, so that a CU holds two workgroups of 16 waves (200,000
+// splats, two views of 1600x1064: 931 us; one workgroup, with 94 registers, 1,365).
 template <int TW, int TH, int BATCH>
-__global__ __launch_bounds__(TW * TH) void k_render_bwd(RenderArgs a) {
+__global__ __launch_bounds__(TW * TH, TW * TH == 1024 ? 8 : 1) void k_render_bwd(RenderArgs a) {
     constexpr int NT = TW * TH;
     constexpr int NW = NT / 64;
     constexpr int NP = GESR_PARTIAL_FLOATS;

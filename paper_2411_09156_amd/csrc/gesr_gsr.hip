@@ -510,9 +510,34 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
     const bool in = p < (uint32_t)a.n;
     const uint32_t j = a.order[in ? p : 0u];
     const int K = a.k;
+    const bool on = in && (a.mask == nullptr || a.mask[j] != 0);
+    const bool with_part = a.partials != nullptr;
+    if (in && !on) *reinterpret_cast<float4*>(a.sample_out + (size_t)j * 4) = make_float4(0.f, 0.f, -1.f, 0.f);
+    const uint32_t* row = a.knn + (size_t)j * K;
+    // A wave without a sample that is on writes its zero records and ends; the other
+    // waves' lanes that are off take no neighbours, so that their frames are not gathered
+    // (500,000 samples: all off 34 us, with gradients 362; 114 and 434 when they went
+    // through the passes; a tenth on at random 76 us without gradients, 114).
+    if (__ballot(on) == 0ull) {
+        if (with_part)
+            for (int s = 0; s < K; ++s) {
+                const uint32_t slot = in && row[s] < (uint32_t)a.n ? a.inv_slot[(size_t)p * K + s] : 0xFFFFFFFFu;
+                const uint4 to = quad_all(slot);
+                const auto zero = [&](uint32_t t) {
+                    if (t != 0xFFFFFFFFu)
+                        __builtin_nontemporal_store(f32x4{0.f, 0.f, 0.f, 0.f},
+                                                    reinterpret_cast<f32x4*>(a.partials + (size_t)t * GSR_PARTIAL_STRIDE) +
+                                                        (threadIdx.x & 3u));
+                };
+                zero(to.x);
+                zero(to.y);
+                zero(to.z);
+                zero(to.w);
+            }
+        return;
+    }
     {
-        const uint32_t* row = a.knn + (size_t)j * K;
-        const uint32_t none = in ? 0u : 0xFFFFFFFFu;
+        const uint32_t none = on ? 0u : 0xFFFFFFFFu;
 #pragma unroll 8
         for (int s = 0; s < K; ++s) s_nb[s][threadIdx.x] = row[s] | none;
     }
@@ -522,18 +547,11 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
 #define quad_at(s) (*reinterpret_cast<const uint4*>(&s_nb[s][threadIdx.x & ~3u]))
     f32x4* stage = s_rec + (threadIdx.x & ~63u) * 4u;
     const uint32_t last = (uint32_t)a.n - 1u;
-    const bool with_part = a.partials != nullptr;
-    const bool on = in && (a.mask == nullptr || a.mask[j] != 0);
-    if (in && !on) {
-        a.sample_out[(size_t)j * 4 + 0] = 0.f;
-        a.sample_out[(size_t)j * 4 + 1] = 0.f;
-        a.sample_out[(size_t)j * 4 + 2] = -1.f;
-        a.sample_out[(size_t)j * 4 + 3] = 0.f;
-    }
     const float kappa = a.kappa;
-    const GFrame f0 = load_gframe(a.frames, j, a.rho);
+    const uint32_t jf = on ? j : 0u;
+    const GFrame f0 = load_gframe(a.frames, jf, a.rho);
     float xi[3];
-    for (int c = 0; c < 3; ++c) xi[c] = a.xi[(size_t)c * a.n + j];
+    for (int c = 0; c < 3; ++c) xi[c] = a.xi[(size_t)c * a.n + jf];
     // the sample x = mu_0 + d0, d0 = R_0 diag(sig_0) xi, kept as the pair
     float d0[3];
     for (int r = 0; r < 3; ++r)
@@ -563,7 +581,7 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
         }
     }
     // SDF terms of g* (Eq. 10-13)
-    const GFrame fg = load_gframe(a.frames, on ? nb_at(gs) : j, a.rho);
+    const GFrame fg = load_gframe(a.frames, on ? nb_at(gs) : jf, a.rho);
     int ks = 0;
     if (fg.sig[1] < fg.sig[ks]) ks = 1;
     if (fg.sig[2] < fg.sig[ks]) ks = 2;
@@ -636,8 +654,9 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
         if (s > 0) next.load(a.frames, quad_at(s - 1), last);
         // the partial of slot s goes to record inv_slot[p * k + s]: each splat's
         // records end up contiguous, in inverse-list order (padding slots have none, and
-        // their frame's terms stay out of the sample point's gradient)
-        const bool valid = i < (uint32_t)a.n;
+        // their frame's terms stay out of the sample point's gradient); a sample that is off
+        // leaves zeros
+        const bool valid = i < (uint32_t)a.n || (in && !on && row[s] < (uint32_t)a.n);
         const uint32_t slot = valid ? a.inv_slot[(size_t)p * K + s] : 0xFFFFFFFFu;
         const Term t = eval_term(f, f0.mu, d0, kappa);
         // b = diag(1/sig) R^T u, scaled by gmax like u

@@ -162,17 +162,27 @@ __device__ __forceinline__ float ray_sum(float x) {
 }
 
 // Four waves share a group of eight rays.  Pass 1 (an exact maximum) takes every
-// fourth set of list entries per wave; in pass 2 each wave takes a quarter of the
-// samples over the whole list, which leaves every sample's sum in its former order;
-// pass 3 runs on the first wave.  65,536 rays of 32 samples on 100k shell splats (1,300
-// list entries a ray, up to 5,300): 3.5 ms with one wave per group and a ray's lanes
-// side by side, 3.1 ms with one wave and the lanes of an entry side by side, 2.5 ms
-// with two waves, 2.4 ms with four (a quarter of the registers for samples, and the
-// longest lists end sooner).  FULL: all kMaxSamples samples, as straight-line code.
+// fourth set of list entries per wave; in pass 2 each wave takes two of the rays over
+// the whole list, a quarter of their samples a lane, so that an entry of a ray is asked
+// for by one wave and by neighbouring lanes, and every sample's sum keeps its order;
+// pass 3 runs on the first wave.  Bound by the gathers of entries' records and frames.
+// 30,000 rays of 32 samples, not grouped by tile, on a shell of 100k splats: 2.6 ms (4.6
+// with all eight rays and a quarter of the samples a wave, where each wave gathers every
+// ray's entries, 3.6 with one wave); 65,536 rays grouped by tile on 20 shells of 100k
+// splats in all (1,300 list entries a ray, up to 5,300): 2.19 ms (2.33 and 3.5).  FULL:
+// all kMaxSamples samples, as straight-line code.
 constexpr int kSurfWaves = 4, kSurfPart = kMaxSamples / kSurfWaves;
+
+// What passes 2 and 3 need of a ray, in LDS: pass 2 takes other rays than the lane's own,
+// whose values would be held beside them.
+struct SurfRay {
+    float x0[3], wd[3], fpx, fpy, s0, step, t0;
+    uint32_t r0, r1, pair0;
+};
 
 template <bool FULL>
 __global__ __launch_bounds__(64 * kSurfWaves) void k_surface_points(SurfaceArgs A) {
+    __shared__ SurfRay sRay[kRaysPerWave];
     __shared__ float sPart[64][kMaxSamples + 1];
     __shared__ float sDen[kRaysPerWave][kMaxSamples];
     __shared__ float sBest[kSurfWaves][kRaysPerWave];
@@ -271,26 +281,37 @@ __global__ __launch_bounds__(64 * kSurfWaves) void k_surface_points(SurfaceArgs 
     }
     if (!live) rg = make_uint2(0u, 0u);
     const int K = FULL ? kMaxSamples : A.n_samples;
-    const float step = 2.0f * A.span * sg / (float)(K - 1), s0 = -A.span * sg;
+    if (threadIdx.x == slot) {
+        const float step = 2.0f * A.span * sg / (float)(K - 1), s0 = -A.span * sg;
+        sRay[slot] = SurfRay{{x0[0], x0[1], x0[2]}, {wd[0], wd[1], wd[2]}, fpx, fpy, s0, step, t0, rg.x, rg.y, pair0};
+    }
+    __syncthreads();
 
-    // pass 2: partial densities of this wave's samples
-    const int j0 = (int)wave * kSurfPart;
-    float part[kSurfPart];
+    // pass 2: partial densities.  A ray's samples are shared by `parts` lanes an entry, at
+    // most kSurfPart each, so that a wave takes 8 / parts rays (waves past the eighth ray
+    // none): lane u2 * 8 + ray * parts + part, over the list entries u2, u2 + 8, ...
+    const uint32_t parts_log = FULL || K > 2 * kSurfPart ? 2u : (K > kSurfPart ? 1u : 0u), parts = 1u << parts_log;
+    const uint32_t u2 = lane >> 3, slot2 = ((wave << 3) + (lane & 7u)) >> parts_log;
+    if (wave < parts) {
+        const int per = FULL ? kSurfPart : (K + (int)parts - 1) >> parts_log, j0 = (int)(lane & (parts - 1u)) * per;
+        const SurfRay r = sRay[slot2];
+        float part[kSurfPart];
 #pragma unroll
-    for (int k = 0; k < kSurfPart; ++k) part[k] = 0.f;
-    if (FULL || j0 < K)
-        for_candidates<kLanesPerRay>(A, rg, pair0, u, fpx, fpy, [&](const Frame& fr, uint32_t) {
+        for (int k = 0; k < kSurfPart; ++k) part[k] = 0.f;
+        for_candidates<kLanesPerRay>(A, make_uint2(r.r0, r.r1), r.pair0, u2, r.fpx, r.fpy, [&](const Frame& fr, uint32_t) {
             Affine f;
-            frame_affine(fr, x0, wd, f);
+            frame_affine(fr, r.x0, r.wd, f);
 #pragma unroll
             for (int j = 0; j < kSurfPart; ++j)
-                if (FULL || j0 + j < K) part[j] += affine_term(f, fmaf((float)(j0 + j), step, s0), nk);
+                if (FULL || j < per) part[j] += affine_term(f, fmaf((float)(j0 + j), r.step, r.s0), nk);
         });
 #pragma unroll
-    for (int j = 0; j < kSurfPart; ++j) sPart[lane][j0 + j] = part[j];
+        for (int j = 0; j < kSurfPart; ++j)
+            if (FULL || j < per) sPart[u2 * kRaysPerWave + slot2][j0 + j] = part[j];
+    }
     __syncthreads();
     // densities: sample j of the ray summed over its lanes in lane order
-    for (int j = j0 + (int)u; j < min(j0 + kSurfPart, K); j += kLanesPerRay) {
+    for (int j = (int)(wave * kLanesPerRay + u); j < K; j += kSurfWaves * kLanesPerRay) {
         float d = 0.f;
         for (int l = 0; l < kLanesPerRay; ++l) d += sPart[l * kRaysPerWave + slot][j];
         sDen[slot][j] = d;
@@ -305,17 +326,18 @@ __global__ __launch_bounds__(64 * kSurfWaves) void k_surface_points(SurfaceArgs 
                 break;
             }
     live = live && kc >= 0;
+    const SurfRay r = sRay[slot];
     float ss = 0.f;
     if (live) {
         const float d0 = sDen[slot][kc], d1 = sDen[slot][kc + 1];
-        ss = fmaf((float)kc, step, s0) + (A.level - d0) / (d1 - d0) * step;
+        ss = fmaf((float)kc, r.step, r.s0) + (A.level - d0) / (d1 - d0) * r.step;
     }
-    if (!live) rg = make_uint2(0u, 0u);
 
     // pass 3: density gradient at x0 + ss w
     float gd[3] = {0.f, 0.f, 0.f};
-    const float xs[3] = {x0[0] + ss * wd[0], x0[1] + ss * wd[1], x0[2] + ss * wd[2]};
-    for_candidates<kLanesPerRay>(A, rg, pair0, u, fpx, fpy, [&](const Frame& fr, uint32_t) {
+    const float xs[3] = {r.x0[0] + ss * r.wd[0], r.x0[1] + ss * r.wd[1], r.x0[2] + ss * r.wd[2]};
+    for_candidates<kLanesPerRay>(A, live ? make_uint2(r.r0, r.r1) : make_uint2(0u, 0u), r.pair0, u, r.fpx, r.fpy,
+                                 [&](const Frame& fr, uint32_t) {
         const float d[3] = {xs[0] - fr.mu[0], xs[1] - fr.mu[1], xs[2] - fr.mu[2]};
         float y[3], m2 = 0.f;
 #pragma unroll
@@ -338,7 +360,7 @@ __global__ __launch_bounds__(64 * kSurfWaves) void k_surface_points(SurfaceArgs 
     const float gn = sqrtf(gd[0] * gd[0] + gd[1] * gd[1] + gd[2] * gd[2]);
     if (live && gn > 0.f && u == 0) {
         reinterpret_cast<float4*>(A.points)[ray] = make_float4(xs[0], xs[1], xs[2], 1.0f);
-        reinterpret_cast<float4*>(A.normals)[ray] = make_float4(-gd[0] / gn, -gd[1] / gn, -gd[2] / gn, t0 + ss);
+        reinterpret_cast<float4*>(A.normals)[ray] = make_float4(-gd[0] / gn, -gd[1] / gn, -gd[2] / gn, r.t0 + ss);
     }
 }
 

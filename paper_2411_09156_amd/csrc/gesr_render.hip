@@ -1259,21 +1259,42 @@ uint32_t fwd_split_tiles(uint32_t n_items) { return n_items <= 8192u ? n_items :
 // The 16x16 adjoint's tiles with eight waves each: all of them up to 2,048, where four
 // would leave SIMDs idle or with one serial chain each (147 -> 92 us on 64 tiles, 236
 // -> 174 on 1,024, 214 -> 207 on 1,936; 2,500 tiles would take 262 us instead of 234,
-// 3,024 321 instead of 231).  With four waves each: all of them up to 4,096 (one wave
-// takes 300 ns per list position and the chip's wave slots would be filled once or
-// less: 360 -> 218 us on 3,024; 6,048 tiles would take 475 us instead of 410), the
-// worklist's first 256 up to 32,768 (2,000 -> 1,826 us on 24,842 tiles of views at 1/8
-// .. 1 of 1600x1064, where the longest list alone took the whole time, 510 -> 346 us on
-// 8,487, 403 against 410 us on 6,048).  Above that a wave slot takes six tiles or more
-// and no list sets the end: one-wave workgroups, whose slots free up singly, take 1,790
-// us on 33,948 tiles and 5.55 ms on 130,560 against 1,890 us and 5.77 ms with four
-// waves to a workgroup.
+// 3,024 321 instead of 231).
 // Rounds of eight records, half the barriers for twice the LDS and so one workgroup on
 // a CU, pay up to 512 tiles (112 -> 92 us on 64, 190 -> 161 on 256, 109 -> 93 on 484;
 // 179 -> 197 on 1,024).
+// With four waves each: all of them up to 5,500, where one-wave tiles would fill the
+// chip's wave slots about once and the kernel would last as long as its longest list
+// (one wave takes 300 ns per list position): 360 -> 218 us on 3,024; 198 -> 134 on 4,347,
+// 196 -> 162 on 5,292; 185 -> 186 on 5,922, 194 -> 202 on 6,700.  Beyond, the worklist's
+// first 256 (4,725 .. 8,487 tiles of one view: 2 to 10% less than one wave for all),
+// while no other tile hides the longest lists:
+//  - Views of one resolution up to 10,240 tiles, with the extended channels 7,168 (two
+//    tiles a wave slot or less).  Workgroups of four one-wave tiles free their slots
+//    together, which costs 2 to 7% where lists are even: 13,400 tiles 320 us (one-wave
+//    workgroups 307), 20,100 465 (449), 26,800 572 (557), with channels 373 (368), 602
+//    (562), 741 (702); 10,032 tiles 250 and 284 us (245, 318), with channels 332 and 367
+//    (318, 362).
+//  - Views of which one has four times another's pixels up to 32,768, with the channels
+//    28,672.  The splats share fewer tiles in the smaller one, so its lists are longer by
+//    that factor, and one of them sets the end: 11,442 tiles of views at 1/8 .. 3/4 of
+//    1600x1064 286 us and 693 (535, 1,160), 24,842 at 1/8 .. 1 469 and 655 (565, 1,118),
+//    with channels 608 and 860 (667, 1,344); 31,553 of 1957x1091 620 and 827 (596, 800 to
+//    844), with channels 812 and 1,097 (756, 1,012 to 1,035).
 constexpr uint32_t kBwdPipeMax = 2048u, kBwdPipe8Max = 512u;
-constexpr uint32_t kBwdMixedMax = 32768u;
-uint32_t bwd_split_tiles(uint32_t n_items) { return n_items <= 4096u ? n_items : 256u; }
+constexpr uint32_t kBwdSplitAllMax = 5500u, kBwdSplit = 256u;
+constexpr uint32_t kBwdMixedMax = 10240u, kBwdMixedExtMax = 7168u;
+constexpr uint32_t kBwdMixedSkewMax = 32768u, kBwdMixedSkewExtMax = 28672u;
+
+bool views_skewed(const DevCams& c) {
+    uint64_t lo = ~0ull, hi = 0;
+    for (int v = 0; v < c.V; ++v) {
+        const uint64_t pixels = (uint64_t)c.v[v].W * (uint64_t)c.v[v].H;
+        lo = pixels < lo ? pixels : lo;
+        hi = pixels > hi ? pixels : hi;
+    }
+    return hi >= 4u * lo;
+}
 
 }  // namespace
 
@@ -1326,14 +1347,16 @@ hipError_t launch_render_bwd(const RenderArgs& a, int tw, int th, int batch, hip
             }
             return hipGetLastError();
         }
-        if (a.n_items > kBwdMixedMax) {
+        const uint32_t mixed_max = views_skewed(a.cams) ? (ext ? kBwdMixedSkewExtMax : kBwdMixedSkewMax)
+                                                        : (ext ? kBwdMixedExtMax : kBwdMixedMax);
+        if (a.n_items > mixed_max) {
             const dim3 grid(a.n_items), block(64);
             if (ext) hipLaunchKernelGGL((k_render_bwd16_wave<true>), grid, block, 0, s, a);
             else hipLaunchKernelGGL((k_render_bwd16_wave<false>), grid, block, 0, s, a);
             return hipGetLastError();
         }
         RenderArgs b = a;
-        b.n_split = bwd_split_tiles(a.n_items);
+        b.n_split = a.n_items <= kBwdSplitAllMax ? a.n_items : kBwdSplit;
         const dim3 grid(b.n_split + (a.n_items - b.n_split + 3) / 4), block(256);
         if (ext) hipLaunchKernelGGL((k_render_bwd16<true>), grid, block, 0, s, b);
         else hipLaunchKernelGGL((k_render_bwd16<false>), grid, block, 0, s, b);

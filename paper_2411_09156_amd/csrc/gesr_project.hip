@@ -15,6 +15,8 @@
 // written by the backward renderer (atomic-free, k_seg_reduce), then the chain
 // rule through the projection, accumulated over views in ascending order.
 
+#include <algorithm>
+
 #include "gesr_device.h"
 #include "gesr_kernels.h"
 
@@ -283,7 +285,9 @@ __global__ __launch_bounds__(256) void k_project(ProjectArgs a) {
     const float L = logf(op / st.alpha_min) / st.kappa;
     const float qmax = exp2f(log2f(L) * (2.0f / beta)) * (1.0f + 1.0f / 1024.0f);
 
-    for (int v = 0; v < a.cams.V; ++v) {
+    // this row of workgroups' share of the views
+    const int share = (a.cams.V + (int)gridDim.y - 1) / (int)gridDim.y, v0 = (int)blockIdx.y * share;
+    for (int v = v0; v < min(v0 + share, a.cams.V); ++v) {
         const DevView& w = a.cams.v[v];
         const size_t vi = (size_t)v * n + i;
         ViewProj vp;
@@ -744,7 +748,11 @@ __global__ __launch_bounds__(256) void k_seg_reduce(SegReduceArgs a) {
 
 hipError_t launch_project(const ProjectArgs& a, int sh_degree, hipStream_t stream) {
     if (a.n == 0) return hipSuccess;
-    dim3 grid((a.n + 255) / 256), block(256);
+    // Few splats: the views are shared by rows of workgroups, up to five for each compute
+    // unit in all, since a workgroup takes its views one after the other (1,000 splats, 32
+    // views: 16 us, 53 with one row; 20,000: 19, 55).
+    const unsigned groups = ((unsigned)a.n + 255u) / 256u, rows = std::max(1u, std::min((unsigned)a.cams.V, 1280u / groups));
+    dim3 grid(groups, rows), block(256);
     switch (sh_degree) {
         case 0: hipLaunchKernelGGL(k_project<0>, grid, block, 0, stream, a); break;
         case 1: hipLaunchKernelGGL(k_project<1>, grid, block, 0, stream, a); break;

@@ -1267,24 +1267,23 @@ uint32_t fwd_split_tiles(uint32_t n_items) { return n_items <= 8192u ? n_items :
 // chip's wave slots about once and the kernel would last as long as its longest list
 // (one wave takes 300 ns per list position): 360 -> 218 us on 3,024; 198 -> 134 on 4,347,
 // 196 -> 162 on 5,292; 185 -> 186 on 5,922, 194 -> 202 on 6,700.  Beyond, the worklist's
-// first 256 (4,725 .. 8,487 tiles of one view: 2 to 10% less than one wave for all),
-// while no other tile hides the longest lists:
-//  - Views of one resolution up to 10,240 tiles, with the extended channels 7,168 (two
-//    tiles a wave slot or less).  Workgroups of four one-wave tiles free their slots
-//    together, which costs 2 to 7% where lists are even: 13,400 tiles 320 us (one-wave
-//    workgroups 307), 20,100 465 (449), 26,800 572 (557), with channels 373 (368), 602
-//    (562), 741 (702); 10,032 tiles 250 and 284 us (245, 318), with channels 332 and 367
-//    (318, 362).
-//  - Views of which one has four times another's pixels up to 32,768, with the channels
-//    28,672.  The splats share fewer tiles in the smaller one, so its lists are longer by
-//    that factor, and one of them sets the end: 11,442 tiles of views at 1/8 .. 3/4 of
-//    1600x1064 286 us and 693 (535, 1,160), 24,842 at 1/8 .. 1 469 and 655 (565, 1,118),
-//    with channels 608 and 860 (667, 1,344); 31,553 of 1957x1091 620 and 827 (596, 800 to
-//    844), with channels 812 and 1,097 (756, 1,012 to 1,035).
+// first 256 as long as another tile does not hide the longest lists; the others of a
+// workgroup's four waves then take a tile each, and free their slots together, which
+// costs 2 to 5% on even lists (with the channels 4 to 7%):
+//  - Up to 32,768 tiles: 11,442 tiles of views at 1/8 .. 3/4 of 1600x1064 286 us and 693
+//    (one-wave workgroups 535, 1,160), 24,842 at 1/8 .. 1 469 and 655 (565, 1,118); even
+//    views 9,500 tiles 312 (316), 15,200 of 400x300 349 (376) and of 800x600 453 (440),
+//    20,100 572 (562), 30,400 842 (809).  Above, 33,948 tiles take 1,890 us and 130,560
+//    5.77 ms, one-wave workgroups 1,790 and 5.55.
+//  - With the channels up to 28,672 where one view has four times another's pixels: the
+//    splats share fewer tiles in the smaller one, so its lists are longer by that factor,
+//    and one of them sets the end (24,842 tiles 608 and 860 us, 667 and 1,344; 31,553 812
+//    and 1,097, 756 and 1,030).  Views of nearer resolution have no such lists: up to
+//    12,288 tiles (9,500 404 us, 467; 10,332 364, 377; 13,400 463, 443; 20,100 720, 681;
+//    30,400 1,097, 1,026).
 constexpr uint32_t kBwdPipeMax = 2048u, kBwdPipe8Max = 512u;
 constexpr uint32_t kBwdSplitAllMax = 5500u, kBwdSplit = 256u;
-constexpr uint32_t kBwdMixedMax = 10240u, kBwdMixedExtMax = 7168u;
-constexpr uint32_t kBwdMixedSkewMax = 32768u, kBwdMixedSkewExtMax = 28672u;
+constexpr uint32_t kBwdMixedMax = 32768u, kBwdMixedExtMax = 12288u, kBwdMixedExtSkewMax = 28672u;
 
 bool views_skewed(const DevCams& c) {
     uint64_t lo = ~0ull, hi = 0;
@@ -1347,8 +1346,8 @@ hipError_t launch_render_bwd(const RenderArgs& a, int tw, int th, int batch, hip
             }
             return hipGetLastError();
         }
-        const uint32_t mixed_max = views_skewed(a.cams) ? (ext ? kBwdMixedSkewExtMax : kBwdMixedSkewMax)
-                                                        : (ext ? kBwdMixedExtMax : kBwdMixedMax);
+        const uint32_t mixed_max =
+            !ext ? kBwdMixedMax : (views_skewed(a.cams) ? kBwdMixedExtSkewMax : kBwdMixedExtMax);
         if (a.n_items > mixed_max) {
             const dim3 grid(a.n_items), block(64);
             if (ext) hipLaunchKernelGGL((k_render_bwd16_wave<true>), grid, block, 0, s, a);

@@ -1,6 +1,6 @@
 """The 16x16 adjoint's ways of sharing tiles between 4,096 and 32,768 tiles: all tiles by
-four waves up to 5,500, then the longest ones, and one wave each above 10,240 tiles (7,168
-with the extended channels) where views are of one resolution.  A view's screen-space
+four waves up to 5,500, then the longest ones; with the extended channels one wave each
+above 12,288 tiles where no view has four times another's pixels.  A view's screen-space
 gradients are the same to the bit in batches on each side of these lines."""
 import numpy as np
 import pytest
@@ -11,9 +11,9 @@ from tests.gpu_util import log, splats_of
 pytestmark = pytest.mark.gpu
 
 W, H = 1100, 1000  # 4,347 tiles
-# views beside the first: none; one that brings the sum over 5,500, 7,168 and 10,240 tiles with
-# a resolution that stays within a factor of four; a small one besides
-BATCHES = [[], [(600, 600)], [(900, 800)], [(1200, 1000)], [(1500, 1100)], [(1500, 1100), (40, 30)]]
+# views beside the first: none; some that bring the sum over 5,500 and 12,288 tiles with
+# resolutions within a factor of four; a small one besides
+BATCHES = [[], [(600, 600)], [(1200, 1000)], [(1500, 1100), (900, 800)], [(1500, 1100), (900, 800), (40, 30)]]
 
 
 @pytest.mark.parametrize("channels", [False, True])
@@ -43,4 +43,4 @@ def test_rows_agree_across_the_lines(channels):
             ref = rows
             assert np.abs(ref).max() > 0
         np.testing.assert_array_equal(rows, ref, err_msg=str(extra))
-    assert tiles[0] <= 5500 < tiles[1] <= 7168 < tiles[2] <= 10240 and tiles[3] < tiles[4] and 10240 < tiles[4]
+    assert tiles[0] <= 5500 < tiles[1] < tiles[2] <= 12288 < tiles[3] < tiles[4] <= 28672

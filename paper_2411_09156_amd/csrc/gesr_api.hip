@@ -1391,10 +1391,10 @@ namespace {
 struct Candidate {
     int tw, th, variant, batch, radix;
 };
-// Renderer candidates (digit width 8), then digit widths for the best of them.
-constexpr Candidate kRenderCands[] = {{16, 16, 0, 64, 8},  {16, 16, 0, 32, 8}, {16, 16, 1, 64, 8},
-                                      {16, 16, 1, 128, 8}, {8, 8, 0, 64, 8},   {32, 16, 0, 64, 8},
-                                      {32, 16, 0, 128, 8}, {32, 32, 0, 64, 8}};
+// Renderer candidates (digit width 8), then digit widths for the best of them.  The 16x16
+// variant-0 renderers stage 64 records whatever the batch, so they are one candidate.
+constexpr Candidate kRenderCands[] = {{16, 16, 0, 64, 8}, {16, 16, 1, 64, 8},  {16, 16, 1, 128, 8}, {8, 8, 0, 64, 8},
+                                      {32, 16, 0, 64, 8}, {32, 16, 0, 128, 8}, {32, 32, 0, 64, 8}};
 constexpr int kNumRender = (int)(sizeof(kRenderCands) / sizeof(kRenderCands[0]));
 constexpr int kRadixCands[] = {7, 6, 5};
 constexpr int kNumCands = kNumRender + (int)(sizeof(kRadixCands) / sizeof(kRadixCands[0]));

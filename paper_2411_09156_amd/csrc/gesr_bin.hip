@@ -944,9 +944,7 @@ __global__ __launch_bounds__(IS_THREADS) __attribute__((amdgpu_waves_per_eu(8)))
                             bits &= bits - 1u;
                             wst[q++] = s_item_p[lane * 32u + k];
                         }
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
-                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                        wave_lds_fence();
                         const uint32_t dst = s_gb[b];
                         for (uint32_t j = lane; j < n_b; j += 64) {
                             if (dst + j < a.out_cap) {
@@ -954,9 +952,7 @@ __global__ __launch_bounds__(IS_THREADS) __attribute__((amdgpu_waves_per_eu(8)))
                                 if (a.out_keys) a.out_keys[dst + j] = key;
                             }
                         }
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
-                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                        wave_lds_fence();
                         continue;
                     }
                     while (bits != 0u) {

@@ -400,14 +400,6 @@ __global__ __launch_bounds__(TW * TH, TW * TH == 1024 ? 8 : 1) void k_render_bwd
     }
 }
 
-// Orders a wave's LDS writes before its own later reads of other lanes' data
-// (the waves of a workgroup run different tiles: no workgroup barrier).
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // One pixel of the forward traversal.  A terminated pixel (and one outside the
 // image) keeps its transmittance with the sign bit set: the sign then fails the
 // termination test of every later fragment, so no separate flag is carried.
@@ -500,7 +492,7 @@ __device__ __forceinline__ void fwd_wave_tile(const RenderArgs& a, uint32_t t, f
             sB[lane] = make_float4(nb.x, nb.y, 0.5f * nb.z, nb.w);
             sC[lane] = nc;
         }
-        wave_lds_sync();
+        wave_lds_fence();
         if (base + B < r1) fetch(base + B);
         const int cnt = (int)__builtin_amdgcn_readfirstlane(min<uint32_t>(B, r1 - base));
         uint32_t pos = in_vgpr(base - r0);
@@ -530,7 +522,7 @@ __device__ __forceinline__ void fwd_wave_tile(const RenderArgs& a, uint32_t t, f
                 blend<EXT>(p[q], al, ok, rc, rc.w, pos, st.t_min);
             }
         }
-        wave_lds_sync();
+        wave_lds_fence();
     }
     if (a.tile_work && lane == 0) a.tile_work[t] = stop - r0;
 #pragma unroll
@@ -633,7 +625,7 @@ __device__ __forceinline__ void fwd_quad_tile(const RenderArgs& a, uint32_t t, u
             sb[cnt] = make_float4(0.f, 0.f, 0.f, -1.f);
             if (EXT) sz[cnt] = 0.f;
         }
-        wave_lds_sync();
+        wave_lds_fence();
         vi = vi_n;
         fetch(base + 64 + lane, vi);
         vi_n = value_at(base + 128 + lane);
@@ -655,7 +647,7 @@ __device__ __forceinline__ void fwd_quad_tile(const RenderArgs& a, uint32_t t, u
                 blend<EXT>(p, al[u], ok[u], rc, EXT ? sz[j + u] : 0.f, __float_as_uint(rc.w), tmin);
             }
         }
-        wave_lds_sync();
+        wave_lds_fence();
     }
     if (a.tile_work) {
         if (lane == 0) s_stop[wave] = stop;
@@ -819,7 +811,7 @@ __device__ __forceinline__ void bwd_wave_tile(const RenderArgs& a, uint32_t t, B
             r.load(a, a.val_sorted[hi - 1u - lane]);
             r.store(a, s, lane, tp.tx, tp.ty);
         }
-        wave_lds_sync();
+        wave_lds_fence();
         for (uint32_t j = 0; j < cnt; ++j) {
             const uint32_t prel = hi - 1u - j - r0;  // 0-based list position
             const float4 ra = s.a[j];
@@ -849,11 +841,104 @@ __device__ __forceinline__ void bwd_wave_tile(const RenderArgs& a, uint32_t t, B
             if (__ballot(act) != 0ull) reduce_record(s, j, gr, gz, lane, slot);
             else if ((int)lane < (EXT ? NP + 1 : NP)) s.red[j][lane] = 0.f;
         }
-        wave_lds_sync();
+        wave_lds_fence();
         write_batch(a, s, lane, cnt);
-        wave_lds_sync();
+        wave_lds_fence();
         hi -= cnt;
     }
+}
+
+// The fragments' terms of a round of R records.
+template <uint32_t R>
+struct BwdTerms {
+    float4 v0[R][4][64];  // [record][quadrant][lane]: aT, dl, G, xl
+    float2 v1[R][4][64];  // tq, wq
+};
+
+// The batch's records that can reach the quadrant, a bit each: `left` list positions are
+// left, the quadrant's pixels composited the first wmax of the list.
+template <bool EXT>
+__device__ __forceinline__ uint64_t quad_records(const BwdStage<EXT>& s, uint32_t lane, uint32_t left, uint32_t wmax,
+                                                 float qx, float qy) {
+    bool can = false;
+    if (lane < left && left - 1u - lane < wmax) {
+        const float4 la = s.a[lane];
+        can = !quad_misses(la, s.b[lane], qx - la.x, (qx + 7.0f) - la.x, qy - la.y, (qy + 7.0f) - la.y);
+    }
+    return __ballot(can);
+}
+
+// Phase 1: the quadrant's pixel (px, py) past the round's records b + k, k the set bits of
+// m; `left` list positions were left at the batch's first record, nc of them are the pixel's.
+template <bool EXT, uint32_t R>
+__device__ __forceinline__ void quad_terms(const DevSettings& st, const BwdStage<EXT>& s, uint32_t b, uint32_t m,
+                                           uint32_t left, uint32_t nc, float px, float py, float amax, float nk,
+                                           const PixelUp& mine, PixelAdjoint& pa, uint32_t quad, uint32_t lane,
+                                           BwdTerms<R>& terms) {
+    constexpr uint32_t GRP = 2;  // records side by side
+    while (m != 0u) {
+        uint32_t k[GRP];
+        bool have[GRP];
+#pragma unroll
+        for (uint32_t u = 0; u < GRP; ++u) {  // past the last record: that one again, off
+            have[u] = m != 0u;
+            k[u] = have[u] ? (uint32_t)__builtin_ctz(m) : k[u > 0 ? u - 1 : 0];
+            m = have[u] ? m & (m - 1) : 0u;
+        }
+        Fragment f[GRP];
+        bool on[GRP];
+#pragma unroll
+        for (uint32_t u = 0; u < GRP; ++u) {
+            const float4 rb = s.b[b + k[u]];
+            const float qq = ges_q(s.a[b + k[u]], rb.x, px, py, f[u]);
+            on[u] = (int)(left - 1u - (b + k[u]) < nc) & (int)!(qq > rb.w) & (int)have[u];
+            // q = 1 where the fragment is not the pixel's: its terms are exact zeros
+            ges_alpha(on[u] ? qq : 1.0f, rb.z, rb.y, nk, amax, f[u]);
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < GRP; ++u) {
+            const float4 rc = s.c[b + k[u]];
+            float aT, dl;
+            pixel_step<EXT, false>(f[u], on[u], rc, EXT ? s.z[b + k[u]] : 0.0f, st, mine, pa, aT, dl);
+            if (have[u]) {
+                const FragmentTerms v = fragment_terms(f[u], rc.w, aT, dl);
+                terms.v0[k[u]][quad][lane] = make_float4(v.aT, v.dl, v.G, v.xl);
+                terms.v1[k[u]][quad][lane] = make_float2(v.tq, v.wq);
+            }
+        }
+    }
+}
+
+// Phase 2: the sums of the batch's record j, the round's k-th, over the whole tile.
+template <bool EXT, uint32_t R>
+__device__ __forceinline__ void tile_sums(BwdStage<EXT>& s, const BwdTerms<R>& terms, uint32_t j, uint32_t k,
+                                          const uint64_t (&live_of)[4], float pxb, float pyb, float c2,
+                                          const PixelUp (&up)[4], uint32_t lane, int slot) {
+    constexpr int NP = GESR_PARTIAL_FLOATS;
+    if (((live_of[0] | live_of[1] | live_of[2] | live_of[3]) >> j & 1u) == 0u) {
+        if ((int)lane < (EXT ? NP + 1 : NP)) s.red[j][lane] = 0.f;
+        return;
+    }
+    const float2 uv = make_float2(s.a[j].x, s.a[j].y);
+    float gr[NP], gz = 0.0f;
+    // all reads in flight together (a quadrant without the record holds stale terms: not added)
+    float4 v0[4];
+    float2 v1[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        v0[q] = terms.v0[k][q][lane];
+        v1[q] = terms.v1[k][q][lane];
+    }
+#pragma unroll
+    for (int i = 0; i < NP; i += 2) opaque_zero2(gr[i], gr[i + 1]);
+    if (EXT) gz = opaque_zero();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (!(live_of[q] >> j & 1u)) continue;
+        add_terms<EXT>(FragmentTerms{v0[q].x, v0[q].y, v0[q].z, v0[q].w, v1[q].x, v1[q].y},
+                       (pxb + (float)((q & 1) * 8)) - uv.x, (pyb + (float)((q >> 1) * 8)) - uv.y, c2, up[q], gr, gz);
+    }
+    reduce_record(s, j, gr, gz, lane, slot);
 }
 
 // Adjoint of one 16x16 tile by the four waves of a workgroup, with the sums of
@@ -869,8 +954,7 @@ __device__ __forceinline__ void bwd_wave_tile(const RenderArgs& a, uint32_t t, B
 template <bool EXT>
 struct BwdSplit {
     BwdStage<EXT> s;
-    float4 v0[4][4][64];  // [record][quadrant][lane]: aT, dl, G, xl
-    float2 v1[4][4][64];  // tq, wq
+    BwdTerms<4> terms;
     uint64_t live[4];
     uint32_t maxnc[4];
 };
@@ -878,7 +962,7 @@ struct BwdSplit {
 template <bool EXT>
 __device__ __forceinline__ bool bwd_split_tile(const RenderArgs& a, uint32_t t, uint32_t wave, BwdSplit<EXT>& S) {
     constexpr int NP = GESR_PARTIAL_FLOATS;
-    constexpr int R = 4, GRP = 2;  // records per round, and side by side in phase 1
+    constexpr uint32_t R = 4;  // records per round
     BwdStage<EXT>& s = S.s;
     const DevSettings& st = a.st;
     const float amax = st.alpha_max, nk = in_vgpr(st.neg_kappa_log2e);
@@ -935,77 +1019,16 @@ __device__ __forceinline__ bool bwd_split_tile(const RenderArgs& a, uint32_t t, 
             if (kBwdBatch + lane < hi - r0) r.load(a, vi);
             vi = value_at(2 * kBwdBatch);
         }
-        bool can = false;
-        if (lane < cnt && hi - 1u - lane - r0 < wmax) {
-            const float4 la = s.a[lane];
-            can = !quad_misses(la, s.b[lane], qx - la.x, (qx + 7.0f) - la.x, qy - la.y, (qy + 7.0f) - la.y);
-        }
-        const uint64_t live = __ballot(can);
+        const uint64_t live = quad_records(s, lane, hi - r0, wmax, qx, qy);
         if (lane == 0) S.live[wave] = live;
         __syncthreads();
         const uint64_t own = S.live[lane & 3];
         const uint64_t live_of[4] = {read_lane(own, 0), read_lane(own, 1), read_lane(own, 2), read_lane(own, 3)};
         for (uint32_t b = 0; b < cnt; b += R) {
-            uint32_t m = (uint32_t)(live >> b) & ((1u << R) - 1u);
-            while (m != 0u) {
-                uint32_t k[GRP];
-                bool have[GRP];
-#pragma unroll
-                for (int u = 0; u < GRP; ++u) {  // past the last record: that one again, off
-                    have[u] = m != 0u;
-                    k[u] = have[u] ? (uint32_t)__builtin_ctz(m) : k[u > 0 ? u - 1 : 0];
-                    m = have[u] ? m & (m - 1) : 0u;
-                }
-                Fragment f[GRP];
-                bool on[GRP];
-#pragma unroll
-                for (int u = 0; u < GRP; ++u) {
-                    const float4 rb = s.b[b + k[u]];
-                    const float qq = ges_q(s.a[b + k[u]], rb.x, px, py, f[u]);
-                    on[u] = (int)(hi - 1u - (b + k[u]) - r0 < nc) & (int)!(qq > rb.w) & (int)have[u];
-                    // q = 1 where the fragment is not the pixel's: its terms are exact zeros
-                    ges_alpha(on[u] ? qq : 1.0f, rb.z, rb.y, nk, amax, f[u]);
-                }
-#pragma unroll
-                for (int u = 0; u < GRP; ++u) {
-                    const float4 rc = s.c[b + k[u]];
-                    float aT, dl;
-                    pixel_step<EXT, false>(f[u], on[u], rc, EXT ? s.z[b + k[u]] : 0.0f, st, mine, pa, aT, dl);
-                    if (have[u]) {
-                        const FragmentTerms v = fragment_terms(f[u], rc.w, aT, dl);
-                        S.v0[k[u]][wave][lane] = make_float4(v.aT, v.dl, v.G, v.xl);
-                        S.v1[k[u]][wave][lane] = make_float2(v.tq, v.wq);
-                    }
-                }
-            }
+            quad_terms<EXT, R>(st, s, b, (uint32_t)(live >> b) & ((1u << R) - 1u), hi - r0, nc, px, py, amax, nk, mine, pa,
+                               wave, lane, S.terms);
             __syncthreads();
-            const uint32_t j = b + wave;
-            if (j >= cnt) {
-            } else if (((live_of[0] | live_of[1] | live_of[2] | live_of[3]) >> j & 1u) == 0u) {
-                if ((int)lane < (EXT ? NP + 1 : NP)) s.red[j][lane] = 0.f;
-            } else {
-                const float2 uv = make_float2(s.a[j].x, s.a[j].y);
-                float gr[NP], gz = 0.0f;
-                // all reads in flight together (a quadrant without the record holds stale terms: not added)
-                float4 v0[4];
-                float2 v1[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    v0[q] = S.v0[wave][q][lane];
-                    v1[q] = S.v1[wave][q][lane];
-                }
-#pragma unroll
-                for (int i = 0; i < NP; i += 2) opaque_zero2(gr[i], gr[i + 1]);
-                if (EXT) gz = opaque_zero();
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (!(live_of[q] >> j & 1u)) continue;
-                    add_terms<EXT>(FragmentTerms{v0[q].x, v0[q].y, v0[q].z, v0[q].w, v1[q].x, v1[q].y},
-                                   (pxb + (float)((q & 1) * 8)) - uv.x, (pyb + (float)((q >> 1) * 8)) - uv.y, c2, up[q],
-                                   gr, gz);
-                }
-                reduce_record(s, j, gr, gz, lane, slot);
-            }
+            if (b + wave < cnt) tile_sums<EXT, R>(s, S.terms, b + wave, wave, live_of, pxb, pyb, c2, up, lane, slot);
             __syncthreads();
         }
         if (wave == 0) write_batch(a, s, lane, cnt);
@@ -1023,8 +1046,7 @@ __device__ __forceinline__ bool bwd_split_tile(const RenderArgs& a, uint32_t t, 
 template <bool EXT, uint32_t R>
 struct BwdPipe {
     BwdStage<EXT> s[2];
-    float4 v0[2][R][4][64];  // as BwdSplit, of even and odd rounds
-    float2 v1[2][R][4][64];
+    BwdTerms<R> terms[2];  // of even and odd rounds
     uint64_t live[2][4];
     uint32_t maxnc[4];
     bool odd;
@@ -1033,8 +1055,7 @@ struct BwdPipe {
 template <bool EXT, uint32_t R>  // R records per round
 __global__ __launch_bounds__(512) void k_render_bwd16_pipe(RenderArgs a) {
     constexpr int NP = GESR_PARTIAL_FLOATS;
-    constexpr uint32_t GRP = 2;                       // side by side in phase 1
-    constexpr uint32_t kRounds = kBwdBatch / R;       // rounds of a full batch
+    constexpr uint32_t kRounds = kBwdBatch / R;  // rounds of a full batch
     __shared__ BwdPipe<EXT, R> S;
     const uint32_t t = a.worklist[blockIdx.x];
     const uint32_t w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = w8 & 3u;
@@ -1106,46 +1127,11 @@ __global__ __launch_bounds__(512) void k_render_bwd16_pipe(RenderArgs a) {
             const uint32_t hi = top - k * kBwdBatch;  // not used past the last round
             if (i < rounds) {
                 if (b == 0) {
-                    bool can = false;
-                    if (lane < hi - r0 && hi - 1u - lane - r0 < wmax) {
-                        const float4 la = s.a[lane];
-                        can = !quad_misses(la, s.b[lane], qx - la.x, (qx + 7.0f) - la.x, qy - la.y, (qy + 7.0f) - la.y);
-                    }
-                    live = __ballot(can);
+                    live = quad_records(s, lane, hi - r0, wmax, qx, qy);
                     if (lane == 0) S.live[k & 1][wave] = live;
                 }
-                uint32_t m = (uint32_t)(live >> b) & ((1u << R) - 1u);
-                while (m != 0u) {
-                    uint32_t e[GRP];
-                    bool have[GRP];
-#pragma unroll
-                    for (uint32_t u = 0; u < GRP; ++u) {  // past the last record: that one again, off
-                        have[u] = m != 0u;
-                        e[u] = have[u] ? (uint32_t)__builtin_ctz(m) : e[u > 0 ? u - 1 : 0];
-                        m = have[u] ? m & (m - 1) : 0u;
-                    }
-                    Fragment f[GRP];
-                    bool on[GRP];
-#pragma unroll
-                    for (uint32_t u = 0; u < GRP; ++u) {
-                        const float4 rb = s.b[b + e[u]];
-                        const float qq = ges_q(s.a[b + e[u]], rb.x, px, py, f[u]);
-                        on[u] = (int)(hi - 1u - (b + e[u]) - r0 < nc) & (int)!(qq > rb.w) & (int)have[u];
-                        // q = 1 where the fragment is not the pixel's: its terms are exact zeros
-                        ges_alpha(on[u] ? qq : 1.0f, rb.z, rb.y, nk, amax, f[u]);
-                    }
-#pragma unroll
-                    for (uint32_t u = 0; u < GRP; ++u) {
-                        const float4 rc = s.c[b + e[u]];
-                        float aT, dl;
-                        pixel_step<EXT, false>(f[u], on[u], rc, EXT ? s.z[b + e[u]] : 0.0f, st, mine, pa, aT, dl);
-                        if (have[u]) {
-                            const FragmentTerms v = fragment_terms(f[u], rc.w, aT, dl);
-                            S.v0[i & 1][e[u]][wave][lane] = make_float4(v.aT, v.dl, v.G, v.xl);
-                            S.v1[i & 1][e[u]][wave][lane] = make_float2(v.tq, v.wq);
-                        }
-                    }
-                }
+                quad_terms<EXT, R>(st, s, b, (uint32_t)(live >> b) & ((1u << R) - 1u), hi - r0, nc, px, py, amax, nk, mine,
+                                   pa, wave, lane, S.terms[i & 1]);
             }
             // the stage's last use, by batch k - 1, ended with the step before
             if (w8 == 0 && b == 2u * R && (k + 1u) * kBwdBatch < total) {
@@ -1163,35 +1149,9 @@ __global__ __launch_bounds__(512) void k_render_bwd16_pipe(RenderArgs a) {
                     for (int q = 0; q < 4; ++q) live_of[q] = read_lane(own, q);
                 }
 #pragma unroll 1
-                for (uint32_t c = wave; c < R; c += 4u) {
-                    const uint32_t j = b + c;
-                    if (k * kBwdBatch + j >= total) {
-                    } else if (((live_of[0] | live_of[1] | live_of[2] | live_of[3]) >> j & 1u) == 0u) {
-                        if ((int)lane < (EXT ? NP + 1 : NP)) s.red[j][lane] = 0.f;
-                    } else {
-                        const float2 uv = make_float2(s.a[j].x, s.a[j].y);
-                        float gr[NP], gz = 0.0f;
-                        // all reads in flight together (a quadrant without the record holds stale terms: not added)
-                        float4 v0[4];
-                        float2 v1[4];
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            v0[q] = S.v0[p & 1][c][q][lane];
-                            v1[q] = S.v1[p & 1][c][q][lane];
-                        }
-#pragma unroll
-                        for (int n = 0; n < NP; n += 2) opaque_zero2(gr[n], gr[n + 1]);
-                        if (EXT) gz = opaque_zero();
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            if (!(live_of[q] >> j & 1u)) continue;
-                            add_terms<EXT>(FragmentTerms{v0[q].x, v0[q].y, v0[q].z, v0[q].w, v1[q].x, v1[q].y},
-                                           (pxb + (float)((q & 1) * 8)) - uv.x, (pyb + (float)((q >> 1) * 8)) - uv.y, c2,
-                                           up[q], gr, gz);
-                        }
-                        reduce_record(s, j, gr, gz, lane, slot);
-                    }
-                }
+                for (uint32_t c = wave; c < R; c += 4u)
+                    if (k * kBwdBatch + b + c < total)
+                        tile_sums<EXT, R>(s, S.terms[p & 1], b + c, c, live_of, pxb, pyb, c2, up, lane, slot);
             }
             // batch k - 1's last round was summed in the step before
             if (w8 == 4 && i % kRounds == 1u && i > kRounds) write_batch(a, S.s[(i / kRounds - 1u) & 1u], lane, kBwdBatch);

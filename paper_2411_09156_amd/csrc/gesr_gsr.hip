@@ -514,28 +514,28 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
     const bool with_part = a.partials != nullptr;
     if (in && !on) *reinterpret_cast<float4*>(a.sample_out + (size_t)j * 4) = make_float4(0.f, 0.f, -1.f, 0.f);
     const uint32_t* row = a.knn + (size_t)j * K;
-    // A wave without a sample that is on writes its zero records and ends; the other
-    // waves' lanes that are off take no neighbours, so that their frames are not gathered
-    // (500,000 samples: all off 34 us, with gradients 362; 114 and 434 when they went
-    // through the passes; a tenth on at random 76 us without gradients, 114).
-    if (__ballot(on) == 0ull) {
-        if (with_part)
-            for (int s = 0; s < K; ++s) {
-                const uint32_t slot = in && row[s] < (uint32_t)a.n ? a.inv_slot[(size_t)p * K + s] : 0xFFFFFFFFu;
-                const uint4 to = quad_all(slot);
-                const auto zero = [&](uint32_t t) {
-                    if (t != 0xFFFFFFFFu)
-                        __builtin_nontemporal_store(f32x4{0.f, 0.f, 0.f, 0.f},
-                                                    reinterpret_cast<f32x4*>(a.partials + (size_t)t * GSR_PARTIAL_STRIDE) +
-                                                        (threadIdx.x & 3u));
-                };
-                zero(to.x);
-                zero(to.y);
-                zero(to.z);
-                zero(to.w);
-            }
-        return;
+    // Samples that are off leave zero records and take no neighbours, so that their frames
+    // are not gathered; a wave with no other sample ends (500,000 samples: all off 34 us,
+    // with gradients 358; 114 and 434 when they went through the passes; a tenth on at
+    // random 76 us without gradients, 114).
+    if (with_part && __ballot(in && !on) != 0ull) {
+        const uint32_t* place = a.inv_slot + (size_t)(in ? p : 0u) * K;
+        for (int s = 0; s < K; ++s) {
+            const uint32_t at = place[s];  // (no place where the list is padded)
+            const uint4 to = quad_all(in && !on && row[s] < (uint32_t)a.n ? at : 0xFFFFFFFFu);
+            const auto zero = [&](uint32_t t) {
+                if (t != 0xFFFFFFFFu)
+                    __builtin_nontemporal_store(
+                        f32x4{0.f, 0.f, 0.f, 0.f},
+                        reinterpret_cast<f32x4*>(a.partials + (size_t)t * GSR_PARTIAL_STRIDE) + (threadIdx.x & 3u));
+            };
+            zero(to.x);
+            zero(to.y);
+            zero(to.z);
+            zero(to.w);
+        }
     }
+    if (__ballot(on) == 0ull) return;
     {
         const uint32_t none = on ? 0u : 0xFFFFFFFFu;
 #pragma unroll 8
@@ -654,9 +654,8 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
         if (s > 0) next.load(a.frames, quad_at(s - 1), last);
         // the partial of slot s goes to record inv_slot[p * k + s]: each splat's
         // records end up contiguous, in inverse-list order (padding slots have none, and
-        // their frame's terms stay out of the sample point's gradient); a sample that is off
-        // leaves zeros
-        const bool valid = i < (uint32_t)a.n || (in && !on && row[s] < (uint32_t)a.n);
+        // their frame's terms stay out of the sample point's gradient)
+        const bool valid = i < (uint32_t)a.n;
         const uint32_t slot = valid ? a.inv_slot[(size_t)p * K + s] : 0xFFFFFFFFu;
         const Term t = eval_term(f, f0.mu, d0, kappa);
         // b = diag(1/sig) R^T u, scaled by gmax like u
@@ -720,10 +719,9 @@ __global__ __launch_bounds__(128) void k_gsr_loss(GsrArgs a) {
         // lane so that neither side meets its banks twice.
         const uint32_t l4 = threadIdx.x & 3u, rot = (threadIdx.x >> 2) & 3u;
         f32x4* mine = stage + __lane_id() * 4u;
-        mine[rot] = on ? f32x4{g_mu[0], g_mu[1], g_mu[2], f.phi * g_sig[0]} : f32x4{0.f, 0.f, 0.f, 0.f};
-        mine[1u ^ rot] =
-            on ? f32x4{f.phi * g_sig[1], f.phi * g_sig[2], g_q[0], g_q[1]} : f32x4{0.f, 0.f, 0.f, 0.f};
-        mine[2u ^ rot] = on ? f32x4{g_q[2], g_q[3], g_o, g_beta} : f32x4{0.f, 0.f, 0.f, 0.f};
+        mine[rot] = f32x4{g_mu[0], g_mu[1], g_mu[2], f.phi * g_sig[0]};
+        mine[1u ^ rot] = f32x4{f.phi * g_sig[1], f.phi * g_sig[2], g_q[0], g_q[1]};
+        mine[2u ^ rot] = f32x4{g_q[2], g_q[3], g_o, g_beta};
         mine[3u ^ rot] = f32x4{__uint_as_float(slot), 0.f, 0.f, 0.f};
         wave_lds_fence();
         const f32x4* quad = stage + (__lane_id() & ~3u) * 4u;

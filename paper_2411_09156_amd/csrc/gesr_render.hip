@@ -876,6 +876,7 @@ __device__ __forceinline__ void quad_terms(const DevSettings& st, const BwdStage
                                            const PixelUp& mine, PixelAdjoint& pa, uint32_t quad, uint32_t lane,
                                            BwdTerms<R>& terms) {
     constexpr uint32_t GRP = 2;  // records side by side
+    const uint32_t top = left - 1u - b;
     while (m != 0u) {
         uint32_t k[GRP];
         bool have[GRP];
@@ -891,7 +892,7 @@ __device__ __forceinline__ void quad_terms(const DevSettings& st, const BwdStage
         for (uint32_t u = 0; u < GRP; ++u) {
             const float4 rb = s.b[b + k[u]];
             const float qq = ges_q(s.a[b + k[u]], rb.x, px, py, f[u]);
-            on[u] = (int)(left - 1u - (b + k[u]) < nc) & (int)!(qq > rb.w) & (int)have[u];
+            on[u] = (int)(top - k[u] < nc) & (int)!(qq > rb.w) & (int)have[u];
             // q = 1 where the fragment is not the pixel's: its terms are exact zeros
             ges_alpha(on[u] ? qq : 1.0f, rb.z, rb.y, nk, amax, f[u]);
         }
@@ -1226,10 +1227,12 @@ uint32_t fwd_split_tiles(uint32_t n_items) { return n_items <= 8192u ? n_items :
 // With four waves each: all of them up to 5,500, where one-wave tiles would fill the
 // chip's wave slots about once and the kernel would last as long as its longest list
 // (one wave takes 300 ns per list position): 360 -> 218 us on 3,024; 198 -> 134 on 4,347,
-// 196 -> 162 on 5,292; 185 -> 186 on 5,922, 194 -> 202 on 6,700.  Beyond, the worklist's
-// first 256 as long as another tile does not hide the longest lists; the others of a
-// workgroup's four waves then take a tile each, and free their slots together, which
-// costs 2 to 5% on even lists (with the channels 4 to 7%):
+// 196 -> 162 on 5,292; 185 -> 186 on 5,922, 194 -> 202 on 6,700; up to 4,096 where one
+// view has four times another's pixels and the longest lists are few (5,326 tiles of
+// views at 1/8 .. 1 of 1468x334: 1,286 us, 1,238 with the worklist's first 256).
+// Beyond, those 256 as long as another tile does not hide the longest lists; the others
+// of a workgroup's four waves then take a tile each, and free their slots together,
+// which costs 2 to 5% on even lists (with the channels 4 to 7%):
 //  - Up to 32,768 tiles: 11,442 tiles of views at 1/8 .. 3/4 of 1600x1064 286 us and 693
 //    (one-wave workgroups 535, 1,160), 24,842 at 1/8 .. 1 469 and 655 (565, 1,118); even
 //    views 9,500 tiles 312 (316), 15,200 of 400x300 349 (376) and of 800x600 453 (440),
@@ -1242,7 +1245,7 @@ uint32_t fwd_split_tiles(uint32_t n_items) { return n_items <= 8192u ? n_items :
 //    12,288 tiles (9,500 404 us, 467; 10,332 364, 377; 13,400 463, 443; 20,100 720, 681;
 //    30,400 1,097, 1,026).
 constexpr uint32_t kBwdPipeMax = 2048u, kBwdPipe8Max = 512u;
-constexpr uint32_t kBwdSplitAllMax = 5500u, kBwdSplit = 256u;
+constexpr uint32_t kBwdSplitAllMax = 5500u, kBwdSplitAllSkewMax = 4096u, kBwdSplit = 256u;
 constexpr uint32_t kBwdMixedMax = 32768u, kBwdMixedExtMax = 12288u, kBwdMixedExtSkewMax = 28672u;
 
 bool views_skewed(const DevCams& c) {
@@ -1306,8 +1309,8 @@ hipError_t launch_render_bwd(const RenderArgs& a, int tw, int th, int batch, hip
             }
             return hipGetLastError();
         }
-        const uint32_t mixed_max =
-            !ext ? kBwdMixedMax : (views_skewed(a.cams) ? kBwdMixedExtSkewMax : kBwdMixedExtMax);
+        const bool skewed = views_skewed(a.cams);
+        const uint32_t mixed_max = !ext ? kBwdMixedMax : (skewed ? kBwdMixedExtSkewMax : kBwdMixedExtMax);
         if (a.n_items > mixed_max) {
             const dim3 grid(a.n_items), block(64);
             if (ext) hipLaunchKernelGGL((k_render_bwd16_wave<true>), grid, block, 0, s, a);
@@ -1315,7 +1318,7 @@ hipError_t launch_render_bwd(const RenderArgs& a, int tw, int th, int batch, hip
             return hipGetLastError();
         }
         RenderArgs b = a;
-        b.n_split = a.n_items <= kBwdSplitAllMax ? a.n_items : kBwdSplit;
+        b.n_split = a.n_items <= (skewed ? kBwdSplitAllSkewMax : kBwdSplitAllMax) ? a.n_items : kBwdSplit;
         const dim3 grid(b.n_split + (a.n_items - b.n_split + 3) / 4), block(256);
         if (ext) hipLaunchKernelGGL((k_render_bwd16<true>), grid, block, 0, s, b);
         else hipLaunchKernelGGL((k_render_bwd16<false>), grid, block, 0, s, b);

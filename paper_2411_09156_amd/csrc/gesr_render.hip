@@ -140,13 +140,15 @@ __device__ __forceinline__ void pixel_step(const Fragment& f, bool on, const flo
     px.T *= hw_rcp(1.0f - al);
     aT = al * px.T;
     const float er = rc.x - px.Br, eg = rc.y - px.Bg, eb = rc.z - px.Bb;
-    float dLda = px.T * fmaf(eb, u.g2, fmaf(er, u.g0, eg * u.g1));
+    const float colour = fmaf(eb, u.g2, fmaf(er, u.g0, eg * u.g1));
+    float dLda = px.T * colour;
     px.Br = fmaf(al, er, px.Br);
     px.Bg = fmaf(al, eg, px.Bg);
     px.Bb = fmaf(al, eb, px.Bb);
     if (EXT) {
         const float ed = z - px.BD, ea = 1.0f - px.BA;
-        dLda = fmaf(px.T, fmaf(ed, u.gD, ea * u.gA), dLda);
+        // (the channels' product is the rounded one)
+        dLda = fmaf(px.T, colour, px.T * fmaf(ed, u.gD, ea * u.gA));
         px.BD = fmaf(al, ed, px.BD);
         px.BA = fmaf(al, ea, px.BA);
     }

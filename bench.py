@@ -41,15 +41,15 @@ HBM_BYTES_PER_S = 8.0e12
 
 # Algorithmic VALU slots per fragment (see the design notes for the count):
 #   forward : 8 per listed fragment, +18 per hit (3 transcendentals x 2)
-#   backward: 9 per listed fragment, +48 per hit (5 transcendentals x 2, sums fused
-#             into multiply-adds)
+#   backward: 9 per listed fragment, +45 per hit (5 transcendentals x 2, sums fused
+#             into multiply-adds; what is the splat's own enters once per tile)
 FWD_LISTED, FWD_HIT = 8, 18
-BWD_LISTED, BWD_HIT = 9, 48
+BWD_LISTED, BWD_HIT = 9, 45
 # with the extended depth and alpha channels (--channels): the forward adds one
 # depth multiply-add per hit; the adjoint adds the two channels' dL/dalpha terms
 # (2 differences, a multiply and 2 multiply-adds), the dz term and the two
 # behind-accumulator updates (8)
-FWD_HIT_CHANNELS, BWD_HIT_CHANNELS = 19, 56
+FWD_HIT_CHANNELS, BWD_HIT_CHANNELS = 19, 53
 # surface points (--surface): per (candidate splat, sample) the affine Mahalanobis
 # vector and its square (6 multiply-adds), log2, scale, exp2, scale, exp2
 # (3 transcendentals x 2 + 2), the opacity and the accumulation: 16 slots
@@ -62,7 +62,7 @@ SURFACE_SLOTS_PER_SAMPLE = 16
 # projection and binning that build the records and tile lists it walks, and the
 # record layout); otherwise null.
 MEASURED_TRAFFIC = {"kernel": "render_bwd_tiles", "workload": "drt-batch-500k-8views",
-                    "fingerprint": "5ab1904e335d3075", "bytes": 1935899691,
+                    "fingerprint": "f5a50a83356cb6bb", "bytes": 1935377593,
                     "settings": (16, 16, 0, 64)}  # tile_w, tile_h, variant, batch of the measured run
 
 
